@@ -87,7 +87,7 @@ def parse():
     return ap.parse_args()
 
 
-KERNEL_SOURCES = ["dfb_kernels.hip", "dfb_internal.h", "sortnet.h"]
+KERNEL_SOURCES = ["dfb_kernels.hip", "dfb_internal.h", "rowsort.h", "sortnet.h"]
 
 
 def kernel_source_hash():

@@ -342,7 +342,7 @@ dfb_status dfb_validate_layers(const dfb_config* cfg, int64_t n_blocks, const df
  * dfb_composite_frame, without accumulation -- into caller-owned outputs.
  * It calls no allocator: its work queue's counters, the frame state and the
  * longest-first work list (built on the device from tile_off_dev) live in a
- * static device array of DFB_NOALLOC_MAX_WORK work units plus 72 KiB, one
+ * static device array of DFB_NOALLOC_MAX_WORK work units plus 208 KiB, one
  * per GPU, held until the process ends; the first call on a device clears
  * it (a fill kernel on hip_stream).  All calls on one GPU share that array:
  * calls that overlap in time on one GPU (different streams or threads)

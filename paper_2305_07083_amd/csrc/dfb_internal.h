@@ -11,8 +11,13 @@ namespace dfb {
 // Layers per tile handled by the register sort; above it, the workgroup-wide
 // LDS sort takes over.
 constexpr int kRegMax = 32;
-// Largest layer count per tile the LDS sort supports (keys + weights of one
-// pixel must fit the LDS budget below).
+// Layers per tile handled by the row sort (16 lanes of a wave sort a pixel in
+// registers); tiles with more, up to kMaxLayers, take the LDS sort.
+// 512: their 32 keys a lane and 74 KB of alphas still leave two workgroups
+// to a compute unit.
+constexpr int kDeepMax = 512;
+constexpr int kDeepThreads = 512;
+constexpr int kDeepPx = 32;  // pixels of a row-sort group: one 128-byte line of an fp32 plane
 // Work queue: the work list is dealt round-robin to kQueues counters, each
 // in its own 4 KB page, served first by the workgroups with the same index
 // mod kQueues, so same-address atomics do not serialise the whole chip.
@@ -20,15 +25,16 @@ constexpr int kRegMax = 32;
 // slot f mod kSlots and clears slot (f + kSlots/2) mod kSlots, which no
 // frame in flight uses, so nothing is reset between frames.  A ring is the
 // kQueues counter pages and one page of per-slot "workgroups finished"
-// counters.  A frame with tiles of more than kRegMax layers runs two
-// launches over the same work list -- the K > kRegMax tiles, then the rest
-// -- each with a ring of its own; after the two rings comes one page
+// counters.  A frame runs up to three launches over the same work list --
+// the tiles of more than kDeepMax layers, those of more than kRegMax, then
+// the rest -- each with a ring of its own; after the rings comes one page
 // holding the FrameState below.
 constexpr int kQueues = 16;
 constexpr int kQueueStride = 1024;  // 4-byte counters between queues
 constexpr int kSlots = 64;
 constexpr int kRingWords = (kQueues + 1) * kQueueStride;
-constexpr int kQueueWords = 2 * kRingWords + kQueueStride;  // the whole allocation, in u32
+constexpr int kRings = 3;
+constexpr int kQueueWords = kRings * kRingWords + kQueueStride;  // the whole allocation, in u32
 
 // Per-handle frame state in device memory.  Kernels read it at their start
 // and the last workgroup of a frame advances it, so a launch carries no
@@ -38,14 +44,14 @@ struct FrameState {
   uint32_t seq;    // frames so far: selects the counter slot
   int32_t n_acc;   // frames folded into the running mean since the reset
 };
-// Ring r (0: the register-path launch, 1: the K > kRegMax launch) and the
-// frame state inside a queue allocation.
+// Ring r (0: the register-path launch, 1: the LDS sort's, 2: the row sort's)
+// and the frame state inside a queue allocation.
 inline uint32_t* ring_of(uint32_t* queue_base, int r) { return queue_base + r * kRingWords; }
 inline FrameState* state_of(uint32_t* queue_base) {
-  return reinterpret_cast<FrameState*>(queue_base + 2 * kRingWords);
+  return reinterpret_cast<FrameState*>(queue_base + kRings * kRingWords);
 }
 constexpr int kMaxLayers = 4096;
-// Largest LDS budget of the large-K path for keys (u64) and weights (f32);
+// Largest LDS budget of the LDS sort for keys (u64) and weights (f32);
 // the host passes 64, 96 or 112 KB depending on the frame's largest tile.
 constexpr int kBigLdsBytes = 112 * 1024;
 
@@ -71,6 +77,7 @@ struct FrameArgs {
   const void* frag;            // fragment blocks (caller's buffer)
   uint32_t* queue;             // this launch's ring: kQueues x kSlots counters, queues
                                // kQueueStride apart, then the kSlots finish counters
+  uint32_t* rings;             // all kRings rings (the last launch recycles a slot of each)
   FrameState* state;           // the frame state (shared by the frame's launches)
   int32_t advance;             // 1: the last workgroup advances the state (the frame's last launch)
   int32_t slot, clear_slot;    // set by the kernel from FrameState::seq
@@ -81,8 +88,12 @@ struct FrameArgs {
   int32_t tile_w, tile_h, P;
   int32_t work_w, work_h, subs_x, subs_per_tile, work_px;
   int32_t work_shift;          // log2(work_w) if a power of two, else -1
-  int32_t big_lds;             // LDS bytes for keys + weights of the K > 32 path
+  int32_t big_lds;             // LDS bytes for keys + weights of the LDS sort
   int32_t vec_ok;              // 16-byte plane loads possible (alignment, work_w, tile_w)
+  int32_t deep_px, deep_subs;  // row-sort launch: pixels per unit, units per tile
+  int32_t deep_layers;         // row-sort launch: layers its LDS holds
+  int32_t quad_ok;             // 4-pixel plane loads are aligned: the row sort can run
+  int32_t big_min;             // LDS sort: it takes the tiles of more layers than this
   float bg[4];
   const float* bg_image;       // [n_tiles][P][4] per-pixel background, or null
   float inv_gamma;
@@ -94,6 +105,7 @@ struct FrameArgs {
   float* m2;                   // [n_tiles][3][P]
   float* tile_var;             // [n_tiles]
   float* var_partial;          // [n_work] M2 sum of each unit (accumulating frames)
+  float* deep_partial;         // [n_tiles * deep_subs] the same of the row-sort units
   void* final_out;             // RGBA8 uint32[n_tiles][P] or float4[n_tiles][P]
   uint16_t* order;             // [n_layers][P]
 };
@@ -112,6 +124,9 @@ struct AccumArgs {
 
 struct VarianceArgs {
   const float* var_partial;    // [n_tiles * subs_per_tile]
+  const float* deep_partial;   // [n_tiles * deep_subs]: the tiles of kRegMax + 1 .. kDeepMax layers
+  const int32_t* tile_off;
+  int32_t deep_subs;           // 0: the frame has no such tiles
   float* tile_var;             // [n_tiles]
   int32_t n_tiles, subs_per_tile, tiles_x, width, height, tile_w, tile_h;
   const FrameState* state;     // n = state->n_acc (already advanced by the frame kernel)
@@ -145,10 +160,16 @@ dfb_status frame_view(dfb_ctx* h, FrameView* out, bool want_denoised);
 // The persistent frame kernel for a fragment dtype, register-sort capacity
 // and tile operation (dfb_tile_op).  dtype: 0 f32, 1 f16.  kcap 8, 16 or 32:
 // the per-pixel sort of tiles with at most kcap layers in registers (tiles
-// with more are left to the kcap 0 kernel); kcap 0 (ALPHA_BLEND only): the
-// workgroup-wide LDS sort of the tiles with more than kRegMax layers, others
+// with more are left to the other launches); kcap 0 (ALPHA_BLEND only): the
+// workgroup-wide LDS sort of the tiles with more than kDeepMax layers, others
 // left alone.
 const void* frame_kernel(int dtype, int kcap, int op);
+// The row sort of the tiles with kRegMax + 1 .. kDeepMax layers
+// (ALPHA_BLEND), others left alone, and its dynamic LDS; kDeepThreads lanes.
+const void* deep_kernel(int dtype, int max_layers);
+size_t deep_lds_bytes(int max_layers);
+// Layers of a row-sort tile its LDS is sized for (even: what follows stays 16-byte aligned).
+inline int deep_layers(int max_layers) { return ((max_layers < kDeepMax ? max_layers : kDeepMax) + 1) & ~1; }
 // Largest-remainder assignment of extra samples (host; dfb_assign_samples_host).
 dfb_status assign_samples(const float* variance, int32_t n_tiles, int64_t extra, int32_t* counts);
 const void* accumulate_kernel();
@@ -163,7 +184,7 @@ const void* lpt_work_kernel();
 constexpr int kLptThreads = 1024;
 const void* validate_kernel(int dtype);
 
-// LDS budget of the K > 32 path for a frame whose largest tile has
+// LDS budget of the LDS sort for a frame whose largest tile has
 // max_layers layers, and the dynamic LDS bytes a frame launch needs (kcap as
 // for frame_kernel).
 int big_lds_bytes(int max_layers);

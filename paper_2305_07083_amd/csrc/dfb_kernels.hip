@@ -1,12 +1,12 @@
 // gfx950 kernels of the per-tile sort-last compositor.
 //
-// One persistent launch per frame.  Each workgroup (64 * waves_per_tile lanes)
-// repeatedly takes a work unit -- a work_w x work_h rectangle of one DFB tile
+// One to three persistent launches per frame (by the layer counts of its
+// tiles).  Each workgroup (64 * waves_per_tile lanes) repeatedly takes a work unit -- a work_w x work_h rectangle of one DFB tile
 // -- from a device queue ordered longest tile first, and for every pixel of it
 //   1. builds the key (ordered depth bits << 32 | layer index) of each of the
 //      tile's K layers from coalesced SoA depth loads, staging alpha in LDS,
-//   2. sorts the keys (registers for K <= 32, an LDS bitonic sort shared by
-//      the workgroup for larger K),
+//   2. sorts the keys (a lane's registers for K <= 32, the registers of 16
+//      lanes for K <= 512, an LDS bitonic sort shared by the workgroup above),
 //   3. walks the sorted keys front to back computing the transmittance T in
 //      front of each layer ("over", Sec. 4.2 of the paper) and writes it back
 //      into the layer's LDS slot,
@@ -22,6 +22,7 @@
 #include <stdint.h>
 
 #include "dfb_internal.h"
+#include "rowsort.h"
 #include "sortnet.h"
 
 namespace dfb {
@@ -49,11 +50,11 @@ namespace {
 #ifndef DFB_UPFRONT_MAX
 #define DFB_UPFRONT_MAX 0
 #endif
-// Streaming (non-temporal) loads in the K > 32 path too (1), or ordinary
-// loads (0, the default): those leave a line in L2 for the pixel group that
-// reads its other half (a group of 16 or fewer fp32 pixels covers half a
-// 128-byte line or less); on the 8192^2 heavy-tailed frame 36.5 against
-// 38.6 ms.
+// Streaming (non-temporal) loads in the LDS sort too (1), or ordinary loads
+// (0, the default): those leave a line in L2 for the pixel group that reads
+// its other half (a group of 16 or fewer fp32 pixels covers half a 128-byte
+// line or less); 36.5 against 38.6 ms on the 8192^2 heavy-tailed frame when
+// this sort took all its tiles of more than 32 layers.
 #ifndef DFB_BIGK_NT
 #define DFB_BIGK_NT 0
 #endif
@@ -729,8 +730,9 @@ __device__ float unit_average(const FrameArgs& a, const Unit& u, const int64_t* 
   return vs;
 }
 
-// ---------------------------------------------------------------- K > 32
-// The workgroup handles G pixels at a time.  LDS holds one row per pixel:
+// --------------------------------------------------------------- K > 512
+// (and K > 32 where the planes are not 4-pixel aligned: the row sort below
+// takes the others.)  The workgroup handles G pixels at a time.  LDS holds one row per pixel:
 // Kp keys (u64) and, in a second array of the same shape, Kp floats (alpha,
 // later the transmittance T); and the unit's layer offsets.  Position i of a
 // row is stored at i + i/16 (one pad slot per 16) and rows are
@@ -774,9 +776,10 @@ constexpr int kBlk = 1 << kBlkLog;
 #endif
 // Layers per lane whose depth and alpha loads are in flight together past
 // the first kBigC, and layers per lane whose colour loads are in flight
-// together after the walk.  On the 8192^2 heavy-tailed frame (16, 16, 8)
-// takes 34.4 ms against 35.7 ms for (8, 8, 4); larger batches of depth and
-// alpha past the first 8 layers were slower (24, 24: 38.0-38.1 ms).
+// together after the walk.  On the 8192^2 heavy-tailed frame, then sorted here
+// whole, (16, 16, 8) took 34.4 ms against 35.7 ms for (8, 8, 4); larger
+// batches of depth and alpha past the first 8 layers were slower (24, 24:
+// 38.0-38.1 ms).
 #ifndef DFB_BIG_FILL
 #define DFB_BIG_FILL 16
 #endif
@@ -789,7 +792,7 @@ constexpr int kBigC = DFB_BIG_C;
 
 __device__ __forceinline__ int kslot(int i) { return i + (i >> 4); }
 
-// Plane loads of the K > 32 path.
+// Plane loads of the LDS sort.
 template <typename FT>
 __device__ __forceinline__ float ldb(const FT* __restrict__ base, uint32_t i) {
 #if DFB_BIGK_NT
@@ -1226,8 +1229,35 @@ __device__ __forceinline__ uint32_t read_frame_state(FrameArgs& a, uint32_t* s_s
   return seq;
 }
 
-// KCAP 8, 16, 32: register-sort capacity (tiles with more layers are the
-// KCAP 0 launch's); KCAP 0: only the tiles with more than kRegMax layers.
+// Recycle the slot of the frame kSlots/2 ahead (counters, finish counts) in
+// every ring.  The frame's last launch does it for all of them: a frame of
+// another layer layout may not run the other launches, and a slot left
+// uncleared would hand out no units kSlots frames later.
+__device__ __forceinline__ void recycle_slots(const FrameArgs& a, int tid) {
+  if (tid < kRings * (kQueues + 1))  // at most 51 words, by the first wave
+    __hip_atomic_store(a.rings + static_cast<size_t>(tid) * kQueueStride + a.clear_slot, 0u, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Count a workgroup finished (thread 0); the last workgroup of the frame's
+// last launch advances the frame state for the next frame (sequence number,
+// and the accumulation count of an accumulating frame).  Every queue access
+// of the workgroup has returned its value before this point.
+__device__ __forceinline__ void finish_workgroup(const FrameArgs& a, uint32_t seq, bool wave0) {
+  const int tid = threadIdx.x;
+  uint32_t done = 0;
+  if (tid == 0)
+    done = __hip_atomic_fetch_add(finish_counters(a) + a.slot, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  done = __builtin_amdgcn_readfirstlane(done);
+  const bool last = a.advance && wave0 && done == gridDim.x - 1;
+  if (last && tid == 0)
+    __hip_atomic_store(&frame_state(a)->seq, seq + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (last && tid == 0 && (a.mode & kModeAccumulate))
+    __hip_atomic_store(&frame_state(a)->n_acc, a.n_acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// KCAP 8, 16, 32: register-sort capacity (tiles with more layers are other
+// launches'); KCAP 0: only the tiles with more than a.big_min layers.
 template <typename FT, int KCAP, int OP>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(min_waves(KCAP, sizeof(FT) == 2))))
 frame_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off,
@@ -1241,9 +1271,7 @@ frame_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off,
   const bool wave0 = __builtin_amdgcn_readfirstlane(tid) < 64;  // uniform per wave
   FrameArgs a = args;
   const uint32_t seq = read_frame_state(a, s_state);
-  if (blockIdx.x == 0 && tid <= kQueues)  // recycle the slot of the frame kSlots/2 ahead (counters, finish count)
-    __hip_atomic_store(a.queue + static_cast<size_t>(tid) * kQueueStride + a.clear_slot, 0u, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
+  if (a.advance && blockIdx.x == 0) recycle_slots(a, tid);
   const int home = static_cast<int>(blockIdx.x) % a.n_queues;
   Queue q = queue_of(a, home);
   int drained = 0;  // counters this workgroup has found empty
@@ -1267,7 +1295,7 @@ frame_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off,
     float vs = 0.f;
     bool mine = true;  // uniform: this launch composites the unit
     if constexpr (KCAP == 0) {
-      mine = K > kRegMax;
+      mine = K > a.big_min;
       if (mine) vs = unit_bigk<FT>(a, u, blk, K, off, lds);
     } else if constexpr (OP == DFB_OP_AVERAGE) {
       vs = (a.vec_ok && K > 0) ? unit_average_vec<FT>(a, u, blk, K) : unit_average<FT>(a, u, blk, K);
@@ -1313,19 +1341,325 @@ frame_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off,
     lds_barrier();
     it = __builtin_amdgcn_readfirstlane(s_item);
   }
-  // Count this workgroup finished; the last one advances the frame state
-  // for the next launch (sequence number, and the accumulation count of an
-  // accumulating frame).  Every queue access of this workgroup has returned
-  // its value before this point.
-  uint32_t done = 0;
-  if (tid == 0)
-    done = __hip_atomic_fetch_add(finish_counters(a) + a.slot, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  done = __builtin_amdgcn_readfirstlane(done);
-  const bool last = a.advance && wave0 && done == gridDim.x - 1;
-  if (last && tid == 0)
-    __hip_atomic_store(&frame_state(a)->seq, seq + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (last && tid == 0 && (a.mode & kModeAccumulate))
-    __hip_atomic_store(&frame_state(a)->n_acc, a.n_acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  finish_workgroup(a, seq, wave0);
+}
+
+// ------------------------------------------------- 32 < K <= 512: row sort
+// A workgroup of 8 waves takes groups of 32 consecutive pixels of a tile (one
+// 128-byte line of an fp32 plane per layer); each wave sorts 4 of them, 16
+// lanes a pixel, in registers (rowsort.h).
+//   1. depth and alpha rows are loaded, 4 pixels a lane; the depths go through
+//      the LDS array rows[layer][32 pixels] to the lanes that sort them, then
+//      the alphas take their place
+//   2. the row sort
+//   3. the walk: each lane reads its positions' alphas by layer, the lanes'
+//      products are scanned over the row, and the transmittance in front of
+//      every layer replaces its alpha
+//   4. colour rows are loaded and weighted, summed over a lane's layers, over
+//      the lanes and waves of a pixel in a fixed order
+// Every sum is split the same way whatever the launch shape is.
+//
+// Bound by memory: 20 bytes a fragment (fp32), against about 85 vector
+// instructions a key in the sort, which the other workgroup of the compute
+// unit overlaps with its loads.  The LDS sort it replaces for these counts was
+// bound by the latency of its passes at 8 waves a compute unit, and read each
+// 128-byte line twice.  8192^2 heavy-tailed frame (57.9 GB, up to 512 layers):
+// 36.9 -> 15.6 ms a frame; 1500x1100 fp16, up to 128 layers: 504 -> 186 us.
+// Rows are 36 words apart: the 16 lanes of a pixel (at consecutive layers)
+// and the wave's 4 pixels hit all 64 banks once.
+constexpr int kDeepPitch = 36;
+constexpr int kDeepWaves = kDeepThreads / 64;
+constexpr int kDeepRows = kDeepThreads / 8;  // layers loaded per pass: 8 lanes of 4 pixels each
+__host__ __device__ constexpr size_t deep_rows_bytes(int max_layers) {  // one row more: the padding keys' alpha 0
+  return static_cast<size_t>(max_layers + 1) * kDeepPitch * sizeof(float);
+}
+// after the rows and the layer offsets: the waves' colour sums, then the
+// final transmittance and alpha of every pixel
+constexpr size_t kDeepTail = (kDeepWaves * 3 + 2) * kDeepPx * sizeof(float);
+
+// 4 consecutive elements of a plane as they lie in memory.
+template <typename FT>
+struct Quad;
+template <>
+struct Quad<float> {
+  typedef float V __attribute__((ext_vector_type(4)));
+  using RK = RowKey64;
+  static __device__ __forceinline__ float4 f(V v) { return make_float4(v.x, v.y, v.z, v.w); }
+  static __device__ __forceinline__ uint4 bits(V v) { return __builtin_bit_cast(uint4, v); }
+  static __device__ __forceinline__ uint64_t key(uint32_t bits, int l) {
+    return big_key(depth_bits(__uint_as_float(bits)), l);
+  }
+  static constexpr uint32_t kNaN = 0x7FC00000u;
+  static __device__ __forceinline__ int index(uint64_t k) { return key_layer(k); }
+};
+template <>
+struct Quad<_Float16> {
+  typedef _Float16 V __attribute__((ext_vector_type(4)));
+  using RK = RowKey32;
+  static __device__ __forceinline__ float4 f(V v) {
+    return make_float4(static_cast<float>(v.x), static_cast<float>(v.y), static_cast<float>(v.z), static_cast<float>(v.w));
+  }
+  static __device__ __forceinline__ uint4 bits(V v) {
+    const uint2 u = __builtin_bit_cast(uint2, v);
+    return make_uint4(u.x & 0xFFFFu, u.x >> 16, u.y & 0xFFFFu, u.y >> 16);
+  }
+  static __device__ __forceinline__ int32_t key(uint32_t bits, int l) {
+    return static_cast<int32_t>(half_depth_bits(static_cast<uint16_t>(bits)) << 12) | l;
+  }
+  static constexpr uint32_t kNaN = 0x7E00u;
+  static __device__ __forceinline__ int index(int32_t k) { return k & 0xFFF; }
+};
+
+// Pixels p .. p + 3 of a plane (aligned: the host checked P % 4 and the base).
+template <typename FT>
+__device__ __forceinline__ typename Quad<FT>::V load_quad(const FT* __restrict__ plane, int p) {
+  return __builtin_nontemporal_load(reinterpret_cast<const typename Quad<FT>::V*>(plane + p));
+}
+
+// x + the value of the lane 16 (32) lanes away, in both.
+__device__ __forceinline__ float add_xor16(float x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float add_xor32(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float add_xor8(float x) {
+  return x + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x128, 0xf, 0xf, true));  // row_ror:8
+}
+
+// Pixels [p0, p1) of tile u.t, K <= 16 R layers.  Returns the M2 sum (wave 0).
+template <typename FT, int R>
+__device__ __forceinline__ float deep_unit(const FrameArgs& a, const Unit& u, int K_in, int off, int p0, int p1, float* rows,
+                                           const int64_t* lofs, float* red) {
+  using Q = Quad<FT>;
+  using V = typename Q::V;
+  using RK = typename Q::RK;
+  constexpr int NP = (16 * R + kDeepRows - 1) / kDeepRows;  // passes over the layers
+  constexpr int NC = NP % 4 == 0 ? 4 : (NP % 3 == 0 ? 3 : NP);  // passes whose colours are in flight together
+  static_assert(NP % NC == 0, "colour batches");
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, j = lane & 15, px = wave * 4 + (lane >> 4);
+  const int quad0 = (tid & 7) * 4;
+  const int P = a.P;
+  const size_t plane = static_cast<size_t>(P);
+  const FT* __restrict__ frag = static_cast<const FT*>(a.frag);
+  float* tend = red + kDeepWaves * 3 * kDeepPx;
+  float* asum = tend + kDeepPx;
+  float vs = 0.f;
+  for (int g0 = p0; g0 < p1; g0 += kDeepPx) {
+    // past the end of a tile whose last group is ragged: its last pixels again
+    const int pq = g0 + quad0 < P ? g0 + quad0 : P - 4;
+    // Opaque copies, made anew in every group and phase: the addresses and
+    // the l < K masks of a phase are computed there and not kept in registers
+    // across the sort.
+    int K = K_in, row0 = tid >> 3;
+    asm volatile("" : "+s"(K), "+v"(row0));
+    // 1. depth and alpha rows
+    V dv[NP], av[NP];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int l = min(row0 + i * kDeepRows, K - 1);
+      dv[i] = load_quad<FT>(frag + lofs[l] + 4 * plane, pq);
+    }
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int l = min(row0 + i * kDeepRows, K - 1);
+      av[i] = load_quad<FT>(frag + lofs[l] + 3 * plane, pq);
+    }
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int l = min(row0 + i * kDeepRows, K - 1);
+      *reinterpret_cast<uint4*>(rows + l * kDeepPitch + quad0) = Q::bits(dv[i]);
+    }
+    // row K: a NaN depth and alpha 0 for the padding keys, which sort last
+    if (tid < 8) *reinterpret_cast<uint4*>(rows + K * kDeepPitch + quad0) = make_uint4(Q::kNaN, Q::kNaN, Q::kNaN, Q::kNaN);
+    lds_barrier();
+    int jl = j;
+    asm volatile("" : "+s"(K), "+v"(jl));
+    typename RK::K key[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int l = min(r * 16 + jl, K);
+      key[r] = Q::key(__float_as_uint(rows[l * kDeepPitch + px]), l);
+    }
+    lds_barrier();
+    asm volatile("" : "+s"(K), "+v"(row0));
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int l = min(row0 + i * kDeepRows, K - 1);
+      *reinterpret_cast<float4*>(rows + l * kDeepPitch + quad0) = Q::f(av[i]);
+    }
+    if (tid < 8) *reinterpret_cast<float4*>(rows + K * kDeepPitch + quad0) = make_float4(0.f, 0.f, 0.f, 0.f);
+    // 2. sort
+    __builtin_amdgcn_sched_barrier(0);
+    row_sort<RK, R>(key, lane);
+    __builtin_amdgcn_sched_barrier(0);
+    lds_barrier();
+    // 3. walk
+    asm volatile("" : "+s"(K), "+v"(row0));
+    const int p_me = g0 + px;
+    if ((a.mode & kModeKeepOrder) && p_me < P) {
+      int i0 = j * R;
+      asm volatile("" : "+v"(i0));
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (i0 + r < K)
+          a.order[static_cast<size_t>(off + i0 + r) * P + p_me] = static_cast<uint16_t>(Q::index(key[r]));
+    }
+    int at[R];
+    float al[R];
+    float prod = 1.f;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      at[r] = Q::index(key[r]) * kDeepPitch + px;
+      al[r] = rows[at[r]];
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) prod *= 1.f - al[r];
+    float T = row_product_before(prod), A = 0.f;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      rows[at[r]] = T;
+      A = fmaf(T, al[r], A);
+      T *= 1.f - al[r];
+    }
+    A = row_sum(A);
+    if (j == 15) {
+      tend[px] = T;
+      asum[px] = A;
+    }
+    lds_barrier();
+    // 4. colours
+    float acc[3][4];
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[c][v] = 0.f;
+#pragma unroll
+    for (int i0 = 0; i0 < NP; i0 += NC) {
+      V cv[NC][3];
+#pragma unroll
+      for (int i = 0; i < NC; ++i) {
+        asm volatile("" : "+s"(K));
+        const int l = row0 + (i0 + i) * kDeepRows;
+        const FT* __restrict__ b = frag + lofs[min(l, K - 1)];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) cv[i][c] = load_quad<FT>(b + c * plane, pq);
+      }
+#pragma unroll
+      for (int i = 0; i < NC; ++i) {
+        const int l = row0 + (i0 + i) * kDeepRows;
+        if (l < K) {
+          const float4 w = *reinterpret_cast<const float4*>(rows + l * kDeepPitch + quad0);
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            const float4 x = Q::f(cv[i][c]);
+            acc[c][0] = fmaf(w.x, x.x, acc[c][0]);
+            acc[c][1] = fmaf(w.y, x.y, acc[c][1]);
+            acc[c][2] = fmaf(w.z, x.z, acc[c][2]);
+            acc[c][3] = fmaf(w.w, x.w, acc[c][3]);
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[c][v] = add_xor32(add_xor16(add_xor8(acc[c][v])));
+    if (lane < 8) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        *reinterpret_cast<float4*>(red + (wave * 3 + c) * kDeepPx + quad0) =
+            make_float4(acc[c][0], acc[c][1], acc[c][2], acc[c][3]);
+    }
+    lds_barrier();
+    if (tid < kDeepPx && g0 + tid < p1) {
+      float s[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < kDeepWaves; ++w)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) s[c] += red[(w * 3 + c) * kDeepPx + tid];
+      const int p = g0 + tid, ty = p / a.tile_w, tx = p - ty * a.tile_w;
+      const bool inside = u.x0 + tx < a.width && u.y0 + ty < a.height;
+      vs += finish_px(a, u, p, inside, with_background(a, u.t, p, make_float4(s[0], s[1], s[2], asum[tid]), tend[tid]));
+    }
+  }
+  return vs;
+}
+
+// Waves per SIMD the register allocation is held to: 512 layers need 74 KB of
+// LDS a workgroup, so two of 8 waves fit a compute unit; up to 256, three.
+constexpr int deep_waves(int rmax) { return rmax >= 32 ? 4 : 6; }
+
+// RMAX: keys per lane, 16 RMAX layers at most.
+template <typename FT, int RMAX>
+__global__ void __launch_bounds__(kDeepThreads) __attribute__((amdgpu_waves_per_eu(deep_waves(RMAX))))
+deep_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off, const int64_t* __restrict__ layer_off,
+              const int32_t* __restrict__ work_list) {
+  extern __shared__ __align__(16) char lds[];
+  __shared__ int s_item;
+  __shared__ uint32_t s_state[2];
+  const int tid = threadIdx.x;
+  const bool wave0 = __builtin_amdgcn_readfirstlane(tid) < 64;  // uniform per wave
+  FrameArgs a = args;
+  const uint32_t seq = read_frame_state(a, s_state);
+  float* red = reinterpret_cast<float*>(lds);
+  int64_t* lofs = reinterpret_cast<int64_t*>(lds + kDeepTail);
+  float* rows = reinterpret_cast<float*>(lds + kDeepTail) + 2 * a.deep_layers;
+  const int home = static_cast<int>(blockIdx.x) % a.n_queues;
+  Queue q = queue_of(a, home);
+  int drained = 0;
+  const int r = static_cast<int>(blockIdx.x) / a.n_queues;
+  int it = r < q.n ? unit_at(a, q, r) : a.n_work;
+  while (it < a.n_work) {
+    const uint32_t next = wave0 ? take_ticket(q) : 0u;
+    // position it of the launch's list: piece it % deep_subs of the tile at
+    // sorted position it / deep_subs
+    const int pos = it / a.deep_subs, piece = it - pos * a.deep_subs;
+    Unit u;
+    u.t = (work_list ? work_list[pos * a.subs_per_tile] : pos * a.subs_per_tile) / a.subs_per_tile;
+    u.sx0 = u.sy0 = 0;
+    u.y0 = (u.t / a.tiles_x) * a.tile_h;
+    u.x0 = (u.t - (u.t / a.tiles_x) * a.tiles_x) * a.tile_w;
+    const int off = tile_off[u.t];
+    const int K = tile_off[u.t + 1] - off;
+    const bool mine = K > kRegMax && K <= kDeepMax && K <= a.deep_layers;
+    if (mine) {
+      for (int i = tid; i < K; i += kDeepThreads) lofs[i] = layer_off[off + i];
+      lds_barrier();
+      const int p0 = piece * a.deep_px, p1 = p0 + a.deep_px < a.P ? p0 + a.deep_px : a.P;
+      float vs;
+      if (K <= 64) vs = deep_unit<FT, 4>(a, u, K, off, p0, p1, rows, lofs, red);
+      else if (K <= 96) vs = deep_unit<FT, 6>(a, u, K, off, p0, p1, rows, lofs, red);
+      else if (RMAX == 8 || K <= 128) vs = deep_unit<FT, 8>(a, u, K, off, p0, p1, rows, lofs, red);
+      else if constexpr (RMAX >= 16) {
+        if (K <= 192) vs = deep_unit<FT, 12>(a, u, K, off, p0, p1, rows, lofs, red);
+        else if (RMAX == 16 || K <= 256) vs = deep_unit<FT, 16>(a, u, K, off, p0, p1, rows, lofs, red);
+        else if constexpr (RMAX >= 32) {
+          if (K <= 384) vs = deep_unit<FT, 24>(a, u, K, off, p0, p1, rows, lofs, red);
+          else vs = deep_unit<FT, 32>(a, u, K, off, p0, p1, rows, lofs, red);
+        }
+      }
+      if ((a.mode & kModeAccumulate) && wave0) {
+        vs = wave_sum(vs);
+        if (__lane_id() == 0) a.deep_partial[static_cast<size_t>(u.t) * a.deep_subs + piece] = vs;
+      }
+    }
+    lds_barrier();  // every lane has read s_item; the LDS rows are free
+    if (wave0) {
+      // the list is in descending order of layers: a tile of few ends the counter
+      int v = K > kRegMax ? ticket_to_unit(a, q, next) : a.n_work;
+      while (v == a.n_work && ++drained < a.n_queues) {
+        q = queue_of(a, (home + drained) % a.n_queues);
+        if (queue_open(q)) v = ticket_to_unit(a, q, take_ticket(q));
+      }
+      if (__lane_id() == 0) s_item = v;
+    }
+    lds_barrier();
+    it = __builtin_amdgcn_readfirstlane(s_item);
+  }
+  finish_workgroup(a, seq, wave0);
 }
 
 // Per-tile variance of the mean from the units' partial M2 sums, added in
@@ -1333,8 +1667,17 @@ frame_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off,
 __global__ void __launch_bounds__(256) tile_variance_kernel_t(VarianceArgs a) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= a.n_tiles) return;
+  const float* __restrict__ part = a.var_partial + t * a.subs_per_tile;
+  int n = a.subs_per_tile;
+  if (a.deep_subs) {  // the tile was composited by the row-sort launch, in units of its own
+    const int K = a.tile_off[t + 1] - a.tile_off[t];
+    if (K > kRegMax && K <= kDeepMax) {
+      part = a.deep_partial + t * a.deep_subs;
+      n = a.deep_subs;
+    }
+  }
   float sum = 0.f;
-  for (int i = 0; i < a.subs_per_tile; ++i) sum += a.var_partial[t * a.subs_per_tile + i];
+  for (int i = 0; i < n; ++i) sum += part[i];
   const int x0 = (t % a.tiles_x) * a.tile_w, y0 = (t / a.tiles_x) * a.tile_h;
   const int wx = a.width - x0, wy = a.height - y0;
   const int inside = (wx < a.tile_w ? wx : a.tile_w) * (wy < a.tile_h ? wy : a.tile_h);
@@ -1476,6 +1819,22 @@ const void* frame_kernel(int dtype, int kcap, int op) {
   if (kcap <= 8) return reinterpret_cast<const void*>(&frame_kernel_t<_Float16, 8, 0>);
   if (kcap <= 16) return reinterpret_cast<const void*>(&frame_kernel_t<_Float16, 16, 0>);
   return reinterpret_cast<const void*>(&frame_kernel_t<_Float16, 32, 0>);
+}
+
+const void* deep_kernel(int dtype, int max_layers) {
+  if (dtype == 0) {
+    if (max_layers <= 128) return reinterpret_cast<const void*>(&deep_kernel_t<float, 8>);
+    if (max_layers <= 256) return reinterpret_cast<const void*>(&deep_kernel_t<float, 16>);
+    return reinterpret_cast<const void*>(&deep_kernel_t<float, 32>);
+  }
+  if (max_layers <= 128) return reinterpret_cast<const void*>(&deep_kernel_t<_Float16, 8>);
+  if (max_layers <= 256) return reinterpret_cast<const void*>(&deep_kernel_t<_Float16, 16>);
+  return reinterpret_cast<const void*>(&deep_kernel_t<_Float16, 32>);
+}
+
+size_t deep_lds_bytes(int max_layers) {
+  const int k = deep_layers(max_layers);
+  return kDeepTail + k * sizeof(int64_t) + deep_rows_bytes(k);
 }
 
 const void* accumulate_kernel() { return reinterpret_cast<const void*>(&accumulate_kernel_t); }

@@ -42,7 +42,7 @@ struct AutotuneKey {
 };
 struct Shape {
   int work_w, work_h, waves;
-  int big_lds;  // LDS budget of the K > 32 path
+  int big_lds;  // LDS budget of the LDS sort
 };
 std::map<AutotuneKey, Shape> g_autotune_cache;
 
@@ -75,6 +75,7 @@ struct dfb_ctx {
   const void* frag = nullptr;
   int64_t n_blocks = 0;
   int n_layers = 0, max_k = 0;
+  int n_deep = 0, n_big = 0;  // tiles of more than kRegMax layers, and of more than kDeepMax
   std::vector<int32_t> h_off;
   std::vector<dfb_layer> last_layers;
   std::vector<int32_t> last_expected;
@@ -293,7 +294,7 @@ dfb_status check_usable(dfb_ctx* h) {
 
 int kcap_for(int max_k) { return max_k <= 8 ? 8 : (max_k <= 16 ? 16 : 32); }
 
-// log2 of the padded sort size of a tile with max_k layers (the K > 32 path
+// log2 of the padded sort size of a tile with max_k layers (the LDS sort
 // pads to a power of two of at least 64).
 int layer_class(int max_k) {
   int lk = 0;
@@ -305,9 +306,9 @@ int layer_class(int max_k) {
 // tile (else the whole tile), and full-width strips of the same pixel count
 // (a strip row is a whole tile row, so a unit's plane rows are contiguous in
 // memory and fp16 rows fill whole cache lines), times 1/2/4 waves, times
-// (frames with tiles of more than 128 layers) a small or a large LDS budget
-// for the K > 32 path -- two workgroups per CU, or one with twice the pixels
-// per sorting group.
+// (frames whose deepest tiles the LDS sort takes) a small or a large LDS
+// budget for the LDS sort -- two workgroups per CU, or one with twice the
+// pixels per sorting group.
 std::vector<Shape> candidates(const dfb_config& c, int max_k) {
   std::vector<std::pair<int, int>> sizes;
   if (c.work_w) {
@@ -326,7 +327,8 @@ std::vector<Shape> candidates(const dfb_config& c, int max_k) {
   if (c.waves_per_tile) waves.push_back(c.waves_per_tile);
   else waves = {1, 2, 4};
   std::vector<int> ldss{dfb::big_lds_bytes(max_k)};
-  if (max_k > 128 && c.tile_op == DFB_OP_ALPHA_BLEND) ldss.push_back(64 * 1024);
+  const bool row_sort = (static_cast<int64_t>(c.tile_w) * c.tile_h) % 4 == 0;
+  if (max_k > (row_sort ? dfb::kDeepMax : 128) && c.tile_op == DFB_OP_ALPHA_BLEND) ldss.push_back(64 * 1024);
   std::vector<Shape> out;
   for (auto& s : sizes)
     for (int w : waves)
@@ -335,6 +337,34 @@ std::vector<Shape> candidates(const dfb_config& c, int max_k) {
 }
 
 void drop_graphs(dfb_ctx* h);
+
+// Units of the row-sort launch: `px` consecutive pixels of a tile (whole
+// groups of kDeepPx), `subs` a tile.  A unit costs one ticket and loads its
+// tile's layer offsets, so larger is cheaper until the launch runs out of
+// units: 128 pixels, or one group where that leaves fewer than four units
+// to each workgroup the chip holds (about two per compute unit).
+struct DeepUnits {
+  int px, subs;
+};
+DeepUnits deep_units(int P, int64_t deep_tiles, int n_cu) {
+  for (int px : {4 * dfb::kDeepPx, 2 * dfb::kDeepPx, dfb::kDeepPx}) {
+    const int subs = (P + px - 1) / px;
+    if (px == dfb::kDeepPx || deep_tiles * subs >= static_cast<int64_t>(8) * n_cu) return {px, subs};
+  }
+  return {dfb::kDeepPx, (P + dfb::kDeepPx - 1) / dfb::kDeepPx};
+}
+
+// The row sort reads 4 pixels a lane: blocks and planes start at multiples
+// of P elements, so P and the base have to be aligned; else the LDS sort
+// takes every tile of more than kRegMax layers.
+bool quad_aligned(const void* frag, int dtype, int P) {
+  return P % 4 == 0 && reinterpret_cast<uintptr_t>(frag) % (dtype == DFB_F16 ? 8 : 16) == 0;
+}
+bool has_deep(const dfb_ctx* h) {
+  return h->cfg.tile_op == DFB_OP_ALPHA_BLEND && h->n_deep > h->n_big &&
+         quad_aligned(h->frag, h->cfg.frag_dtype, h->P);
+}
+DeepUnits deep_units(const dfb_ctx* h) { return deep_units(h->P, h->n_deep, h->n_cu); }
 
 // Device array of a table set, grown when too small.  Only called on a set
 // no frame in flight reads (the other set's, or during the autotuner's
@@ -420,7 +450,7 @@ dfb_status build_work(dfb_ctx* h, const Shape& s) {
   const size_t n = static_cast<size_t>(h->n_work);
   dfb_status st = ensure_device_table(h, T.work, T.work_cap, n);
   if (st != DFB_OK) return st;
-  st = ensure(h, h->d_var_partial, h->partial_cap, n);
+  st = ensure(h, h->d_var_partial, h->partial_cap, n + static_cast<size_t>(h->n_tiles) * (h->n_deep ? deep_units(h).subs : 0));
   if (st != DFB_OK) return st;
   st = stage(h, T, 2, T.st_work, T.st_work_cap, n);
   if (st != DFB_OK) return st;
@@ -475,6 +505,7 @@ FrameArgs base_args(const dfb_config& c, int tiles_x, int n_tiles, const Shape& 
   // blocks (P % V == 0 follows from tile_w % V == 0) and rows of whole vectors
   const int V = c.frag_dtype == DFB_F16 ? 8 : 4;
   a.vec_ok = (reinterpret_cast<uintptr_t>(frag) % 16 == 0) && c.tile_w % V == 0 && sh.work_w % V == 0;
+  a.quad_ok = quad_aligned(frag, c.frag_dtype, a.P);
   for (int k = 0; k < 4; ++k) a.bg[k] = c.background[k];
   a.bg_image = c.background_image;
   a.inv_gamma = 1.f / c.tonemap_gamma;
@@ -492,6 +523,7 @@ FrameArgs make_args(dfb_ctx* h, uint32_t mode) {
   a.m2 = h->m2;
   a.tile_var = h->tile_var;
   a.var_partial = h->d_var_partial;
+  a.deep_partial = h->d_var_partial + h->n_work;
   a.final_out = h->final_out;
   a.order = h->order;
   return a;
@@ -515,13 +547,12 @@ dfb_status grid_of(dfb_ctx* h, const void* func, int threads, size_t lds, int n_
   return DFB_OK;
 }
 
-dfb_status grid_for(dfb_ctx* h, const void* func, int threads, size_t lds, int& grid) {
-  return grid_of(h, func, threads, lds, h->n_work, h->n_cu, grid);
-}
-
 dfb::VarianceArgs make_var_args(dfb_ctx* h) {
   dfb::VarianceArgs v{};
   v.var_partial = h->d_var_partial;
+  v.deep_partial = h->d_var_partial + h->n_work;
+  v.tile_off = h->d_off;
+  v.deep_subs = has_deep(h) ? deep_units(h).subs : 0;
   v.tile_var = h->tile_var;
   v.n_tiles = h->n_tiles;
   v.subs_per_tile = h->subs_per_tile;
@@ -534,14 +565,15 @@ dfb::VarianceArgs make_var_args(dfb_ctx* h) {
   return v;
 }
 
-// Everything one frame's launches take: one or two persistent frame
-// kernels over the same work list -- the LDS-sort kernel for the tiles with
-// more than kRegMax layers (alpha-blend frames that have such tiles), then
-// the register-path kernel for the others, whose last workgroup advances the
-// frame state -- and, for accumulating frames, the per-tile variance
-// combine.  Nothing in it changes from frame to frame (the frame's counter
-// slot and accumulation count live in the device frame state), so the same
-// launches serve as a graph replayed every frame.
+// Everything one frame's launches take: up to three persistent kernels over
+// the same work list -- the LDS sort for the tiles with more than kDeepMax
+// layers and the row sort for those with more than kRegMax (alpha-blend
+// frames that have such tiles), then the register-path kernel for the
+// others, whose last workgroup advances the frame state -- and, for
+// accumulating frames, the per-tile variance combine.  Nothing in it changes
+// from frame to frame (the frame's counter slot and accumulation count live
+// in the device frame state), so the same launches serve as a graph replayed
+// every frame.
 struct KernelLaunch {
   const void* func;
   int grid, threads;
@@ -561,7 +593,7 @@ struct KernelLaunch {
 
 struct FrameLaunch {
   int nk;
-  KernelLaunch k[2];
+  KernelLaunch k[dfb::kRings];
   bool acc;
   dfb::VarianceArgs va;
   void* vparams[1];
@@ -571,42 +603,74 @@ struct FrameLaunch {
   }
 };
 
+// What a frame's launches depend on besides its geometry.  n_deep and n_big
+// are the tiles of more than kRegMax and of more than kDeepMax layers, known
+// where the host built the work list (each launch then takes its own range
+// of the list, which is in descending order of layers), else -1: every
+// launch walks the whole list and leaves out what is not its own.
+struct FrameShape {
+  int max_k, kcap, n_tiles, n_cu;
+  int n_deep, n_big;
+  bool big, deep;
+  DeepUnits du;
+};
+
 // The frame kernels of a frame (geometry args, queue allocation, tables and
 // per-kernel buffers filled in by the caller's base): fills L.k[0..nk).
 dfb_status plan_kernels(dfb_ctx* h, const dfb_config& c, const FrameArgs& base, uint32_t* queue_base,
-                        const Shape& sh, int max_k, int kcap, int n_work, int n_cu, const int32_t* tab_off,
+                        const Shape& sh, const FrameShape& fs, const int32_t* tab_off,
                         const int64_t* tab_layer, const int32_t* tab_work, FrameLaunch& L) {
-  const int threads = 64 * sh.waves;
   const bool sorting = c.tile_op == DFB_OP_ALPHA_BLEND;
   L.nk = 0;
-  const bool big = sorting && max_k > dfb::kRegMax;
-  for (int pass = big ? 0 : 1; pass < 2; ++pass) {
+  for (int ring : {1, 2, 0}) {
+    if ((ring == 1 && !fs.big) || (ring == 2 && !fs.deep)) continue;
     KernelLaunch& K = L.k[L.nk++];
-    const int kc = pass == 0 ? 0 : kcap;
-    K.func = dfb::frame_kernel(c.frag_dtype, kc, c.tile_op);
-    K.threads = threads;
-    // the list and averaging operations keep nothing in LDS
-    K.lds = sorting ? dfb::frame_lds_bytes(kc, threads, max_k, sh.big_lds) : 0;
-    dfb_status st = grid_of(h, K.func, threads, K.lds, n_work, n_cu, K.grid);
-    if (st != DFB_OK) return st;
-    if (K.lds > 64 * 1024)
-      DFB_HIP(h, hipFuncSetAttribute(K.func, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(K.lds)));
     K.fa = base;
-    K.fa.queue = dfb::ring_of(queue_base, pass == 0 ? 1 : 0);
+    K.fa.queue = dfb::ring_of(queue_base, ring);
+    K.fa.rings = queue_base;
     K.fa.state = dfb::state_of(queue_base);
-    K.fa.advance = pass == 1;
-    K.fa.n_queues = std::min(dfb::kQueues, K.grid);
+    K.fa.advance = ring == 0;
     K.tab_off = tab_off;
     K.tab_layer = tab_layer;
     K.tab_work = tab_work;
+    if (ring == 2) {
+      const int first = fs.n_big > 0 ? fs.n_big : 0;
+      K.func = dfb::deep_kernel(c.frag_dtype, fs.max_k);
+      K.threads = dfb::kDeepThreads;
+      K.lds = dfb::deep_lds_bytes(fs.max_k);
+      K.fa.deep_px = fs.du.px;
+      K.fa.deep_subs = K.fa.queue_block = fs.du.subs;
+      K.fa.deep_layers = dfb::deep_layers(fs.max_k);
+      K.fa.n_work = ((fs.n_deep < 0 ? fs.n_tiles : fs.n_deep) - first) * fs.du.subs;
+      K.tab_work = tab_work + static_cast<size_t>(first) * base.subs_per_tile;
+    } else {
+      const int kc = ring == 1 ? 0 : fs.kcap;
+      K.func = dfb::frame_kernel(c.frag_dtype, kc, c.tile_op);
+      K.threads = 64 * sh.waves;
+      // the list and averaging operations keep nothing in LDS
+      K.lds = sorting ? dfb::frame_lds_bytes(kc, K.threads, fs.max_k, sh.big_lds) : 0;
+      K.fa.big_min = base.quad_ok ? dfb::kDeepMax : dfb::kRegMax;
+      if (ring == 1 && fs.n_big >= 0) K.fa.n_work = (base.quad_ok ? fs.n_big : fs.n_deep) * base.subs_per_tile;
+      if (ring == 0 && sorting && fs.n_deep > 0) {
+        K.fa.n_work -= fs.n_deep * base.subs_per_tile;
+        K.tab_work = tab_work + static_cast<size_t>(fs.n_deep) * base.subs_per_tile;
+      }
+    }
+    dfb_status st = grid_of(h, K.func, K.threads, K.lds, K.fa.n_work, fs.n_cu, K.grid);
+    if (st != DFB_OK) return st;
+    if (K.lds > 64 * 1024)
+      DFB_HIP(h, hipFuncSetAttribute(K.func, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(K.lds)));
+    K.fa.n_queues = std::min(dfb::kQueues, K.grid);
   }
   return DFB_OK;
 }
 
 dfb_status prepare_launch(dfb_ctx* h, uint32_t mode, FrameLaunch& L) {
   FrameArgs base = make_args(h, mode);
-  dfb_status st = plan_kernels(h, h->cfg, base, h->d_queue_ring, h->shape, h->max_k, h->kcap, h->n_work, h->n_cu,
-                               h->d_off, h->d_block, h->d_work, L);
+  const FrameShape fs{h->max_k, h->kcap, h->n_tiles, h->n_cu, h->n_deep, h->n_big,
+                      h->cfg.tile_op == DFB_OP_ALPHA_BLEND && (base.quad_ok ? h->n_big : h->n_deep) > 0, has_deep(h),
+                      deep_units(h)};
+  dfb_status st = plan_kernels(h, h->cfg, base, h->d_queue_ring, h->shape, fs, h->d_off, h->d_block, h->d_work, L);
   if (st != DFB_OK) return st;
   L.acc = (mode & dfb::kModeAccumulate) != 0;
   L.va = make_var_args(h);
@@ -616,14 +680,19 @@ dfb_status prepare_launch(dfb_ctx* h, uint32_t mode, FrameLaunch& L) {
 
 // Launch one frame with the current shape on the caller's stream.  With
 // t0/t1 given, the two events bracket the frame kernels.
-dfb_status launch_frame(dfb_ctx* h, uint32_t mode, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr) {
+// skip_deep leaves the row-sort launch out (the autotuner: the launch shape
+// does not touch it).
+dfb_status launch_frame(dfb_ctx* h, uint32_t mode, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr,
+                        bool skip_deep = false) {
   FrameLaunch L;
   dfb_status st = prepare_launch(h, mode, L);
   if (st != DFB_OK) return st;
   if (t0) DFB_HIP(h, hipEventRecord(t0, h->stream));
-  for (int i = 0; i < L.nk; ++i)
+  for (int i = 0; i < L.nk; ++i) {
+    if (skip_deep && L.k[i].fa.deep_px) continue;
     DFB_HIP(h, hipLaunchKernel(L.k[i].func, dim3(L.k[i].grid), dim3(L.k[i].threads), L.k[i].params, L.k[i].lds,
                                h->stream));
+  }
   if (t1) DFB_HIP(h, hipEventRecord(t1, h->stream));
   if (L.acc)
     DFB_HIP(h, hipLaunchKernel(dfb::tile_variance_kernel(), dim3((h->n_tiles + 255) / 256), dim3(256), L.vparams, 0,
@@ -754,7 +823,7 @@ dfb_status autotune(dfb_ctx* h) {
     int warm = 5, timed = 5;  // frames longer than 5 ms: 1 warm-up, 3 timed
     for (int r = 0; r < warm + timed; ++r) {
       DFB_HIP(h, hipEventRecord(e0, h->stream));
-      st = launch_frame(h, mode);
+      st = launch_frame(h, mode, nullptr, nullptr, true);
       if (st != DFB_OK) return st;
       DFB_HIP(h, hipEventRecord(e1, h->stream));
       DFB_HIP(h, hipEventSynchronize(e1));
@@ -1017,7 +1086,7 @@ dfb_status dfb_set_fragments(dfb_handle h, const void* frag_dev, int64_t n_block
     for (int32_t i = 0; i < n_layers; ++i) idx[fill[layers[i].tile_id]++] = i;
   }
   std::vector<int64_t> block(n_layers);
-  int max_k = 0;
+  int max_k = 0, n_deep = 0, n_big = 0;
   for (int t = 0; t < h->n_tiles; ++t) {
     auto b = idx.begin() + off[t], e = idx.begin() + off[t + 1];
     std::sort(b, e, [&](int32_t x, int32_t y) { return layers[x].source_id < layers[y].source_id; });
@@ -1028,6 +1097,8 @@ dfb_status dfb_set_fragments(dfb_handle h, const void* frag_dev, int64_t n_block
       block[it - idx.begin()] = layers[*it].block * 5 * static_cast<int64_t>(h->P);
     }
     max_k = std::max(max_k, counts[t]);
+    n_deep += counts[t] > dfb::kRegMax;
+    n_big += counts[t] > dfb::kDeepMax;
   }
   // Upload into the table set that no frame in flight reads (no wait for
   // the frames of the current layout).
@@ -1078,6 +1149,8 @@ dfb_status dfb_set_fragments(dfb_handle h, const void* frag_dev, int64_t n_block
   h->n_layers = n_layers;
   h->n_blocks = n_blocks;
   h->max_k = max_k;
+  h->n_deep = n_deep;
+  h->n_big = n_big;
   h->kcap = kcap_for(max_k);
   h->frag = frag_dev;
   h->last_layers.assign(layers, layers + n_layers);
@@ -1437,9 +1510,10 @@ dfb_status dfb_composite_noalloc(const dfb_config* cfg, const void* frag_dev, co
   DFB_HIP(nullptr, hipGetDevice(&dev));
   DFB_HIP(nullptr, hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
   FrameLaunch L;
-  if ((s = plan_kernels(nullptr, *cfg, a, queue, sh, max_layers, kcap_for(max_layers), a.n_work, n_cu, tile_off_dev,
-                        layer_off_dev, work, L)) != DFB_OK)
-    return s;
+  const bool blend = cfg->tile_op == DFB_OP_ALPHA_BLEND;
+  const FrameShape fs{max_layers, kcap_for(max_layers), n_tiles, n_cu, -1, -1, blend && max_layers > (a.quad_ok ? dfb::kDeepMax : dfb::kRegMax),
+                      blend && max_layers > dfb::kRegMax && a.quad_ok, deep_units(a.P, n_tiles, n_cu)};
+  if ((s = plan_kernels(nullptr, *cfg, a, queue, sh, fs, tile_off_dev, layer_off_dev, work, L)) != DFB_OK) return s;
   L.bind();
   int32_t nt = n_tiles, subs = a.subs_per_tile;
   void* lp[] = {&tile_off_dev, &nt, &subs, &work};
