@@ -38,24 +38,63 @@ hipError_t conv3x3_fwd(const Map& x, const uint16_t* w_fwd, const float* bias, c
                        const Map* x2 = nullptr);
 // g = bf16(dy * (y > 0)), the ReLU-gated output gradient (g.c == dy.c, a
 // multiple of 8 dividing 2048; rows and offsets of y and g multiples of 8),
-// and db[c] = sum_p dy*(y>0) in f32.  `partial` needs conv3x3_wgrad_scratch
-// floats.
-hipError_t conv3x3_gate(const MapF& dy, const Map& y, const Map& g, float* db, float* partial, const Shape& s,
-                        hipStream_t st);
+// and partial[row][c], whose sum over the gate_rows rows is the bias gradient
+// sum_p dy*(y>0) in f32.
+hipError_t conv3x3_gate(const MapF& dy, const Map& y, const Map& g, float* partial, const Shape& s, hipStream_t st);
+int gate_rows(const Shape& s, int c);
 // dx = conv3x3^T(g) (overwrites dx).
 hipError_t conv3x3_dgrad(const Map& g, const uint16_t* w_dgrad, const MapF& dx, const Shape& s, hipStream_t st);
-// dw[9][ci][co] = sum_p x[p + tap] * g[p] for ci < ci_out (ci_out < x.c when
-// x carries zero padding channels).  `partial` needs conv3x3_wgrad_scratch
-// floats; g's row stride and offset are multiples of 4 elements.
-hipError_t conv3x3_wgrad(const Map& x, const Map& g, float* dw, float* partial, const Shape& s, hipStream_t st,
-                         int ci_out);
-size_t conv3x3_wgrad_scratch(int ci, int co, const Shape& s);
 
-hipError_t avgpool2(const Map& x, const Map& y, const Shape& s_in, hipStream_t st);
+// Weight gradients of the 12 conv3x3 layers, one launch: partial sums of
+// dw[9][ci][co] = sum_p x[p + tap] * g[p] over `chunks` runs of pixel tiles.
+constexpr int kConvLayers = 12;
+struct WgradLayer {
+  const uint16_t* x;   // input map [source pixels][xld], its xc channels first (16-byte aligned)
+  const uint16_t* g;   // gated output gradient [pixels][co]
+  int xld, xc, co;
+  int up;              // x is the map the layer's input is 2x up-sampled from
+  Shape s;             // output shape
+  int cb, ob;          // 32-channel slices of c_in and c_out a workgroup takes (1 or 2)
+  int cig, cog;        // such groups
+  int tiles, chunks, first_wg;
+  size_t part;         // first float of the layer's partial sums
+};
+struct WgradPlan {
+  WgradLayer l[kConvLayers];
+  int n_wg;
+};
+int wgrad_chunks(int layer, long long tiles);
+long long wgrad_tiles(const Shape& s);
+size_t wgrad_floats(const WgradLayer& L);  // of its partial sums
+hipError_t conv3x3_wgrad(const WgradPlan& plan, float* partial, hipStream_t st);
+
+// The sums of every gradient's partials, Adam, and the bf16 weight copies.
+struct UpdateLayer {
+  int cb, ob, cig, cog, chunks, first_block;
+  int ci, ci_pad, co;
+  int off_w;           // first weight in the parameter vector
+  size_t part;
+  uint16_t *wf, *wd;   // forward [9][co][ci_pad] and data-gradient [9][ci_pad][co] copies
+};
+struct BiasPart {      // n columns (parameters) of `rows` partial rows
+  int first, n, rows, param;
+  size_t part;
+};
+struct UpdatePlan {
+  UpdateLayer l[kConvLayers];
+  BiasPart bias[kConvLayers + 1];  // the layers' biases, then the output conv's 99 parameters and the loss sum
+  int conv_blocks;
+};
+struct AdamArgs {
+  float *w, *g, *m, *v, *loss;
+  float lr, b1, b2, eps, c1, c2;
+  int update;          // 0: gradients and loss only
+};
+int update_blocks(const UpdateLayer& L);
+hipError_t update_params(const UpdatePlan& plan, const float* partial, const AdamArgs& a, hipStream_t st);
+
 hipError_t avgpool2_backward_add(const MapF& dy, const MapF& dx, const Shape& s_in, hipStream_t st);
-hipError_t upsample2(const Map& x, const Map& y, const Shape& s_in, hipStream_t st);
 hipError_t upsample2_backward(const MapF& dy, const MapF& dx, const Shape& s_in, hipStream_t st);
-hipError_t add_into(const MapF& src, const MapF& dst, const Shape& s, hipStream_t st);
 
 // The first conv3x3 (8 input channels -> 32, ReLU, bf16) with the nine
 // taps packed into a 72-deep contraction, reading the packed bf16 input x
@@ -65,18 +104,16 @@ hipError_t conv3x3_in_fwd(const Map& x, const uint16_t* w_fwd, const float* bias
 // out[p][c] = base[p][c] + b[c] + sum_i x[p][i] w[i][c]   (c < 3, f32)
 hipError_t out_conv_fwd(const Map& x, const float* w, const float* b, const float* base,
                         int base_ld, float* out, const Shape& s, hipStream_t st);
-// dout = 2 (out - target) / count; loss partial sums; dx = dout w^T; dw, db.
+// dout = 2 (out - target) / count; dx = dout w^T; partial[row] = {dw[c][3],
+// db[3], sum (out - target)^2} over out_rows rows.
 hipError_t out_conv_backward(const Map& x, const float* out, const float* target, const float* w,
-                             const MapF& dx, float* dw, float* db, float* loss, float* partial,
-                             const Shape& s, hipStream_t st);
-size_t out_conv_scratch(const Shape& s);
+                             const MapF& dx, float* partial, const Shape& s, hipStream_t st);
+int out_rows(const Shape& s);
 
 // bf16 input [p][8] from f32 [p][in_ld] (first 6 channels), channels 6,7 zero.
 hipError_t pack_input(const float* in, int in_ld, uint16_t* x, const Shape& s, hipStream_t st);
 
-// Adam over a flat f32 parameter vector, then refresh the bf16 weight copies.
-hipError_t adam_update(float* w, const float* g, float* m, float* v, long long n, float lr,
-                       float beta1, float beta2, float eps, float c1, float c2, hipStream_t st);
+// The bf16 copies of a layer's master weights.
 hipError_t refresh_bf16(const float* w_master, uint16_t* w_fwd, uint16_t* w_dgrad, int ci, int co,
                         hipStream_t st);
 

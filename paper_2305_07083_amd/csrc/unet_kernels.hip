@@ -12,10 +12,10 @@
 // All three use v_mfma_f32_32x32x16_bf16.  Operand layout (checked on the
 // device): lane l holds k = (l/32)*8 .. +7 of row/column l%32; the result
 // element r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l%32.  In
-// dgrad and wgrad a workgroup is 4 waves over a 64-row tile and every
-// 32-column block of N: wave w takes 32x32 blocks w, w + 4, ...; with only
-// two blocks (N = 32) two waves share a block, each taking half of the K
-// steps, and their sums are added in a fixed order.
+// dgrad a workgroup is 4 waves over a 64-row tile and every 32-column block
+// of N: wave w takes 32x32 blocks w, w + 4, ...; with only two blocks
+// (N = 32) two waves share a block, each taking half of the K steps, and their
+// sums are added in a fixed order.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -884,200 +884,249 @@ __global__ void __launch_bounds__(256) gate_k(MapF dy, Map y, Map g, float* __re
 }
 
 // ------------------------------------------------------------- wgrad
-// Per tap and 64-wide c_in tile, over one chunk of pixels:
-// partial[chunk][tap][ci][co] = sum_p x[p + tap][ci] * g[p][co], g = bf16(dy * (y > 0)).
-constexpr int kWgradChunk = 1024;
+// dw[tap][ci][co] = sum_p x[p + tap][ci] g[p][co], g = bf16(dy * (y > 0)), of
+// every conv layer in one launch.  A workgroup takes up to 64 x 64 (c_in,
+// c_out) of one layer over a run of 8 x 32-pixel tiles; a wave holds one
+// 32 x 32 block for all nine taps (144 accumulators), so a staged tile is
+// read from memory once and not once per tap.  With fewer than four blocks
+// the waves of a block split the tile's rows.
+//
+// x (with its halo) and g are staged as they lie in memory, [32-channel
+// slice][pixel][32]; the operands need pixels along K, and
+// ds_read_b64_tr_b16 transposes them on the way out: in each 16 lanes, lane
+// 4 k + b addresses 4 channels of pixel k and lane l receives channel l of
+// the 4 pixels (checked on the device).  A pixel's slice is 64 bytes, so the
+// four pixels of 32 lanes cover the 64 banks once wherever they start, and a
+// tap is an offset of whole pixels.  A row of x serves the three taps above,
+// at and below it: three x operands and one g operand feed nine MFMAs.
+//
+// All layers in one launch because one layer's tiles fill the chip for only
+// a few microseconds: 8 x 128^2 step, all 12 layers: 12 launches with one tap
+// per workgroup 367 us, 88 us now.
+constexpr int kWgTH = 8;                                // tile rows
+constexpr int kWgXP = (kWgTH + 2) * (kTW + 2);          // halo pixels
+constexpr int kWgGP = kWgTH * kTW;                      // pixels
+constexpr int kWgAcc = 9 * 16;                          // accumulators of a wave
+typedef short s16x4 __attribute__((ext_vector_type(4)));
 
-// A stage is KS slices of 32 pixels (one barrier pair per stage); the
-// next stage's x and g are loaded into registers while this stage's MFMAs
-// run.  Slices past the image end stage zeros.
-constexpr int kWgradKS = 4;
-constexpr int LDW = 32 * kWgradKS + 8;  // LDS row: the stage's pixels + 8 padding
+// 16 pixels x 32 channels of a slice as an MFMA operand: this lane's channel,
+// pixels 8 (lane / 32) .. + 7.  `at` is the lane's byte address of pixel 0.
+__device__ __forceinline__ bf16x8 frag_tr(const char* at) {
+  typedef __attribute__((address_space(3))) s16x4* P;
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((P)(at));
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((P)(at + 4 * 64));
+  bf16x8 r;
+  __builtin_memcpy(&r, &lo, 8);
+  __builtin_memcpy(reinterpret_cast<char*>(&r) + 8, &hi, 8);
+  return r;
+}
 
-// The MFMA is v_mfma_f32_32x32x16_bf16 on 32 c_in x 32 c_out blocks (row
-// and column operands read as 32 consecutive LDS rows at one 16-byte chunk;
-// the 136-element row pitch is an odd number of chunks, so the reads are free
-// of bank conflicts).  Wave w takes blocks w, w + 4, ... of the MBLK * BN / 32
-// blocks (MBLK = 1 when the input has at most 32 channels: the c_in tile's
-// upper half is zero and is not multiplied); with fewer blocks than waves the
-// stage's pixels are split between 4 / blocks waves per block and their sums
-// added in a fixed order.
-template <int BN, bool HALF>
-__global__ void __launch_bounds__(256) conv_wgrad_k(Map x, Map g, float* __restrict__ partial, Shape s) {
-  __shared__ __align__(16) uint16_t As[BM * LDW];   // [ci][px]
-  __shared__ __align__(16) uint16_t Bs[BN * LDW];   // [co][px]
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, lh = lane >> 5;
-  const int chunk = blockIdx.x, tap = blockIdx.y, ci0 = blockIdx.z * BM;
-  const int dr = tap / 3 - 1, dc = tap % 3 - 1;
-  const long long P = s.pixels();
-  const long long p_begin = static_cast<long long>(chunk) * kWgradChunk;
-  constexpr int MBLK = HALF ? 1 : 2;                       // 32-row c_in blocks multiplied
-  constexpr int NBLK = MBLK * (BN / 32);                   // 32 x 32 output blocks
-  constexpr int KSPLIT = NBLK >= 4 ? 1 : 4 / NBLK;         // waves per block
-  constexpr int BPW = NBLK >= 4 ? NBLK / 4 : 1;            // blocks per wave
-  constexpr int KSUB = 32 * kWgradKS / 16 / KSPLIT;        // 16-pixel MFMA steps per wave and stage
-  const int kpart = wave / (4 / KSPLIT);                   // which part of the stage's pixels
-  f32x16 acc[BPW];
+// NR tile rows from the rows xr (halo) and gr point at.
+template <int NR>
+__device__ __forceinline__ void wgrad_rows(const char* xr, const char* gr, f32x16 (&acc)[9]) {
 #pragma unroll
-  for (int b = 0; b < BPW; ++b)
+  for (int sg = 0; sg < kTW / 16; ++sg) {
+    bf16x8 gv[3];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
-  // thread (q, cg) stages the 4 consecutive pixels 4q..4q+3 of the stage
-  // (q < 32) for channel group cg: 4 loads of x and of g, then one 8-byte
-  // LDS store per channel (4 pixels of one channel, transposed in registers)
-  const int q4 = (tid >> 3) * 4;
-  const int a8 = (tid & 7) * 8;            // 8 c_in values
-  constexpr int BPER = BN / 8;             // c_out values per thread
-  const int b0 = (tid & 7) * BPER;
-  uint4 v[4];
-  uint32_t gw[4][BPER / 2];
-  auto load = [&](int k0) {
+    for (int rr = 0; rr < NR + 2; ++rr) {
+      bf16x8 xv[3];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const long long p = p_begin + k0 + q4 + i;
-      const Pix q = pixel_of(p, s);
-      bool in;
-      const long long src = shifted(q, dr, dc, s, in);
-      v[i] = uint4{0u, 0u, 0u, 0u};
-      if (in && ci0 + a8 < x.c) v[i] = *reinterpret_cast<const uint4*>(x.p + src * x.ld + x.off + ci0 + a8);
+      for (int dc = 0; dc < 3; ++dc) xv[dc] = frag_tr(xr + (rr * (kTW + 2) + sg * 16 + dc) * 64);
+      if (rr < NR) gv[rr % 3] = frag_tr(gr + (rr * kTW + sg * 16) * 64);
 #pragma unroll
-      for (int k = 0; k < BPER / 2; ++k) gw[i][k] = 0u;
-      if (q.ok) {  // 8-byte loads (g's row stride and offset are multiples of 4)
-        const uint16_t* gp = g.p + p * g.ld + g.off + b0;
+      for (int dr = 0; dr < 3; ++dr) {
+        if (rr - dr >= 0 && rr - dr < NR) {
 #pragma unroll
-        for (int k = 0; k < BPER / 4; ++k) {
-          const uint2 t = *reinterpret_cast<const uint2*>(gp + 4 * k);
-          gw[i][2 * k] = t.x;
-          gw[i][2 * k + 1] = t.y;
+          for (int dc = 0; dc < 3; ++dc)
+            acc[dr * 3 + dc] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv[dc], gv[(rr - dr) % 3], acc[dr * 3 + dc], 0, 0, 0);
         }
       }
     }
-  };
-  // channel c of 4 pixels' packed words w[i] (2 channels per word) as 4 bf16
-  auto column = [](const uint32_t (&w)[4], int c) {
-    const int sh = (c & 1) * 16;
-    const uint32_t e0 = (w[0] >> sh) & 0xFFFFu, e1 = (w[1] >> sh) & 0xFFFFu, e2 = (w[2] >> sh) & 0xFFFFu,
-                   e3 = (w[3] >> sh) & 0xFFFFu;
-    return uint2{e0 | (e1 << 16), e2 | (e3 << 16)};
-  };
-  load(0);
-  for (int k0 = 0; k0 < kWgradChunk; k0 += 32 * kWgradKS) {
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const int wi = c >> 1;
-      const uint32_t w[4] = {wi == 0 ? v[0].x : wi == 1 ? v[0].y : wi == 2 ? v[0].z : v[0].w,
-                             wi == 0 ? v[1].x : wi == 1 ? v[1].y : wi == 2 ? v[1].z : v[1].w,
-                             wi == 0 ? v[2].x : wi == 1 ? v[2].y : wi == 2 ? v[2].z : v[2].w,
-                             wi == 0 ? v[3].x : wi == 1 ? v[3].y : wi == 2 ? v[3].z : v[3].w};
-      *reinterpret_cast<uint2*>(As + (a8 + c) * LDW + q4) = column(w, c);
-    }
-#pragma unroll
-    for (int c = 0; c < BPER; ++c) {
-      const uint32_t w[4] = {gw[0][c >> 1], gw[1][c >> 1], gw[2][c >> 1], gw[3][c >> 1]};
-      *reinterpret_cast<uint2*>(Bs + (b0 + c) * LDW + q4) = column(w, c);
-    }
-    __syncthreads();
-    const int k1 = k0 + 32 * kWgradKS;
-    const bool more = k1 < kWgradChunk && p_begin + k1 < P;
-    if (more) load(k1);
-#pragma unroll
-    for (int kk = 0; kk < KSUB; ++kk) {
-      const int px = (kpart * KSUB + kk) * 16 + lh * 8;
-#pragma unroll
-      for (int b = 0; b < BPW; ++b) {
-        const int blk = KSPLIT > 1 ? wave % NBLK : wave + 4 * b, mb = blk % MBLK, nb = blk / MBLK;
-        const bf16x8 a = lds_frag(As + (mb * 32 + l32) * LDW + px);
-        const bf16x8 bv = lds_frag(Bs + (nb * 32 + l32) * LDW + px);
-        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bv, acc[b], 0, 0, 0);
-      }
-    }
-    __syncthreads();
-    if (!more) break;
-  }
-  if constexpr (KSPLIT > 1) {  // part 0 + part 1 + ... (the stage loop ended on a barrier: As is free)
-    static_assert((KSPLIT - 1) * NBLK * 64 * 16 * 4 <= BM * LDW * 2, "reduction fits As");
-    float* red = reinterpret_cast<float*>(As);
-    const int blk = wave % NBLK;
-    if (kpart > 0) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) red[(((kpart - 1) * NBLK + blk) * 16 + r) * 64 + lane] = acc[0][r];
-    }
-    __syncthreads();
-    if (kpart == 0) {
-#pragma unroll
-      for (int k = 1; k < KSPLIT; ++k)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[0][r] += red[(((k - 1) * NBLK + blk) * 16 + r) * 64 + lane];
-    }
-  }
-  const int ci_n = x.c;
-  if (kpart == 0) {
-#pragma unroll
-    for (int b = 0; b < BPW; ++b) {
-      const int blk = KSPLIT > 1 ? wave % NBLK : wave + 4 * b, mb = blk % MBLK, nb = blk / MBLK;
-      const int co = nb * 32 + l32;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int ci = ci0 + mb * 32 + 8 * (r / 4) + 4 * lh + (r % 4);
-        if (ci < ci_n) partial[((static_cast<size_t>(chunk) * 9 + tap) * ci_n + ci) * BN + co] = acc[b][r];
-      }
-    }
   }
 }
 
-// dw[tap][ci][co] (ci < ci_out) = sum over chunks: a workgroup takes 64
-// outputs; wave g sums chunks g, g + 4, g + 8, ... in order, then the four
-// wave sums are added in wave order (deterministic).
-__global__ void __launch_bounds__(256) wgrad_reduce_k(const float* __restrict__ partial, float* __restrict__ dw,
-                                                      int chunks, int ci_n, int ci_out, int co_n) {
-  __shared__ float red[4][64];
-  const int t = threadIdx.x & 63, g = threadIdx.x >> 6;
-  const long long e = static_cast<long long>(blockIdx.x) * 64 + t;
-  const long long total = 9LL * ci_out * co_n;
-  float sum = 0.f;
-  if (e < total) {
-    const int co = static_cast<int>(e % co_n);
-    const int ci = static_cast<int>((e / co_n) % ci_out);
-    const int tap = static_cast<int>(e / (static_cast<long long>(co_n) * ci_out));
-    for (int c = g; c < chunks; c += 4) sum += partial[((static_cast<size_t>(c) * 9 + tap) * ci_n + ci) * co_n + co];
+// One workgroup's share of layer L, a wave taking NR rows of a tile (8 / 4 / 2
+// with 4 / 2 / 1 blocks).
+template <int NR>
+__device__ __forceinline__ void wgrad_layer(const WgradLayer& L, int local, uint4* lds, float* __restrict__ partial) {
+  constexpr int rows = NR, parts = kWgTH / NR, nblk = 4 / parts;
+  uint4* xs = lds;                   // [2][kWgXP][4]
+  uint4* gs = lds + 2 * kWgXP * 4;   // [2][kWgGP][4]
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int ng = L.cig * L.cog, chunk = local / ng, group = local - chunk * ng;
+  const int c0 = (group % L.cig) * L.cb * 32, o0 = (group / L.cig) * L.ob * 32;
+  const int h = L.s.h, w = L.s.w, sw = L.up ? w / 2 : w, sh = L.up ? h / 2 : h, up = L.up;
+  const int tiles_x = (w + kTW - 1) / kTW, tiles_y = (h + kWgTH - 1) / kWgTH, per_img = tiles_x * tiles_y;
+  const int t0 = static_cast<int>(static_cast<long long>(chunk) * L.tiles / L.chunks);
+  const int t1 = static_cast<int>(static_cast<long long>(chunk + 1) * L.tiles / L.chunks);
+  // wave -> block (c_in slice, c_out slice) and part of the rows
+  const int blk = wave % nblk, part = wave / nblk, bc = blk % L.cb, bo = blk / L.cb;
+  const int l16 = lane & 15, lbyte = ((lane >> 5) * 8 + (l16 >> 2)) * 64 + ((lane >> 4) & 1) * 32 + (l16 & 3) * 8;
+  const int r0 = part * rows;
+  const char* xr = reinterpret_cast<const char*>(xs) + (bc * kWgXP + r0 * (kTW + 2)) * 64 + lbyte;
+  const char* gr = reinterpret_cast<const char*>(gs) + (bo * kWgGP + r0 * kTW) * 64 + lbyte;
+  f32x16 acc[9];
+#pragma unroll
+  for (int t = 0; t < 9; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+  constexpr int XIT = (2 * kWgXP * 4 + 255) / 256, GIT = 2 * kWgGP * 4 / 256;
+  for (int t = t0; t < t1; ++t) {
+    const int n = t / per_img, rem = t - n * per_img, oy = (rem / tiles_x) * kWgTH, ox = (rem % tiles_x) * kTW;
+    const __amdgpu_buffer_rsrc_t xb = buf_rsrc(L.x + static_cast<long long>(n) * sh * sw * L.xld);
+    const __amdgpu_buffer_rsrc_t gb = buf_rsrc(L.g + static_cast<long long>(n) * h * w * L.co);
+    // x, then g: the two together, beside the accumulators, would not fit 256
+    // registers (the other workgroup of the compute unit computes meanwhile)
+    int tl = tid;  // opaque: the chunks' coordinates are computed per tile, not kept beside the accumulators
+    asm volatile("" : "+v"(tl));
+    uint4 xv[XIT];
+#pragma unroll
+    for (int k = 0; k < XIT; ++k) {
+      const int e = tl + 256 * k, sl = e / (kWgXP * 4), q = e - sl * (kWgXP * 4), px = q >> 2, hr = px / (kTW + 2);
+      const int r = oy - 1 + hr, c = ox - 1 + px - hr * (kTW + 2), ch = c0 + sl * 32 + (q & 3) * 8;
+      const int ok = (sl < L.cb) & (static_cast<unsigned>(r) < static_cast<unsigned>(h)) &
+                     (static_cast<unsigned>(c) < static_cast<unsigned>(w)) & (ch < L.xc);
+      const int src = up ? (r >> 1) * sw + (c >> 1) : r * sw + c;
+      xv[k] = buf_load16(xb, ok ? (src * L.xld + ch) * 2 : kOOB);
+    }
+    __syncthreads();  // the previous tile's reads are done
+#pragma unroll
+    for (int k = 0; k < XIT; ++k)
+      if (tl + 256 * k < 2 * kWgXP * 4) xs[tl + 256 * k] = xv[k];
+    __builtin_amdgcn_sched_barrier(0);
+    uint4 gv[GIT];
+#pragma unroll
+    for (int k = 0; k < GIT; ++k) {
+      const int e = tl + 256 * k, sl = e / (kWgGP * 4), q = e - sl * (kWgGP * 4), px = q >> 2;
+      const int r = oy + px / kTW, c = ox + px % kTW, ch = o0 + sl * 32 + (q & 3) * 8;
+      const int ok = (sl < L.ob) & (r < h) & (c < w);
+      gv[k] = buf_load16(gb, ok ? ((r * w + c) * L.co + ch) * 2 : kOOB);
+    }
+#pragma unroll
+    for (int k = 0; k < GIT; ++k) gs[tl + 256 * k] = gv[k];
+    __syncthreads();
+    wgrad_rows<NR>(xr, gr, acc);
   }
-  red[g][t] = sum;
-  __syncthreads();
-  if (g == 0 && e < total) dw[e] = ((red[0][t] + red[1][t]) + red[2][t]) + red[3][t];
+  // the parts of a block, added in a fixed order: 2 and 3 to 0 and 1, then 1 to 0
+  float* red = reinterpret_cast<float*>(lds);
+#pragma unroll
+  for (int half = parts / 2; half > 0; half /= 2) {
+    __syncthreads();
+    if (part >= half && part < 2 * half) {
+      float* q = red + ((part - half) * nblk + blk) * kWgAcc * 64 + lane;
+#pragma unroll
+      for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) q[(t * 16 + r) * 64] = acc[t][r];
+    }
+    __syncthreads();
+    if (part < half) {
+      const float* q = red + (part * nblk + blk) * kWgAcc * 64 + lane;
+#pragma unroll
+      for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[t][r] += q[(t * 16 + r) * 64];
+    }
+  }
+  if (part == 0) {
+    float* q = partial + L.part + (static_cast<size_t>(local) * nblk + blk) * kWgAcc * 64 + lane;
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) q[(t * 16 + r) * 64] = acc[t][r];
+  }
 }
 
-// out[i] = sum over chunks of partial[chunk][i]: a strided sum per thread, then a
-// fixed tree (one workgroup per output): deterministic.
-__global__ void __launch_bounds__(256) chunk_reduce_k(const float* __restrict__ partial, float* __restrict__ out,
-                                                      int chunks, int n) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+wgrad_k(WgradPlan plan, float* __restrict__ partial) {
+  __shared__ __align__(16) uint4 lds[2 * kWgXP * 4 + 2 * kWgGP * 4];
+  const int bid = static_cast<int>(blockIdx.x);
+  int li = 0;
+  for (int i = 1; i < kConvLayers; ++i)
+    if (bid >= plan.l[i].first_wg) li = i;
+  const WgradLayer& L = plan.l[li];
+  const int nblk = L.cb * L.ob;
+  if (nblk == 4) wgrad_layer<8>(L, bid - L.first_wg, lds, partial);
+  else if (nblk == 2) wgrad_layer<4>(L, bid - L.first_wg, lds, partial);
+  else wgrad_layer<2>(L, bid - L.first_wg, lds, partial);
+}
+
+// ------------------------------------------------------- gradient sums, Adam
+__device__ __forceinline__ float adam_step(float w, float gi, float& m, float& v, const AdamArgs& a) {
+  const float mi = a.b1 * m + (1.f - a.b1) * gi;
+  const float vi = a.b2 * v + (1.f - a.b2) * gi * gi;
+  m = mi;
+  v = vi;
+  return w - a.lr * (mi * a.c1) / (sqrtf(vi * a.c2) + a.eps);
+}
+
+// Every parameter's gradient from its partial sums (added in a fixed order)
+// and, with a.update, its Adam step and its bf16 copies, in one launch (38
+// launches before: two sums a layer, Adam, a copy a layer; 8 x 128^2 step:
+// 199 us, now 23).  The first plan.conv_blocks workgroups take 256 conv weights each, in the order
+// the weight gradient's accumulators were stored; the others one bias, output
+// conv parameter or the loss sum each.
+__global__ void __launch_bounds__(256) update_k(UpdatePlan plan, const float* __restrict__ partial, AdamArgs a) {
   __shared__ float red[256];
-  const int i = blockIdx.x, t = threadIdx.x;
+  const int t = threadIdx.x, bid = static_cast<int>(blockIdx.x);
+  if (bid < plan.conv_blocks) {
+    int li = 0;
+    for (int i = 1; i < kConvLayers; ++i)
+      if (bid >= plan.l[i].first_block) li = i;
+    const UpdateLayer& L = plan.l[li];
+    const int e = (bid - L.first_block) * 256 + t;  // [group][block][tap][r][lane]
+    const int nblk = L.cb * L.ob, gb = e / (kWgAcc * 64), q = e - gb * (kWgAcc * 64), group = gb / nblk, blk = gb - group * nblk;
+    const int tap = q >> 10, r = (q >> 6) & 15, lane = q & 63;
+    const int ci = ((group % L.cig) * L.cb + blk % L.cb) * 32 + 8 * (r / 4) + 4 * (lane >> 5) + r % 4;
+    const int co = ((group / L.cig) * L.ob + blk / L.cb) * 32 + (lane & 31);
+    if (ci >= L.ci) return;
+    const size_t step = static_cast<size_t>(L.cig * L.cog) * nblk * kWgAcc * 64;
+    const float* p = partial + L.part + e;
+    float s4[4] = {0.f, 0.f, 0.f, 0.f};
+    int c = 0;
+    for (; c + 4 <= L.chunks; c += 4)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) s4[k] += p[(c + k) * step];
+    for (; c < L.chunks; ++c) s4[0] += p[c * step];
+    const float gi = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+    const int i = L.off_w + (tap * L.ci + ci) * L.co + co;
+    a.g[i] = gi;
+    if (a.update) {
+      const float wn = adam_step(a.w[i], gi, a.m[i], a.v[i], a);
+      a.w[i] = wn;
+      const uint16_t hb = to_bf16(wn);
+      L.wd[(tap * L.ci_pad + ci) * L.co + co] = hb;
+      L.wf[(tap * L.co + co) * L.ci_pad + ci] = hb;
+    }
+    return;
+  }
+  int o = bid - plan.conv_blocks, li = 0;
+  for (int i = 1; i <= kConvLayers; ++i)
+    if (o >= plan.bias[i].first) li = i;
+  const BiasPart& B = plan.bias[li];
+  o -= B.first;
+  const float* p = partial + B.part + o;
   float sum = 0.f;
-  for (int c = t; c < chunks; c += 256) sum += partial[static_cast<size_t>(c) * n + i];
+  for (int c = t; c < B.rows; c += 256) sum += p[static_cast<size_t>(c) * B.n];
   red[t] = sum;
   __syncthreads();
-  for (int h = 128; h > 0; h >>= 1) {
-    if (t < h) red[t] += red[t + h];
+  for (int hf = 128; hf > 0; hf >>= 1) {
+    if (t < hf) red[t] += red[t + hf];
     __syncthreads();
   }
-  if (t == 0) out[i] = red[0];
+  if (t == 0) {
+    const float gi = red[0];
+    if (li == kConvLayers && o == B.n - 1) {  // the output conv's last column is the loss
+      *a.loss = gi;
+    } else {
+      const int i = B.param + o;
+      a.g[i] = gi;
+      if (a.update) a.w[i] = adam_step(a.w[i], gi, a.m[i], a.v[i], a);
+    }
+  }
 }
 
 // ------------------------------------------------------------- glue kernels
-__global__ void avgpool2_k(Map x, Map y, Shape so) {
-  const long long e = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
-  const long long total = so.pixels() * x.c;
-  if (e >= total) return;
-  const int ch = static_cast<int>(e % x.c);
-  const long long p = e / x.c;
-  const Pix q = pixel_of(p, so);
-  const int wi = so.w * 2, hi = so.h * 2;
-  const long long b = (static_cast<long long>(q.n) * hi + 2 * q.r) * wi + 2 * q.c;
-  const float v = from_bf16(x.p[b * x.ld + x.off + ch]) + from_bf16(x.p[(b + 1) * x.ld + x.off + ch]) +
-                  from_bf16(x.p[(b + wi) * x.ld + x.off + ch]) + from_bf16(x.p[(b + wi + 1) * x.ld + x.off + ch]);
-  y.p[p * y.ld + y.off + ch] = to_bf16(0.25f * v);
-}
-
 __global__ void avgpool2_bwd_add_k(MapF dy, MapF dx, Shape si) {
   const long long e = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
   const long long total = si.pixels() * dx.c;
@@ -1087,18 +1136,6 @@ __global__ void avgpool2_bwd_add_k(MapF dy, MapF dx, Shape si) {
   const Pix q = pixel_of(p, si);
   const long long po = (static_cast<long long>(q.n) * (si.h / 2) + q.r / 2) * (si.w / 2) + q.c / 2;
   dx.p[p * dx.ld + dx.off + ch] += 0.25f * dy.p[po * dy.ld + dy.off + ch];
-}
-
-__global__ void upsample2_k(Map x, Map y, Shape si) {
-  const long long e = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
-  Shape so{si.n, si.h * 2, si.w * 2};
-  const long long total = so.pixels() * x.c;
-  if (e >= total) return;
-  const int ch = static_cast<int>(e % x.c);
-  const long long p = e / x.c;
-  const Pix q = pixel_of(p, so);
-  const long long pi = (static_cast<long long>(q.n) * si.h + q.r / 2) * si.w + q.c / 2;
-  y.p[p * y.ld + y.off + ch] = x.p[pi * x.ld + x.off + ch];
 }
 
 __global__ void upsample2_bwd_k(MapF dy, MapF dx, Shape si) {
@@ -1115,15 +1152,6 @@ __global__ void upsample2_bwd_k(MapF dy, MapF dx, Shape si) {
   v += dy.p[(b + wo) * dy.ld + dy.off + ch];
   v += dy.p[(b + wo + 1) * dy.ld + dy.off + ch];
   dx.p[p * dx.ld + dx.off + ch] = v;
-}
-
-__global__ void add_into_k(MapF src, MapF dst, Shape s) {
-  const long long e = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
-  const long long total = s.pixels() * dst.c;
-  if (e >= total) return;
-  const int ch = static_cast<int>(e % dst.c);
-  const long long p = e / dst.c;
-  dst.p[p * dst.ld + dst.off + ch] += src.p[p * src.ld + src.off + ch];
 }
 
 __global__ void out_fwd_k(Map x, const float* __restrict__ w, const float* __restrict__ b,
@@ -1214,19 +1242,6 @@ __global__ void pack_input_k(const float* __restrict__ in, int in_ld, uint16_t* 
 #pragma unroll
   for (int c = 0; c < 6; ++c) h[c] = to_bf16(q[c]);
   *reinterpret_cast<uint4*>(x + p * 8) = uint4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), 0u};
-}
-
-__global__ void adam_k(float* __restrict__ w, const float* __restrict__ g, float* __restrict__ m,
-                       float* __restrict__ v, long long n, float lr, float b1, float b2, float eps,
-                       float c1, float c2) {
-  const long long i = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.f - b1) * gi;
-  const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  w[i] -= lr * (mi * c1) / (sqrtf(vi * c2) + eps);
 }
 
 // master [9][ci][co] -> fwd [9][co][ci_pad] and dgrad [9][ci_pad][co] (bf16,
@@ -1375,16 +1390,13 @@ hipError_t conv3x3_fwd(const Map& x, const uint16_t* w_fwd, const float* bias, c
   return up ? conv_tile<true>(x, xb, w_fwd, bias, y, pl, s, st) : conv_tile<false>(x, xb, w_fwd, bias, y, pl, s, st);
 }
 
-hipError_t conv3x3_gate(const MapF& dy, const Map& y, const Map& g, float* db, float* partial, const Shape& s,
-                        hipStream_t st) {
+int gate_rows(const Shape& s, int c) { return static_cast<int>(blocks(s.pixels() * (c / 8), 256)); }
+
+hipError_t conv3x3_gate(const MapF& dy, const Map& y, const Map& g, float* partial, const Shape& s, hipStream_t st) {
   if (dy.c % 8 || dy.ld % 4 || dy.off % 4 || y.ld % 8 || y.off % 8 || g.ld % 8 || g.off % 8 || g.c != dy.c ||
       256 % (dy.c / 8))
     return hipErrorInvalidValue;
-  const unsigned nb = blocks(s.pixels() * (dy.c / 8), 256);
-  gate_k<<<nb, 256, 0, st>>>(dy, y, g, partial, s);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  chunk_reduce_k<<<dy.c, 256, 0, st>>>(partial, db, static_cast<int>(nb), dy.c);
+  gate_k<<<static_cast<unsigned>(gate_rows(s, dy.c)), 256, 0, st>>>(dy, y, g, partial, s);
   return hipGetLastError();
 }
 
@@ -1400,60 +1412,46 @@ hipError_t conv3x3_dgrad(const Map& g, const uint16_t* w_dgrad, const MapF& dx, 
   return hipGetLastError();
 }
 
-size_t conv3x3_wgrad_scratch(int ci, int co, const Shape& s) {
-  const long long chunks = (s.pixels() + kWgradChunk - 1) / kWgradChunk;
-  const long long bchunks = (s.pixels() * (co / 8) + 255) / 256;  // gate_k's blocks
-  const size_t wsum = static_cast<size_t>(chunks) * 9 * ci * co, bsum = static_cast<size_t>(bchunks) * co;
-  return wsum > bsum ? wsum : bsum;
+// Workgroups of the weight-gradient launch at most, per layer (rows of 64 x 64
+// channel groups included): the layers' shares of about 512, two for every
+// compute unit, by their tiles at the three resolutions and the cycles of a
+// tile (its MFMAs, and as much again to stage it for the 32-channel layers).
+int wgrad_chunks(int layer, long long tiles) {
+  static const int cap[kConvLayers] = {51, 51, 17, 27, 7, 7, 27, 27, 27, 70, 70, 51};
+  return static_cast<int>(tiles < cap[layer] ? (tiles < 1 ? 1 : tiles) : cap[layer]);
+}
+long long wgrad_tiles(const Shape& s) {
+  return static_cast<long long>(s.n) * ((s.h + kWgTH - 1) / kWgTH) * ((s.w + kTW - 1) / kTW);
+}
+size_t wgrad_floats(const WgradLayer& L) {
+  return static_cast<size_t>(L.chunks) * L.cig * L.cog * L.cb * L.ob * kWgAcc * 64;
 }
 
-hipError_t conv3x3_wgrad(const Map& x, const Map& g, float* dw, float* partial, const Shape& s, hipStream_t st,
-                         int ci_out) {
-  const int chunks = static_cast<int>((s.pixels() + kWgradChunk - 1) / kWgradChunk);
-  if (x.c % 8 || x.ld % 8 || x.off % 8) return hipErrorInvalidValue;
-  if (g.ld % 4 || g.off % 4) return hipErrorInvalidValue;
-  dim3 grid(chunks, 9, (x.c + BM - 1) / BM);
-  const bool half = x.c <= 32;  // one 32-row c_in block carries every input channel
-  switch (g.c) {
-    case 32:
-      if (half) conv_wgrad_k<32, true><<<grid, 256, 0, st>>>(x, g, partial, s);
-      else conv_wgrad_k<32, false><<<grid, 256, 0, st>>>(x, g, partial, s);
-      break;
-    case 64:
-      if (half) conv_wgrad_k<64, true><<<grid, 256, 0, st>>>(x, g, partial, s);
-      else conv_wgrad_k<64, false><<<grid, 256, 0, st>>>(x, g, partial, s);
-      break;
-    case 128:
-      if (half) conv_wgrad_k<128, true><<<grid, 256, 0, st>>>(x, g, partial, s);
-      else conv_wgrad_k<128, false><<<grid, 256, 0, st>>>(x, g, partial, s);
-      break;
-    default: return hipErrorInvalidValue;
+hipError_t conv3x3_wgrad(const WgradPlan& plan, float* partial, hipStream_t st) {
+  for (const WgradLayer& L : plan.l) {
+    if (L.xld % 8 || L.xc % 8 || L.co % 32 || reinterpret_cast<uintptr_t>(L.x) % 16 || reinterpret_cast<uintptr_t>(L.g) % 16)
+      return hipErrorInvalidValue;
+    const long long img = static_cast<long long>(L.s.h) * L.s.w;  // per-image byte offsets are 32-bit
+    if (img * L.xld >= (1LL << 30) || img * L.co >= (1LL << 30)) return hipErrorInvalidValue;
   }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  wgrad_reduce_k<<<blocks(9LL * ci_out * g.c, 64), 256, 0, st>>>(partial, dw, chunks, x.c, ci_out, g.c);
+  wgrad_k<<<static_cast<unsigned>(plan.n_wg), 256, 0, st>>>(plan, partial);
   return hipGetLastError();
 }
 
-hipError_t avgpool2(const Map& x, const Map& y, const Shape& s_in, hipStream_t st) {
-  Shape so{s_in.n, s_in.h / 2, s_in.w / 2};
-  avgpool2_k<<<blocks(so.pixels() * x.c, 256), 256, 0, st>>>(x, y, so);
+int update_blocks(const UpdateLayer& L) { return L.cig * L.cog * L.cb * L.ob * kWgAcc * 64 / 256; }
+
+hipError_t update_params(const UpdatePlan& plan, const float* partial, const AdamArgs& a, hipStream_t st) {
+  const int n = plan.conv_blocks + plan.bias[kConvLayers].first + plan.bias[kConvLayers].n;
+  update_k<<<static_cast<unsigned>(n), 256, 0, st>>>(plan, partial, a);
   return hipGetLastError();
 }
+
 hipError_t avgpool2_backward_add(const MapF& dy, const MapF& dx, const Shape& s_in, hipStream_t st) {
   avgpool2_bwd_add_k<<<blocks(s_in.pixels() * dx.c, 256), 256, 0, st>>>(dy, dx, s_in);
   return hipGetLastError();
 }
-hipError_t upsample2(const Map& x, const Map& y, const Shape& s_in, hipStream_t st) {
-  upsample2_k<<<blocks(s_in.pixels() * 4 * x.c, 256), 256, 0, st>>>(x, y, s_in);
-  return hipGetLastError();
-}
 hipError_t upsample2_backward(const MapF& dy, const MapF& dx, const Shape& s_in, hipStream_t st) {
   upsample2_bwd_k<<<blocks(s_in.pixels() * dx.c, 256), 256, 0, st>>>(dy, dx, s_in);
-  return hipGetLastError();
-}
-hipError_t add_into(const MapF& src, const MapF& dst, const Shape& s, hipStream_t st) {
-  add_into_k<<<blocks(s.pixels() * dst.c, 256), 256, 0, st>>>(src, dst, s);
   return hipGetLastError();
 }
 
@@ -1505,30 +1503,14 @@ hipError_t out_conv_fwd(const Map& x, const float* w, const float* b, const floa
   return hipGetLastError();
 }
 
-size_t out_conv_scratch(const Shape& s) {  // per-chunk partials + their sum
-  const long long chunks = (s.pixels() + kOutChunk - 1) / kOutChunk;
-  return static_cast<size_t>(chunks + 1) * (32 * 3 + 4);
-}
+int out_rows(const Shape& s) { return static_cast<int>((s.pixels() + kOutChunk - 1) / kOutChunk); }
 
 hipError_t out_conv_backward(const Map& x, const float* out, const float* target, const float* w, const MapF& dx,
-                             float* dw, float* db, float* loss, float* partial, const Shape& s, hipStream_t st) {
+                             float* partial, const Shape& s, hipStream_t st) {
   if (x.c > 64) return hipErrorInvalidValue;
-  const int chunks = static_cast<int>((s.pixels() + kOutChunk - 1) / kOutChunk);
   const float scale = 2.f / static_cast<float>(s.pixels() * 3);
-  out_bwd_k<<<chunks, 256, 0, st>>>(x, out, target, w, dx, partial, s, scale);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int n = x.c * 3 + 4;
-  // dw (ci*3), db (3) and the loss sum are consecutive in each partial row
-  chunk_reduce_k<<<n, 256, 0, st>>>(partial, partial + static_cast<size_t>(chunks) * n, chunks, n);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const float* red = partial + static_cast<size_t>(chunks) * n;
-  e = hipMemcpyAsync(dw, red, sizeof(float) * x.c * 3, hipMemcpyDeviceToDevice, st);
-  if (e != hipSuccess) return e;
-  e = hipMemcpyAsync(db, red + x.c * 3, sizeof(float) * 3, hipMemcpyDeviceToDevice, st);
-  if (e != hipSuccess) return e;
-  return hipMemcpyAsync(loss, red + x.c * 3 + 3, sizeof(float), hipMemcpyDeviceToDevice, st);
+  out_bwd_k<<<static_cast<unsigned>(out_rows(s)), 256, 0, st>>>(x, out, target, w, dx, partial, s, scale);
+  return hipGetLastError();
 }
 
 hipError_t pack_input(const float* in, int in_ld, uint16_t* x, const Shape& s, hipStream_t st) {
@@ -1537,11 +1519,6 @@ hipError_t pack_input(const float* in, int in_ld, uint16_t* x, const Shape& s, h
   return hipGetLastError();
 }
 
-hipError_t adam_update(float* w, const float* g, float* m, float* v, long long n, float lr, float beta1, float beta2,
-                       float eps, float c1, float c2, hipStream_t st) {
-  adam_k<<<blocks(n, 256), 256, 0, st>>>(w, g, m, v, n, lr, beta1, beta2, eps, c1, c2);
-  return hipGetLastError();
-}
 
 hipError_t refresh_bf16(const float* w_master, uint16_t* w_fwd, uint16_t* w_dgrad, int ci, int co, hipStream_t st) {
   const int ci_pad = (ci + 7) / 8 * 8;

@@ -70,16 +70,15 @@ struct dfb_denoiser_ctx {
   // activations (bf16) at the maximum size
   int64_t P0 = 0;
   uint16_t *xin = nullptr, *e1a = nullptr, *cat1 = nullptr, *pool1 = nullptr, *e2a = nullptr, *cat2 = nullptr,
-           *pool2 = nullptr, *e3a = nullptr, *e3b = nullptr, *up3 = nullptr, *d2a = nullptr, *d2b = nullptr,
-           *upd2 = nullptr, *d1a = nullptr, *d1b = nullptr;
+           *pool2 = nullptr, *e3a = nullptr, *e3b = nullptr, *d2a = nullptr, *d2b = nullptr,
+           *d1a = nullptr, *d1b = nullptr;
   float* out = nullptr;  // [P0][3] network output of the last forward
   // gradients (f32)
   float *g_d1b = nullptr, *g_d1a = nullptr, *g_cat1 = nullptr, *g_upd2 = nullptr, *g_d2b = nullptr,
         *g_d2a = nullptr, *g_cat2 = nullptr, *g_up3 = nullptr, *g_e3b = nullptr, *g_e3a = nullptr,
         *g_pool2 = nullptr, *g_e2a = nullptr, *g_pool1 = nullptr, *g_e1a = nullptr;
-  float* scratch = nullptr;
-  size_t scratch_n = 0;
-  uint16_t* gate = nullptr;  // gated output gradient of the layer in the backward pass (bf16)
+  float* scratch = nullptr;    // partial sums of every gradient (TrainPlan)
+  uint16_t* gate[12] = {};     // gated output gradients of the layers (bf16)
   float* loss_dev = nullptr;
   Shape last{0, 0, 0};
   bool planar = false;  // the last forward kept the skip concatenations as separate maps
@@ -152,8 +151,8 @@ CatLayout cat_layout(const dfb_denoiser_ctx* n, const Shape& s0, bool planar) {
 
 // forward on in (f32 NHWC 6 ch) -> n->out.  The 2x2 pools come out of the
 // enc1b / enc2b epilogues and the up-sampling is read through by up2 / up1;
-// `training` also materialises the up-sampled maps the backward pass reads
-// and keeps the skip concatenations interleaved.  With a frame `fv`
+// `training` keeps the skip concatenations interleaved, as the backward pass
+// reads them.  With a frame `fv`
 // (inference; in unused) the first layer reads its input from the frame's
 // accumulation, and the last computes the output conv in its epilogue and
 // writes the frame's denoised and display pixels (fallback threshold tau)
@@ -179,14 +178,12 @@ dfb_status forward(dfb_denoiser_ctx* n, const float* in, const Shape& s0, bool t
   NHIP(n, conv3x3_fwd(mp(n->e2a, 64, 0, 64), n->wf[ENC2B], B(ENC2B), c.enc2b, s1, st, false, &pool2));
   NHIP(n, conv3x3_fwd(pool2, n->wf[ENC3A], B(ENC3A), mp(n->e3a, 128, 0, 128), s2, st));
   NHIP(n, conv3x3_fwd(mp(n->e3a, 128, 0, 128), n->wf[ENC3B], B(ENC3B), mp(n->e3b, 128, 0, 128), s2, st));
-  if (training) NHIP(n, dfb::unet::upsample2(mp(n->e3b, 128, 0, 128), mp(n->up3, 128, 0, 128), s2, st));
   NHIP(n, conv3x3_fwd(mp(n->e3b, 128, 0, 128), n->wf[UP2], B(UP2), c.up2, s1, st, true));
   if (training)
     NHIP(n, conv3x3_fwd(mp(n->cat2, 128, 0, 128), n->wf[DEC2A], B(DEC2A), mp(n->d2a, 64, 0, 64), s1, st));
   else
     NHIP(n, conv3x3_fwd(c.up2, n->wf[DEC2A], B(DEC2A), mp(n->d2a, 64, 0, 64), s1, st, false, nullptr, &c.enc2b));
   NHIP(n, conv3x3_fwd(mp(n->d2a, 64, 0, 64), n->wf[DEC2B], B(DEC2B), mp(n->d2b, 64, 0, 64), s1, st));
-  if (training) NHIP(n, dfb::unet::upsample2(mp(n->d2b, 64, 0, 64), mp(n->upd2, 64, 0, 64), s1, st));
   NHIP(n, conv3x3_fwd(mp(n->d2b, 64, 0, 64), n->wf[UP1], B(UP1), c.up1, s0, st, true));
   if (training)
     NHIP(n, conv3x3_fwd(mp(n->cat1, 64, 0, 64), n->wf[DEC1A], B(DEC1A), mp(n->d1a, 32, 0, 32), s0, st));
@@ -206,24 +203,82 @@ dfb_status forward(dfb_denoiser_ctx* n, const float* in, const Shape& s0, bool t
   return DFB_OK;
 }
 
-dfb_status backward(dfb_denoiser_ctx* n, const float* target, const Shape& s0) {
-  const Shape s1{s0.n, s0.h / 2, s0.w / 2}, s2{s0.n, s0.h / 4, s0.w / 4};
+Shape level_shape(const Shape& s0, int level) { return Shape{s0.n, s0.h >> level, s0.w >> level}; }
+
+// Where the partial sums of a training step on a batch of shape s0 lie in the
+// scratch allocation, and what the two launches that make and use them take.
+struct TrainPlan {
+  dfb::unet::WgradPlan wg;
+  dfb::unet::UpdatePlan up;
+  size_t floats;
+};
+TrainPlan train_plan(const dfb_denoiser_ctx* n, const Shape& s0) {
+  TrainPlan T{};
+  const struct {
+    const uint16_t* x;
+    int ld, up;
+  } in[12] = {{n->xin, 8, 0},   {n->e1a, 32, 0},   {n->pool1, 32, 0},  {n->e2a, 64, 0}, {n->pool2, 64, 0}, {n->e3a, 128, 0},
+              {n->e3b, 128, 1}, {n->cat2, 128, 0}, {n->d2a, 64, 0}, {n->d2b, 64, 1},   {n->cat1, 64, 0},  {n->d1a, 32, 0}};
+  int first_out = 0;
+  for (int i = 0; i < 12; ++i) {
+    const Conv& c = kConv[i];
+    const Shape s = level_shape(s0, c.level);
+    dfb::unet::WgradLayer& L = T.wg.l[i];
+    const int ci_pad = (c.ci + 7) / 8 * 8;
+    L.x = in[i].x;
+    L.g = n->gate[i];
+    L.xld = in[i].ld;
+    L.xc = ci_pad;
+    L.co = c.co;
+    L.up = in[i].up;
+    L.s = s;
+    L.cb = c.ci > 32 ? 2 : 1;
+    L.ob = c.co > 32 ? 2 : 1;
+    L.cig = (c.ci + 63) / 64;
+    L.cog = (c.co + 63) / 64;
+    L.tiles = static_cast<int>(dfb::unet::wgrad_tiles(s));
+    L.chunks = dfb::unet::wgrad_chunks(i, L.tiles);
+    L.first_wg = T.wg.n_wg;
+    L.part = T.floats;
+    T.wg.n_wg += L.chunks * L.cig * L.cog;
+    T.floats += dfb::unet::wgrad_floats(L);
+    dfb::unet::UpdateLayer& U = T.up.l[i];
+    U.cb = L.cb;
+    U.ob = L.ob;
+    U.cig = L.cig;
+    U.cog = L.cog;
+    U.chunks = L.chunks;
+    U.first_block = T.up.conv_blocks;
+    U.ci = c.ci;
+    U.ci_pad = ci_pad;
+    U.co = c.co;
+    U.off_w = static_cast<int>(n->off_w[i]);
+    U.part = L.part;
+    U.wf = n->wf[i];
+    U.wd = n->wd[i];
+    T.up.conv_blocks += dfb::unet::update_blocks(U);
+    T.up.bias[i] = {first_out, c.co, dfb::unet::gate_rows(s, c.co), static_cast<int>(n->off_b[i]), T.floats};
+    T.floats += static_cast<size_t>(T.up.bias[i].rows) * c.co;
+    first_out += c.co;
+  }
+  T.up.bias[12] = {first_out, 100, dfb::unet::out_rows(s0), static_cast<int>(n->off_ow), T.floats};
+  T.floats += static_cast<size_t>(T.up.bias[12].rows) * 100;
+  return T;
+}
+
+dfb_status backward(dfb_denoiser_ctx* n, const float* target, const Shape& s0, const TrainPlan& T) {
+  const Shape s1 = level_shape(s0, 1), s2 = level_shape(s0, 2);
   hipStream_t st = n->stream;
-  float* G = n->g;
-  auto gw = [&](int i) { return G + n->off_w[i]; };
-  auto gb = [&](int i) { return G + n->off_b[i]; };
   float* S = n->scratch;
   using namespace dfb::unet;
   NHIP(n, out_conv_backward(mp(n->d1b, 32, 0, 32), n->out, target, n->w + n->off_ow, mf(n->g_d1b, 32, 0, 32),
-                            G + n->off_ow, G + n->off_ob, n->loss_dev, S, s0, st));
+                            S + T.up.bias[12].part, s0, st));
   // one conv layer: gate its output gradient dy (output y) once, with the
-  // bias gradient, then the data gradient into dx (unless null) and the
-  // weight gradient
-  auto layer = [&](int L, const MapF& dy, const Map& y, const Map& x, const MapF* dx, const Shape& sh, int ci_out) {
-    const Map gm{n->gate, dy.c, 0, dy.c};
-    hipError_t e = conv3x3_gate(dy, y, gm, gb(L), S, sh, st);
+  // bias gradient's partial sums, then the data gradient into dx (unless null)
+  auto layer = [&](int L, const MapF& dy, const Map& y, const MapF* dx, const Shape& sh) {
+    const Map gm{n->gate[L], dy.c, 0, dy.c};
+    hipError_t e = conv3x3_gate(dy, y, gm, S + T.up.bias[L].part, sh, st);
     if (e == hipSuccess && dx) e = conv3x3_dgrad(gm, n->wd[L], *dx, sh, st);
-    if (e == hipSuccess) e = conv3x3_wgrad(x, gm, gw(L), S, sh, st, ci_out);
     return e;
   };
   const MapF dx_d1a = mf(n->g_d1a, 32, 0, 32), dx_cat1 = mf(n->g_cat1, 64, 0, 64), dx_upd2 = mf(n->g_upd2, 64, 0, 64);
@@ -231,28 +286,30 @@ dfb_status backward(dfb_denoiser_ctx* n, const float* target, const Shape& s0) {
   const MapF dx_e3a = mf(n->g_e3a, 128, 0, 128), dx_pool2 = mf(n->g_pool2, 64, 0, 64), dx_e2a = mf(n->g_e2a, 64, 0, 64);
   const MapF dx_pool1 = mf(n->g_pool1, 32, 0, 32), dx_e1a = mf(n->g_e1a, 32, 0, 32);
   // dec1b, dec1a
-  NHIP(n, layer(DEC1B, mf(n->g_d1b, 32, 0, 32), mp(n->d1b, 32, 0, 32), mp(n->d1a, 32, 0, 32), &dx_d1a, s0, 32));
-  NHIP(n, layer(DEC1A, mf(n->g_d1a, 32, 0, 32), mp(n->d1a, 32, 0, 32), mp(n->cat1, 64, 0, 64), &dx_cat1, s0, 64));
+  NHIP(n, layer(DEC1B, mf(n->g_d1b, 32, 0, 32), mp(n->d1b, 32, 0, 32), &dx_d1a, s0));
+  NHIP(n, layer(DEC1A, mf(n->g_d1a, 32, 0, 32), mp(n->d1a, 32, 0, 32), &dx_cat1, s0));
   // up1 (input: upsampled dec2b), output cat1[0:32]
-  NHIP(n, layer(UP1, mf(n->g_cat1, 64, 0, 32), mp(n->cat1, 64, 0, 32), mp(n->upd2, 64, 0, 64), &dx_upd2, s0, 64));
+  NHIP(n, layer(UP1, mf(n->g_cat1, 64, 0, 32), mp(n->cat1, 64, 0, 32), &dx_upd2, s0));
   NHIP(n, upsample2_backward(mf(n->g_upd2, 64, 0, 64), mf(n->g_d2b, 64, 0, 64), s1, st));
   // dec2b, dec2a
-  NHIP(n, layer(DEC2B, mf(n->g_d2b, 64, 0, 64), mp(n->d2b, 64, 0, 64), mp(n->d2a, 64, 0, 64), &dx_d2a, s1, 64));
-  NHIP(n, layer(DEC2A, mf(n->g_d2a, 64, 0, 64), mp(n->d2a, 64, 0, 64), mp(n->cat2, 128, 0, 128), &dx_cat2, s1, 128));
+  NHIP(n, layer(DEC2B, mf(n->g_d2b, 64, 0, 64), mp(n->d2b, 64, 0, 64), &dx_d2a, s1));
+  NHIP(n, layer(DEC2A, mf(n->g_d2a, 64, 0, 64), mp(n->d2a, 64, 0, 64), &dx_cat2, s1));
   // up2 (input: upsampled enc3b), output cat2[0:64]
-  NHIP(n, layer(UP2, mf(n->g_cat2, 128, 0, 64), mp(n->cat2, 128, 0, 64), mp(n->up3, 128, 0, 128), &dx_up3, s1, 128));
+  NHIP(n, layer(UP2, mf(n->g_cat2, 128, 0, 64), mp(n->cat2, 128, 0, 64), &dx_up3, s1));
   NHIP(n, upsample2_backward(mf(n->g_up3, 128, 0, 128), mf(n->g_e3b, 128, 0, 128), s2, st));
   // enc3b, enc3a
-  NHIP(n, layer(ENC3B, mf(n->g_e3b, 128, 0, 128), mp(n->e3b, 128, 0, 128), mp(n->e3a, 128, 0, 128), &dx_e3a, s2, 128));
-  NHIP(n, layer(ENC3A, mf(n->g_e3a, 128, 0, 128), mp(n->e3a, 128, 0, 128), mp(n->pool2, 64, 0, 64), &dx_pool2, s2, 64));
+  NHIP(n, layer(ENC3B, mf(n->g_e3b, 128, 0, 128), mp(n->e3b, 128, 0, 128), &dx_e3a, s2));
+  NHIP(n, layer(ENC3A, mf(n->g_e3a, 128, 0, 128), mp(n->e3a, 128, 0, 128), &dx_pool2, s2));
   // skip 2: the enc2b output also fed pool2
   NHIP(n, avgpool2_backward_add(mf(n->g_pool2, 64, 0, 64), mf(n->g_cat2, 128, 64, 64), s1, st));
-  NHIP(n, layer(ENC2B, mf(n->g_cat2, 128, 64, 64), mp(n->cat2, 128, 64, 64), mp(n->e2a, 64, 0, 64), &dx_e2a, s1, 64));
-  NHIP(n, layer(ENC2A, mf(n->g_e2a, 64, 0, 64), mp(n->e2a, 64, 0, 64), mp(n->pool1, 32, 0, 32), &dx_pool1, s1, 32));
+  NHIP(n, layer(ENC2B, mf(n->g_cat2, 128, 64, 64), mp(n->cat2, 128, 64, 64), &dx_e2a, s1));
+  NHIP(n, layer(ENC2A, mf(n->g_e2a, 64, 0, 64), mp(n->e2a, 64, 0, 64), &dx_pool1, s1));
   // skip 1: the enc1b output also fed pool1
   NHIP(n, avgpool2_backward_add(mf(n->g_pool1, 32, 0, 32), mf(n->g_cat1, 64, 32, 32), s0, st));
-  NHIP(n, layer(ENC1B, mf(n->g_cat1, 64, 32, 32), mp(n->cat1, 64, 32, 32), mp(n->e1a, 32, 0, 32), &dx_e1a, s0, 32));
-  NHIP(n, layer(ENC1A, mf(n->g_e1a, 32, 0, 32), mp(n->e1a, 32, 0, 32), mp(n->xin, 8, 0, 8), nullptr, s0, 6));
+  NHIP(n, layer(ENC1B, mf(n->g_cat1, 64, 32, 32), mp(n->cat1, 64, 32, 32), &dx_e1a, s0));
+  NHIP(n, layer(ENC1A, mf(n->g_e1a, 32, 0, 32), mp(n->e1a, 32, 0, 32), nullptr, s0));
+  // every layer's weight gradient
+  NHIP(n, conv3x3_wgrad(T.wg, S, st));
   return DFB_OK;
 }
 
@@ -321,8 +378,8 @@ dfb_status dfb_denoiser_create(const dfb_unet_config* cfg, void* hip_stream, dfb
     int64_t n;
   } acts[] = {{&n->xin, P0 * 8},   {&n->e1a, P0 * 32},   {&n->cat1, P0 * 64}, {&n->pool1, P1 * 32},
               {&n->e2a, P1 * 64},  {&n->cat2, P1 * 128}, {&n->pool2, P2 * 64}, {&n->e3a, P2 * 128},
-              {&n->e3b, P2 * 128}, {&n->up3, P1 * 128},  {&n->d2a, P1 * 64},  {&n->d2b, P1 * 64},
-              {&n->upd2, P0 * 64}, {&n->d1a, P0 * 32},   {&n->d1b, P0 * 32}};
+              {&n->e3b, P2 * 128}, {&n->d2a, P1 * 64},  {&n->d2b, P1 * 64},
+              {&n->d1a, P0 * 32},  {&n->d1b, P0 * 32}};
   for (auto& a : acts)
     if ((s = dalloc(n, a.p, static_cast<size_t>(a.n)))) return bail(s);
   struct {
@@ -334,16 +391,14 @@ dfb_status dfb_denoiser_create(const dfb_unet_config* cfg, void* hip_stream, dfb
                {&n->g_pool1, P1 * 32}, {&n->g_e1a, P0 * 32}, {&n->out, P0 * 3}};
   for (auto& a : grads)
     if ((s = dalloc(n, a.p, static_cast<size_t>(a.n)))) return bail(s);
-  size_t sc = dfb::unet::out_conv_scratch(Shape{1, 1, static_cast<int>(P0)});
   for (int i = 0; i < 12; ++i) {
-    const int lvl = kConv[i].level;
-    const int64_t px = lvl == 0 ? P0 : (lvl == 1 ? P1 : P2);
-    const int ci_store = kConv[i].ci == 6 ? 8 : kConv[i].ci;
-    sc = std::max(sc, dfb::unet::conv3x3_wgrad_scratch(ci_store, kConv[i].co, Shape{1, 1, static_cast<int>(px)}));
+    const int64_t px = kConv[i].level == 0 ? P0 : (kConv[i].level == 1 ? P1 : P2);
+    if ((s = dalloc(n, &n->gate[i], static_cast<size_t>(px * kConv[i].co)))) return bail(s);
   }
-  n->scratch_n = sc;
+  // the most partial sums of any batch of at most P0 pixels: its images are at
+  // least 4 x 4, so the smallest ones have the most tiles
+  const size_t sc = train_plan(n, Shape{static_cast<int>((P0 + 15) / 16), 4, 4}).floats;
   if ((s = dalloc(n, &n->scratch, sc)) || (s = dalloc(n, &n->loss_dev, 4))) return bail(s);
-  if ((s = dalloc(n, &n->gate, static_cast<size_t>(std::max(P0 * 32, std::max(P1 * 64, P2 * 128)))))) return bail(s);
   // initial parameters: He-normal conv3x3 weights, zero biases, N(0, 0.01) output weights
   std::vector<float> h(np, 0.f);
   uint64_t st = 0x5DEECE66Dull ^ cfg->seed;
@@ -402,16 +457,17 @@ dfb_status dfb_denoiser_train_step(dfb_denoiser n, const float* in, const float*
   if (!in || !target) return nfail(n, DFB_ERR_INVALID_ARG, "null tensor");
   if ((s = check_shape(n, b, h, w)) != DFB_OK) return s;
   const Shape s0{b, h, w};
+  const TrainPlan T = train_plan(n, s0);
   if ((s = forward(n, in, s0, true)) != DFB_OK) return s;
-  if ((s = backward(n, target, s0)) != DFB_OK) return s;
+  if ((s = backward(n, target, s0, T)) != DFB_OK) return s;
+  dfb::unet::AdamArgs a{n->w, n->g, n->m, n->v, n->loss_dev, lr, n->cfg.beta1, n->cfg.beta2, n->cfg.eps, 1.f, 1.f, 0};
   if (apply_update) {
     n->step += 1;
-    const float c1 = 1.f / (1.f - std::pow(n->cfg.beta1, static_cast<float>(n->step)));
-    const float c2 = 1.f / (1.f - std::pow(n->cfg.beta2, static_cast<float>(n->step)));
-    NHIP(n, dfb::unet::adam_update(n->w, n->g, n->m, n->v, n->n_params, lr, n->cfg.beta1, n->cfg.beta2, n->cfg.eps,
-                                   c1, c2, n->stream));
-    if ((s = refresh(n)) != DFB_OK) return s;
+    a.update = 1;
+    a.c1 = 1.f / (1.f - std::pow(n->cfg.beta1, static_cast<float>(n->step)));
+    a.c2 = 1.f / (1.f - std::pow(n->cfg.beta2, static_cast<float>(n->step)));
   }
+  NHIP(n, dfb::unet::update_params(T.up, n->scratch, a, n->stream));
   if (loss_out) {
     float sum = 0.f;
     NHIP(n, hipMemcpyAsync(&sum, n->loss_dev, sizeof(float), hipMemcpyDeviceToHost, n->stream));
