@@ -24,14 +24,17 @@ constexpr int kDeepPx = 32;  // pixels of a row-sort group: one 128-byte line of
 // Each counter has kSlots per-frame slots used as a ring: frame f counts in
 // slot f mod kSlots and clears slot (f + kSlots/2) mod kSlots, which no
 // frame in flight uses, so nothing is reset between frames.  A ring is the
-// kQueues counter pages and one page of per-slot "workgroups finished"
-// counters.  A frame runs up to three launches over the same work list --
-// the tiles of more than kDeepMax layers, those of more than kRegMax, then
-// the rest -- each with a ring of its own; after the rings comes one page
-// holding the FrameState below.
+// kQueues counter pages and one page more; kFinishWord words into a page lie
+// the slots of its "workgroups finished" counter (the counters' own, then the
+// one that counts the counters).  A frame runs up to three launches over the
+// same work list -- the tiles of more than kDeepMax layers, those of more
+// than kRegMax, then the rest, which counts its finished workgroups -- each
+// with a ring of its own; after the rings comes one page holding the
+// FrameState below.
 constexpr int kQueues = 16;
 constexpr int kQueueStride = 1024;  // 4-byte counters between queues
 constexpr int kSlots = 64;
+constexpr int kFinishWord = 512;    // in a page, so a ticket and a finish counter share no line
 constexpr int kRingWords = (kQueues + 1) * kQueueStride;
 constexpr int kRings = 3;
 constexpr int kQueueWords = kRings * kRingWords + kQueueStride;  // the whole allocation, in u32
@@ -47,6 +50,14 @@ struct FrameState {
 // Ring r (0: the register-path launch, 1: the LDS sort's, 2: the row sort's)
 // and the frame state inside a queue allocation.
 inline uint32_t* ring_of(uint32_t* queue_base, int r) { return queue_base + r * kRingWords; }
+// Units that counter s of S holds of n_work units dealt in blocks of B.
+__host__ __device__ inline int queue_units(int n_work, int B, int S, int s) {
+  const int nb = (n_work + B - 1) / B;
+  const int cnt = s < nb ? (nb - s + S - 1) / S : 0;
+  int n = cnt * B;
+  if (cnt > 0 && s + (cnt - 1) * S == nb - 1 && n_work % B) n -= B - n_work % B;  // partial last block
+  return n;
+}
 inline FrameState* state_of(uint32_t* queue_base) {
   return reinterpret_cast<FrameState*>(queue_base + kRings * kRingWords);
 }
@@ -75,11 +86,10 @@ enum ModeBits : uint32_t {
 // table, the fragment buffer and the launch shape stay the same.
 struct FrameArgs {
   const void* frag;            // fragment blocks (caller's buffer)
-  uint32_t* queue;             // this launch's ring: kQueues x kSlots counters, queues
-                               // kQueueStride apart, then the kSlots finish counters
-  uint32_t* rings;             // all kRings rings (the last launch recycles a slot of each)
+  uint32_t* queue;             // this launch's ring
+  uint32_t* rings;             // all kRings rings (the frame's last launch recycles a slot of each)
   FrameState* state;           // the frame state (shared by the frame's launches)
-  int32_t advance;             // 1: the last workgroup advances the state (the frame's last launch)
+  int32_t one_each;            // no counter holds more units than workgroups start on it: no tickets
   int32_t slot, clear_slot;    // set by the kernel from FrameState::seq
   int32_t n_queues;            // counters in use: min(kQueues, grid)
   int32_t queue_block;         // consecutive work-list positions per counter block (units per tile)

@@ -1128,27 +1128,25 @@ __device__ __forceinline__ float variance_of_mean(float sum, int inside_px, int 
 // workgroups (no atomic).  Each ticket c of a counter names its unit g + c,
 // g being the number of workgroups that start on it.  Lane 0 of wave 0
 // takes the next ticket at the start of a unit and the result is read at
-// its end, so the atomic's latency hides behind the unit's work.  A drained
-// counter sends the workgroup on to the next one (s + 1, s + 2, ... mod S);
-// a coherent read skips counters that are already drained without an
-// atomic.  Workgroups are dealt to the 8 XCDs in turn and S is a multiple of
-// 8 on every grid of 8 workgroups or more, so the units of one tile run at
-// about the same time under one XCD's L2: unit rows that share cache lines
-// (fp16 planes, units narrower than a line) are fetched from memory once.
+// its end, so the atomic's latency hides behind the unit's work.  A workgroup
+// whose counter is drained reads all counters at once, one a lane, and goes
+// on to the next open one (s + 1, s + 2, ... mod S) or ends.  A launch whose
+// counters hold no more units than workgroups start on them (a.one_each)
+// takes no tickets at all.  Workgroups are dealt to the 8 XCDs in turn and S
+// is a multiple of 8 on every grid of 8 workgroups or more, so the units of
+// one tile run at about the same time under one XCD's L2: unit rows that
+// share cache lines (fp16 planes, units narrower than a line) are fetched
+// from memory once.
 struct Queue {
   uint32_t* ctr;
   int s, g, n;  // counter, workgroups starting on it, units it holds
 };
 
 __device__ __forceinline__ Queue queue_of(const FrameArgs& a, int s) {
-  const int S = a.n_queues, B = a.queue_block;
-  const int nb = (a.n_work + B - 1) / B;  // blocks
-  const int cnt = s < nb ? (nb - s + S - 1) / S : 0;
   Queue q;
   q.s = s;
-  q.g = (static_cast<int>(gridDim.x) - s + S - 1) / S;
-  q.n = cnt * B;
-  if (cnt > 0 && s + (cnt - 1) * S == nb - 1 && a.n_work % B) q.n -= B - a.n_work % B;  // partial last block
+  q.g = (static_cast<int>(gridDim.x) - s + a.n_queues - 1) / a.n_queues;
+  q.n = queue_units(a.n_work, a.queue_block, a.n_queues, s);
   q.ctr = a.queue + static_cast<size_t>(s) * kQueueStride + a.slot;
   return q;
 }
@@ -1170,12 +1168,28 @@ __device__ __forceinline__ int ticket_to_unit(const FrameArgs& a, const Queue& q
   return j < q.n ? unit_at(a, q, static_cast<int>(j)) : a.n_work;
 }
 
-// Whether a counter may still hand out a unit (never wrong the other way:
-// counters only grow within a frame).
-__device__ __forceinline__ bool queue_open(const Queue& q) {
-  uint32_t v = 0;
-  if (__lane_id() == 0) v = __hip_atomic_load(q.ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return static_cast<int64_t>(__builtin_amdgcn_readfirstlane(v)) + q.g < q.n;
+// The next unit after counter q has no more for this launch (wave 0, all
+// lanes): lane s reads counter s, so finding the open ones costs one trip to
+// the coherent level and not one a counter.  `closed` holds the counters this
+// workgroup is done with, so the loop ends.  Reading them in turn put 15
+// dependent trips behind the last unit of every workgroup; kernel times
+// before, and now with the split finish counts and ticketless launches too:
+// 256^2, 4 ranks 13.9 -> 7.1 us, 1280x720 27.4 -> 15.5, 1920x1080 fp16 average
+// 25.4 -> 21.3, 4096x1024 fp16 159 -> 154 a frame.
+__device__ __forceinline__ int next_open_unit(const FrameArgs& a, Queue& q, uint64_t& closed) {
+  const int S = a.n_queues, lane = static_cast<int>(__lane_id());
+  const Queue mine = queue_of(a, lane < S ? lane : 0);
+  int v = a.n_work;
+  while (v == a.n_work) {
+    closed |= 1ull << q.s;
+    const uint32_t c = __hip_atomic_load(mine.ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint64_t open = __ballot(lane < S && static_cast<int64_t>(c) + mine.g < mine.n) & ~closed;
+    if (open == 0) break;
+    const uint64_t after = open & (~0ull << q.s);  // counters past q.s first, then from 0
+    q = queue_of(a, __builtin_ctzll(after ? after : open));
+    v = ticket_to_unit(a, q, take_ticket(q));
+  }
+  return v;
 }
 
 // A unit's M2 sum (all waves) -> var_partial[w].  Runs on all lanes of wave
@@ -1202,26 +1216,23 @@ constexpr int min_waves(int kcap, bool half) {
                                                                  : (DFB_WAVES_K32 > 0 ? DFB_WAVES_K32 : 1));
 }
 
-__device__ __forceinline__ uint32_t* finish_counters(const FrameArgs& a) {
-  return a.queue + static_cast<size_t>(kQueues) * kQueueStride;
-}
 __device__ __forceinline__ FrameState* frame_state(const FrameArgs& a) { return a.state; }
 
-// The frame's sequence number and accumulation count, read once per
-// workgroup from the device state and shared through LDS.  The load's value
-// is stored to LDS before the barrier, so it has returned before anything
-// else of the workgroup runs; the last workgroup to finish advances the
-// state only after every workgroup has counted itself finished, hence after
-// every read of this frame.
-__device__ __forceinline__ uint32_t read_frame_state(FrameArgs& a, uint32_t* s_state) {
-  if (threadIdx.x == 0) {
-    const FrameState* st = frame_state(a);
-    s_state[0] = __hip_atomic_load(&st->seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s_state[1] = static_cast<uint32_t>(__hip_atomic_load(&st->n_acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-  }
-  lds_barrier();
-  const uint32_t seq = __builtin_amdgcn_readfirstlane(s_state[0]);
-  const int n_prev = static_cast<int>(__builtin_amdgcn_readfirstlane(s_state[1]));
+// The frame's sequence number and accumulation count, read by every wave from
+// the device state.  Nothing waits for them until they are used, so the
+// unit's table reads run meanwhile; a wave that uses one has its value before
+// the barrier that ends its first unit, and the last workgroup to finish
+// advances the state only after every workgroup has counted itself finished,
+// hence after every read of this frame.
+__device__ __forceinline__ uint32_t read_frame_state(FrameArgs& a) {
+  const FrameState* st = frame_state(a);
+  const uint32_t seq = __hip_atomic_load(&st->seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  a.n_acc = __hip_atomic_load(&st->n_acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return seq;
+}
+__device__ __forceinline__ uint32_t use_frame_state(FrameArgs& a, uint32_t seq_in) {
+  const uint32_t seq = __builtin_amdgcn_readfirstlane(seq_in);
+  const int n_prev = static_cast<int>(__builtin_amdgcn_readfirstlane(a.n_acc));
   a.slot = static_cast<int32_t>(seq % kSlots);
   a.clear_slot = static_cast<int32_t>((seq + kSlots / 2) % kSlots);
   a.n_acc = (a.mode & kModeAccumulate) ? n_prev + 1 : n_prev;
@@ -1233,27 +1244,36 @@ __device__ __forceinline__ uint32_t read_frame_state(FrameArgs& a, uint32_t* s_s
 // every ring.  The frame's last launch does it for all of them: a frame of
 // another layer layout may not run the other launches, and a slot left
 // uncleared would hand out no units kSlots frames later.
-__device__ __forceinline__ void recycle_slots(const FrameArgs& a, int tid) {
-  if (tid < kRings * (kQueues + 1))  // at most 51 words, by the first wave
-    __hip_atomic_store(a.rings + static_cast<size_t>(tid) * kQueueStride + a.clear_slot, 0u, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ void recycle_slots(const FrameArgs& a) {
+  constexpr int kPages = kRings * (kQueues + 1);
+  for (int i = threadIdx.x; i < 2 * kPages; i += blockDim.x)  // a page's ticket and finish counters
+    __hip_atomic_store(a.rings + static_cast<size_t>(i % kPages) * kQueueStride + (i / kPages) * kFinishWord + a.clear_slot,
+                       0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Count a workgroup finished (thread 0); the last workgroup of the frame's
-// last launch advances the frame state for the next frame (sequence number,
-// and the accumulation count of an accumulating frame).  Every queue access
-// of the workgroup has returned its value before this point.
-__device__ __forceinline__ void finish_workgroup(const FrameArgs& a, uint32_t seq, bool wave0) {
+// Count a workgroup finished (thread 0): among the workgroups of its home
+// counter, and the last of those among the counters, so that no address takes
+// more than grid / kQueues adds (an add to one address takes about 16 ns: 960
+// workgroups that end together would queue for 15 us).  The last workgroup
+// advances the frame state for the next frame (sequence number, and the
+// accumulation count of an accumulating frame).  Every queue access of the
+// workgroup has returned its value before this point.  Only the frame's last
+// launch is counted.
+__device__ __forceinline__ void finish_workgroup(const FrameArgs& a, uint32_t seq, int home) {
   const int tid = threadIdx.x;
+  const int g = (static_cast<int>(gridDim.x) - home + a.n_queues - 1) / a.n_queues;
+  uint32_t* mine = a.queue + static_cast<size_t>(home) * kQueueStride + kFinishWord + a.slot;
+  uint32_t* all = a.queue + static_cast<size_t>(kQueues) * kQueueStride + kFinishWord + a.slot;
   uint32_t done = 0;
-  if (tid == 0)
-    done = __hip_atomic_fetch_add(finish_counters(a) + a.slot, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  done = __builtin_amdgcn_readfirstlane(done);
-  const bool last = a.advance && wave0 && done == gridDim.x - 1;
-  if (last && tid == 0)
-    __hip_atomic_store(&frame_state(a)->seq, seq + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (last && tid == 0 && (a.mode & kModeAccumulate))
-    __hip_atomic_store(&frame_state(a)->n_acc, a.n_acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (tid == 0) done = __hip_atomic_fetch_add(mine, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (tid == 0 && done == static_cast<uint32_t>(g - 1)) {
+    done = __hip_atomic_fetch_add(all, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (done == static_cast<uint32_t>(a.n_queues - 1)) {
+      __hip_atomic_store(&frame_state(a)->seq, seq + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (a.mode & kModeAccumulate)
+        __hip_atomic_store(&frame_state(a)->n_acc, a.n_acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
 }
 
 // KCAP 8, 16, 32: register-sort capacity (tiles with more layers are other
@@ -1265,22 +1285,32 @@ frame_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off,
   extern __shared__ __align__(16) char lds[];
   __shared__ int s_item;
   __shared__ float s_red[4];
-  __shared__ uint32_t s_state[2];
+  constexpr bool kLast = KCAP > 0;  // the frame's last launch: it counts its workgroups and advances the state
   const int tid = threadIdx.x;
   const int n_waves = static_cast<int>(blockDim.x >> 6);
   const bool wave0 = __builtin_amdgcn_readfirstlane(tid) < 64;  // uniform per wave
   FrameArgs a = args;
-  const uint32_t seq = read_frame_state(a, s_state);
-  if (a.advance && blockIdx.x == 0) recycle_slots(a, tid);
+  const uint32_t seq_read = read_frame_state(a);
   const int home = static_cast<int>(blockIdx.x) % a.n_queues;
-  Queue q = queue_of(a, home);
-  int drained = 0;  // counters this workgroup has found empty
   const int r = static_cast<int>(blockIdx.x) / a.n_queues;
+  Queue q = queue_of(a, home);
   int it = r < q.n ? unit_at(a, q, r) : a.n_work;  // the first unit is static
+  // its table entries are on their way while the state is read
+  int w = 0, off = 0, K = 0;
+  auto unit_tables = [&] {
+    w = work_list ? work_list[it] : it;
+    const int t = w / a.subs_per_tile;
+    off = tile_off[t];
+    K = tile_off[t + 1] - off;
+  };
+  if (it < a.n_work) unit_tables();
+  const uint32_t seq = use_frame_state(a, seq_read);
+  q.ctr += a.slot;
+  if (kLast && blockIdx.x == 0) recycle_slots(a);
+  uint64_t closed = 0;  // counters this workgroup has found empty
   while (it < a.n_work) {
     // the next unit's ticket is taken now and read after this unit's work
-    const uint32_t next = wave0 ? take_ticket(q) : 0u;
-    const int w = work_list ? work_list[it] : it;
+    const uint32_t next = wave0 && !a.one_each ? take_ticket(q) : 0u;
     Unit u;
     u.t = w / a.subs_per_tile;
     const int s = w - u.t * a.subs_per_tile;
@@ -1288,8 +1318,6 @@ frame_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off,
     u.sx0 = (s - (s / a.subs_x) * a.subs_x) * a.work_w;
     u.y0 = (u.t / a.tiles_x) * a.tile_h;
     u.x0 = (u.t - (u.t / a.tiles_x) * a.tiles_x) * a.tile_w;
-    const int off = tile_off[u.t];
-    const int K = tile_off[u.t + 1] - off;
     const int64_t* __restrict__ blk = layer_off + off;
     float* wl = reinterpret_cast<float*>(lds);
     float vs = 0.f;
@@ -1329,19 +1357,18 @@ frame_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off,
       if ((tid & 63) == 0) s_red[tid >> 6] = vs;
     }
     lds_barrier();  // s_red complete; every lane has read s_item
+    if (wave0 && acc) store_partial(a, w, s_red, n_waves);
+    if (a.one_each) break;
     if (wave0) {
-      if (acc) store_partial(a, w, s_red, n_waves);
       int v = ticket_to_unit(a, q, next);
-      while (v == a.n_work && ++drained < a.n_queues) {  // move on to the next counter
-        q = queue_of(a, (home + drained) % a.n_queues);
-        if (queue_open(q)) v = ticket_to_unit(a, q, take_ticket(q));
-      }
+      if (v == a.n_work) v = next_open_unit(a, q, closed);
       if (__lane_id() == 0) s_item = v;
     }
     lds_barrier();
     it = __builtin_amdgcn_readfirstlane(s_item);
+    if (it < a.n_work) unit_tables();
   }
-  finish_workgroup(a, seq, wave0);
+  if (kLast) finish_workgroup(a, seq, home);
 }
 
 // ------------------------------------------------- 32 < K <= 512: row sort
@@ -1599,21 +1626,20 @@ deep_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off, const int64_
               const int32_t* __restrict__ work_list) {
   extern __shared__ __align__(16) char lds[];
   __shared__ int s_item;
-  __shared__ uint32_t s_state[2];
   const int tid = threadIdx.x;
   const bool wave0 = __builtin_amdgcn_readfirstlane(tid) < 64;  // uniform per wave
   FrameArgs a = args;
-  const uint32_t seq = read_frame_state(a, s_state);
+  use_frame_state(a, read_frame_state(a));
   float* red = reinterpret_cast<float*>(lds);
   int64_t* lofs = reinterpret_cast<int64_t*>(lds + kDeepTail);
   float* rows = reinterpret_cast<float*>(lds + kDeepTail) + 2 * a.deep_layers;
   const int home = static_cast<int>(blockIdx.x) % a.n_queues;
   Queue q = queue_of(a, home);
-  int drained = 0;
+  uint64_t closed = 0;
   const int r = static_cast<int>(blockIdx.x) / a.n_queues;
   int it = r < q.n ? unit_at(a, q, r) : a.n_work;
   while (it < a.n_work) {
-    const uint32_t next = wave0 ? take_ticket(q) : 0u;
+    const uint32_t next = wave0 && !a.one_each ? take_ticket(q) : 0u;
     // position it of the launch's list: piece it % deep_subs of the tile at
     // sorted position it / deep_subs
     const int pos = it / a.deep_subs, piece = it - pos * a.deep_subs;
@@ -1647,19 +1673,16 @@ deep_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off, const int64_
       }
     }
     lds_barrier();  // every lane has read s_item; the LDS rows are free
+    if (a.one_each) break;
     if (wave0) {
       // the list is in descending order of layers: a tile of few ends the counter
       int v = K > kRegMax ? ticket_to_unit(a, q, next) : a.n_work;
-      while (v == a.n_work && ++drained < a.n_queues) {
-        q = queue_of(a, (home + drained) % a.n_queues);
-        if (queue_open(q)) v = ticket_to_unit(a, q, take_ticket(q));
-      }
+      if (v == a.n_work) v = next_open_unit(a, q, closed);
       if (__lane_id() == 0) s_item = v;
     }
     lds_barrier();
     it = __builtin_amdgcn_readfirstlane(s_item);
   }
-  finish_workgroup(a, seq, wave0);
 }
 
 // Per-tile variance of the mean from the units' partial M2 sums, added in

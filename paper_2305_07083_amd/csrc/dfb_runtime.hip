@@ -537,13 +537,15 @@ uint32_t display_mode(const dfb_config& c) {
   return m;
 }
 
-// Persistent grid: as many workgroups as fit on the chip at once, at most
-// one per work unit.
-dfb_status grid_of(dfb_ctx* h, const void* func, int threads, size_t lds, int n_work, int n_cu, int& grid) {
+// Persistent grid: as many workgroups as fit on the chip at once (grid_max),
+// at most one per work unit.
+dfb_status grid_of(dfb_ctx* h, const void* func, int threads, size_t lds, int n_work, int n_cu, int& grid,
+                   int& grid_max) {
   int per_cu = 0;
   DFB_HIP(h, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, func, threads, lds));
   if (per_cu < 1) return fail(h, DFB_ERR_UNSUPPORTED, "kernel does not fit on a compute unit with this shape");
-  grid = std::max(1, std::min(n_work, per_cu * n_cu));
+  grid_max = per_cu * n_cu;
+  grid = std::max(1, std::min(n_work, grid_max));
   return DFB_OK;
 }
 
@@ -603,6 +605,20 @@ struct FrameLaunch {
   }
 };
 
+// Work-queue counters of a launch whose grid is K.grid.  Where every counter's
+// units can have a workgroup of their own on the chip at once, the grid is
+// that large and the launch takes no tickets: small frames, whose time is the
+// latency of a unit, save its queue trips (@ONEEACH@).
+void set_queues(KernelLaunch& K, int grid_max) {
+  FrameArgs& a = K.fa;
+  a.n_queues = std::min(dfb::kQueues, K.grid);
+  int most = 0;
+  for (int s = 0; s < a.n_queues; ++s)
+    most = std::max(most, dfb::queue_units(a.n_work, a.queue_block, a.n_queues, s));
+  a.one_each = static_cast<int64_t>(most) * a.n_queues <= grid_max;
+  if (a.one_each) K.grid = std::max(1, most * a.n_queues);
+}
+
 // What a frame's launches depend on besides its geometry.  n_deep and n_big
 // are the tiles of more than kRegMax and of more than kDeepMax layers, known
 // where the host built the work list (each launch then takes its own range
@@ -629,7 +645,6 @@ dfb_status plan_kernels(dfb_ctx* h, const dfb_config& c, const FrameArgs& base, 
     K.fa.queue = dfb::ring_of(queue_base, ring);
     K.fa.rings = queue_base;
     K.fa.state = dfb::state_of(queue_base);
-    K.fa.advance = ring == 0;
     K.tab_off = tab_off;
     K.tab_layer = tab_layer;
     K.tab_work = tab_work;
@@ -656,11 +671,12 @@ dfb_status plan_kernels(dfb_ctx* h, const dfb_config& c, const FrameArgs& base, 
         K.tab_work = tab_work + static_cast<size_t>(fs.n_deep) * base.subs_per_tile;
       }
     }
-    dfb_status st = grid_of(h, K.func, K.threads, K.lds, K.fa.n_work, fs.n_cu, K.grid);
+    int grid_max = 0;
+    dfb_status st = grid_of(h, K.func, K.threads, K.lds, K.fa.n_work, fs.n_cu, K.grid, grid_max);
     if (st != DFB_OK) return st;
     if (K.lds > 64 * 1024)
       DFB_HIP(h, hipFuncSetAttribute(K.func, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(K.lds)));
-    K.fa.n_queues = std::min(dfb::kQueues, K.grid);
+    set_queues(K, grid_max);
   }
   return DFB_OK;
 }
@@ -1515,9 +1531,13 @@ dfb_status dfb_composite_noalloc(const dfb_config* cfg, const void* frag_dev, co
                       blend && max_layers > dfb::kRegMax && a.quad_ok, deep_units(a.P, n_tiles, n_cu)};
   if ((s = plan_kernels(nullptr, *cfg, a, queue, sh, fs, tile_off_dev, layer_off_dev, work, L)) != DFB_OK) return s;
   L.bind();
-  int32_t nt = n_tiles, subs = a.subs_per_tile;
-  void* lp[] = {&tile_off_dev, &nt, &subs, &work};
-  DFB_HIP(nullptr, hipLaunchKernel(dfb::lpt_work_kernel(), dim3(1), dim3(dfb::kLptThreads), lp, 0, st));
+  if (L.nk == 1 && L.k[0].fa.one_each) {
+    L.k[0].tab_work = nullptr;  // every unit has a workgroup of its own: their order does not matter
+  } else {
+    int32_t nt = n_tiles, subs = a.subs_per_tile;
+    void* lp[] = {&tile_off_dev, &nt, &subs, &work};
+    DFB_HIP(nullptr, hipLaunchKernel(dfb::lpt_work_kernel(), dim3(1), dim3(dfb::kLptThreads), lp, 0, st));
+  }
   for (int i = 0; i < L.nk; ++i)
     DFB_HIP(nullptr, hipLaunchKernel(L.k[i].func, dim3(L.k[i].grid), dim3(L.k[i].threads), L.k[i].params,
                                      L.k[i].lds, st));
