@@ -18,10 +18,6 @@ struct Map {          // bf16 NHWC map (or a channel slice of one)
   uint16_t* p;
   int ld, off, c;     // row stride (channels), first channel, channels
 };
-struct MapF {         // f32 NHWC map
-  float* p;
-  int ld, off, c;
-};
 struct Shape {
   int n, h, w;        // batch, height, width
   __host__ __device__ long long pixels() const { return static_cast<long long>(n) * h * w; }
@@ -36,14 +32,26 @@ struct Shape {
 hipError_t conv3x3_fwd(const Map& x, const uint16_t* w_fwd, const float* bias, const Map& y,
                        const Shape& s, hipStream_t st, bool up = false, const Map* pool = nullptr,
                        const Map* x2 = nullptr);
-// g = bf16(dy * (y > 0)), the ReLU-gated output gradient (g.c == dy.c, a
-// multiple of 8 dividing 2048; rows and offsets of y and g multiples of 8),
-// and partial[row][c], whose sum over the gate_rows rows is the bias gradient
-// sum_p dy*(y>0) in f32.
-hipError_t conv3x3_gate(const MapF& dy, const Map& y, const Map& g, float* partial, const Shape& s, hipStream_t st);
-int gate_rows(const Shape& s, int c);
-// dx = conv3x3^T(g) (overwrites dx).
-hipError_t conv3x3_dgrad(const Map& g, const uint16_t* w_dgrad, const MapF& dx, const Shape& s, hipStream_t st);
+// The data gradient of a conv3x3 (ci input channels, a multiple of 32; g its
+// gated output gradient at shape s), carried through to the gated output
+// gradient o.g of the layer that made its input: g' = bf16(dx' * (y > 0)), y
+// that layer's output.  dx' is dx itself; with kUp (the input was 2x
+// up-sampled) the 2x2 sums of dx, at s / 2; with kPool (it was 2x2 pooled)
+// o.skip + dx / 4 at 2 s.  With kSame, channels from 32 o.split on are the
+// skip of a concatenation: their dx goes to o.skip, ungated.  partial[row][c],
+// c < o.g.c, over the conv_tiles(s, ci) rows, sums to the layer's bias gradient
+// in f32.
+enum class Adjoint { kSame, kUp, kPool };
+struct TileOut {
+  Map y;               // forward: the output; gradient: the activation that gates
+  Map g, pool;
+  float* skip;         // [pixel][skip_ld]
+  int skip_ld, split;
+  float* partial;
+};
+int conv_tiles(const Shape& s, int co);
+hipError_t conv3x3_bwd(const Map& g, const uint16_t* w_dgrad, int ci, Adjoint adj, const TileOut& o, const Shape& s,
+                       hipStream_t st);
 
 // Weight gradients of the 12 conv3x3 layers, one launch: partial sums of
 // dw[9][ci][co] = sum_p x[p + tap] * g[p] over `chunks` runs of pixel tiles.
@@ -93,9 +101,6 @@ struct AdamArgs {
 int update_blocks(const UpdateLayer& L);
 hipError_t update_params(const UpdatePlan& plan, const float* partial, const AdamArgs& a, hipStream_t st);
 
-hipError_t avgpool2_backward_add(const MapF& dy, const MapF& dx, const Shape& s_in, hipStream_t st);
-hipError_t upsample2_backward(const MapF& dy, const MapF& dx, const Shape& s_in, hipStream_t st);
-
 // The first conv3x3 (8 input channels -> 32, ReLU, bf16) with the nine
 // taps packed into a 72-deep contraction, reading the packed bf16 input x
 // (x.c == 8).
@@ -104,10 +109,12 @@ hipError_t conv3x3_in_fwd(const Map& x, const uint16_t* w_fwd, const float* bias
 // out[p][c] = base[p][c] + b[c] + sum_i x[p][i] w[i][c]   (c < 3, f32)
 hipError_t out_conv_fwd(const Map& x, const float* w, const float* b, const float* base,
                         int base_ld, float* out, const Shape& s, hipStream_t st);
-// dout = 2 (out - target) / count; dx = dout w^T; partial[row] = {dw[c][3],
-// db[3], sum (out - target)^2} over out_rows rows.
-hipError_t out_conv_backward(const Map& x, const float* out, const float* target, const float* w,
-                             const MapF& dx, float* partial, const Shape& s, hipStream_t st);
+// out as out_conv_fwd's, dout = 2 (out - target) / count, g = bf16(dout w^T *
+// (x > 0)), the gated output gradient of the conv that made x (32 channels);
+// over out_rows rows, bias[row][32] sums to that conv's bias gradient and
+// partial[row] to {dw[c][3], db[3], sum (out - target)^2}.
+hipError_t out_conv_backward(const Map& x, const float* base, int base_ld, const float* target, const float* w,
+                             const float* b, const Map& g, float* bias, float* partial, const Shape& s, hipStream_t st);
 int out_rows(const Shape& s);
 
 // bf16 input [p][8] from f32 [p][in_ld] (first 6 channels), channels 6,7 zero.

@@ -7,15 +7,11 @@
 // The three convolutions are one GEMM shape, D[M][N] += A[M][K] B[K][N],
 // read from LDS in K slices:
 //   forward  M = c_out,  N = pixels, K = (tap, c_in)   A = W, B = x[p + tap]
-//   dgrad    M = pixels, N = c_in,  K = (tap, c_out)  A = dy[p - tap], B = W^T
+//   dgrad    M = c_in,   N = pixels, K = (tap, c_out)  A = W^T, B = dy[p - tap]
 //   wgrad    M = c_in,   N = c_out, K = pixels (per tap, split over chunks)
 // All three use v_mfma_f32_32x32x16_bf16.  Operand layout (checked on the
 // device): lane l holds k = (l/32)*8 .. +7 of row/column l%32; the result
-// element r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l%32.  In
-// dgrad a workgroup is 4 waves over a 64-row tile and every 32-column block
-// of N: wave w takes 32x32 blocks w, w + 4, ...; with only two blocks
-// (N = 32) two waves share a block, each taking half of the K steps, and their
-// sums are added in a fixed order.
+// element r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l%32.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -31,40 +27,12 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int BM = 64;    // rows per workgroup tile
-constexpr int LDK = 40;   // LDS row length in bf16 (32 + 8 padding)
-
 __device__ __forceinline__ uint16_t to_bf16(float f) {  // round to nearest even
   uint32_t u = __float_as_uint(f);
   u += 0x7FFFu + ((u >> 16) & 1u);
   return static_cast<uint16_t>(u >> 16);
 }
 __device__ __forceinline__ float from_bf16(uint16_t h) { return __uint_as_float(static_cast<uint32_t>(h) << 16); }
-
-__device__ __forceinline__ bf16x8 lds_frag(const uint16_t* p) {
-  const uint4 v = *reinterpret_cast<const uint4*>(p);
-  return __builtin_bit_cast(bf16x8, v);
-}
-
-struct Pix {
-  int n, r, c;
-  bool ok;
-};
-__device__ __forceinline__ Pix pixel_of(long long p, const Shape& s) {
-  Pix q;
-  q.ok = p < s.pixels();
-  const long long hw = static_cast<long long>(s.h) * s.w;
-  q.n = q.ok ? static_cast<int>(p / hw) : 0;
-  const int rem = q.ok ? static_cast<int>(p - q.n * hw) : 0;
-  q.r = rem / s.w;
-  q.c = rem - q.r * s.w;
-  return q;
-}
-__device__ __forceinline__ long long shifted(const Pix& q, int dr, int dc, const Shape& s, bool& in) {
-  const int rr = q.r + dr, cc = q.c + dc;
-  in = q.ok && rr >= 0 && rr < s.h && cc >= 0 && cc < s.w;
-  return (static_cast<long long>(q.n) * s.h + rr) * s.w + cc;
-}
 
 // ------------------------------------------------------------- forward
 // Persistent implicit-GEMM conv3x3 forward.  A workgroup computes a
@@ -727,160 +695,340 @@ __global__ void __launch_bounds__(256) conv_in_k(Map x, FrameGlue fg,
   }
 }
 
-// ------------------------------------------------------------- dgrad
-// A[p][(tap, co)] = g[p - tap][co], g = bf16(dy * (y > 0)) (gate_k); B =
-// W[tap][ci][co].  K runs over (tap, 32-wide c_out slice) in stages of
-// kDgradKS slices (one barrier pair per stage; slots past the last slice
-// stage zeros); the next stage's A chunks and weights are loaded into
-// registers while this stage's MFMAs run.  The MFMA is
-// v_mfma_f32_32x32x16_bf16 on 32-pixel x 32-c_in blocks, split over the
-// waves as in the weight gradient below (the K steps of a slice are split
-// between two waves per block when there are only two blocks).
-constexpr int kDgradKS = 4;
-constexpr int LDD = 32 * kDgradKS + 8;  // LDS row: the stage's K + 8 padding
+// ------------------------------------------------------- one-tile convolution
+// conv3x3 with one TH x 32-pixel tile and 32 output channels per workgroup:
+// the data gradients (dx[p] = sum over taps of W[tap]^T g[p - tap]), and the
+// forward layers of maps with too few tiles for the persistent kernel to fill
+// the chip.  4 waves, each MB tile rows (TH = 4 MB), in the persistent
+// kernel's LDS layout.
+//
+// Forward: per 32-channel input slice the halo and the nine taps' weights are
+// staged and the next slice is loaded into registers during the MFMAs, which
+// take their operands in the persistent kernel's order (the same bits).
+// Gradient: the halo of every slice is staged once and the weights follow in
+// stages of TS taps, so that a sum runs over (tap, channel) in that order; with
+// 32 output channels the two 16-channel halves of the slices are summed apart
+// and added (two chains of MFMAs instead of one).
+//
+// The epilogue goes through an f32 staging tile, so that everything it reads
+// and writes is 16 bytes of 8 channels with consecutive lanes on consecutive
+// addresses, and does what were passes of their own over f32 maps: the ReLU
+// gate of the layer below (g = bf16(dx * (y > 0))) with its bias gradient's
+// partial sums, the adjoints of the 2x up-sampling and of the 2x2 pool (added
+// to the skip's gradient).  Bound by latency: a workgroup's loads, MFMAs and
+// epilogue are a few microseconds, so what counts is that a layer has
+// workgroups for every compute unit and is one launch (8 x 128^2
+// step: 27 launches of gates, gradients and adjoints 304 us, these 11 122).
+enum TileEpi {
+  kTileFwd = 0,   // y = bf16(relu(acc)), acc starting from the bias
+  kTileFwdPool,   // ... and its 2x2 average
+  kTileGate,      // g = bf16(acc * (y > 0)), channel groups from o.split on: skip = acc (f32)
+  kTileUpGate,    // the same of the 2x2 sums (y, g at half the resolution)
+  kTilePoolGate,  // g = bf16((skip + acc / 4) * (y > 0)) at twice the resolution
+};
 
-template <int BN>
-__global__ void __launch_bounds__(256) conv_dgrad_k(Map g, const uint16_t* __restrict__ w, MapF dx, Shape s) {
-  __shared__ __align__(16) uint16_t As[BM * LDD];
-  __shared__ __align__(16) uint16_t Bs[BN * LDD];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, lh = lane >> 5;
-  const long long m0 = static_cast<long long>(blockIdx.x) * BM;
-  const int ap = tid >> 2, ach = (tid & 3) * 8;
-  const Pix q = pixel_of(m0 + ap, s);
-  const int co_n = g.c;
-  constexpr int NBLK = 2 * (BN / 32);                      // 32 x 32 output blocks
-  constexpr int KSPLIT = NBLK >= 4 ? 1 : 4 / NBLK;         // waves per block
-  constexpr int BPW = NBLK >= 4 ? NBLK / 4 : 1;            // blocks per wave
-  const int kpart = wave / (4 / KSPLIT);                   // which 16-wide K step of a slice
-  f32x16 acc[BPW];
+template <int NCH, int MB, bool UP, bool FWD>
+struct TileCfg {
+  static constexpr int TH = 4 * MB, SHH = UP ? TH / 2 + 2 : TH + 2, SHW = UP ? kTW / 2 + 2 : kTW + 2, HP = 5;
+  static constexpr int HALO_CH = SHH * SHW * HP;                    // 16-byte chunks of a slice's halo
+  static constexpr int TS = FWD || NCH == 1 ? 9 : NCH == 2 ? 3 : 1;  // taps of a weight stage
+  static constexpr int WSL = FWD ? 1 : NCH;                         // input slices of a weight stage
+  static constexpr int W_CH = TS * WSL * 32 * 4;
+  static constexpr int WBUF = TS == 9 ? 1 : 2;
+  static constexpr int PITCH = 36;  // staged floats of a pixel
+  static constexpr int LOAD = (WSL * HALO_CH + WBUF * W_CH) * 16, STG = (TH * kTW * PITCH + 4 * 32) * 4;
+  static constexpr int BYTES = LOAD > STG ? LOAD : STG;
+};
+
+template <int NCH, int MB, bool UP, int EPI, bool SPLIT>
+__global__ void __launch_bounds__(256) conv_tile_k(Map x, Map x2, const uint16_t* __restrict__ w, int co_n,
+                                                   const float* __restrict__ bias, TileOut o, Shape s) {
+  constexpr bool FWD = EPI == kTileFwd || EPI == kTileFwdPool;
+  using C = TileCfg<NCH, MB, UP, FWD>;
+  static_assert(!(FWD && SPLIT) && !(UP && !FWD), "forward sums are one chain; gradients read no up-sampled map");
+  constexpr int TH = C::TH, NT = 256, SHH = C::SHH, SHW = C::SHW, HP = C::HP, PITCH = C::PITCH;
+  constexpr int HALO_EL = C::WSL * SHH * SHW * 4, W_CH = C::W_CH, CPP = C::WSL * 4;  // CPP: chunks loaded per pixel
+  constexpr int HIT = (HALO_EL + NT - 1) / NT, WIT = (W_CH + NT - 1) / NT, CIN = NCH * 32;
+  extern __shared__ __align__(16) uint4 lds4[];
+  uint4* halo = lds4;                          // [WSL][SHH * SHW][HP]
+  uint4* wts = lds4 + C::WSL * C::HALO_CH;     // [WBUF][TS][WSL][32][4]
+  float* stg = reinterpret_cast<float*>(lds4);
+  float* red = stg + TH * kTW * PITCH;         // [4][32]
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // the channel groups of a tile, and the tiles of a band, on one XCD
+  const int N = static_cast<int>(gridDim.x), xcd = static_cast<int>(blockIdx.x) % kXcds;
+  const int id = xcd * (N / kXcds) + (xcd < N % kXcds ? xcd : N % kXcds) + static_cast<int>(blockIdx.x) / kXcds;
+  const int groups = co_n / 32, tile = id / groups, grp = id - tile * groups, o0 = grp * 32;
+  const int tiles_x = (s.w + kTW - 1) / kTW, tiles_y = (s.h + TH - 1) / TH;
+  const int n = tile / (tiles_x * tiles_y), rem = tile - n * tiles_x * tiles_y;
+  const int oy0 = (rem / tiles_x) * TH, ox0 = (rem % tiles_x) * kTW;
+  const int hi = UP ? s.h / 2 : s.h, wi = UP ? s.w / 2 : s.w;  // the map x is read from
+  const int sy0 = UP ? oy0 / 2 - 1 : oy0 - 1, sx0 = UP ? ox0 / 2 - 1 : ox0 - 1;
+
+  int hoff[HIT];  // byte offset of this thread's halo chunks from the halo's top-left pixel
 #pragma unroll
-  for (int b = 0; b < BPW; ++b)
+  for (int k = 0; k < HIT; ++k) {
+    const int e = tid + NT * k, hp = e / CPP, cc = e % CPP, hr = hp / SHW, hc = hp - hr * SHW;
+    const int ok = (e < HALO_EL) & (static_cast<unsigned>(sy0 + hr) < static_cast<unsigned>(hi)) &
+                   (static_cast<unsigned>(sx0 + hc) < static_cast<unsigned>(wi));
+    hoff[k] = ok ? ((hr * wi + hc) * x.ld + cc * 8) * 2 : kOOB;
+  }
+  const __amdgpu_buffer_rsrc_t wsrc = buf_rsrc(w);
+  uint4 hreg[HIT], wreg[WIT];
+  auto load_halo = [&](int ck) {
+    const bool second = ck * kKC >= x.c;
+    const Map& xm = second ? x2 : x;
+    const int cb = second ? ck * kKC - x.c : ck * kKC;
+    const __amdgpu_buffer_rsrc_t src =
+        buf_rsrc(xm.p + xm.off + cb + (static_cast<long long>(n) * hi * wi + static_cast<long long>(sy0) * wi + sx0) * xm.ld);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
-  const int nk = (co_n + 31) / 32, n_it = 9 * nk;
-  constexpr int WPT = (BN * 4 + 255) / 256;  // 16-byte weight chunks per thread and slice
-  uint4 av[kDgradKS], wv[kDgradKS][WPT];
-  auto load = [&](int it0) {
+    for (int k = 0; k < HIT; ++k) hreg[k] = buf_load16(src, hoff[k]);
+  };
+  auto load_w = [&](int tap0, int ck) {  // LDS row (tap, slice, channel)
 #pragma unroll
-    for (int sl = 0; sl < kDgradKS; ++sl) {
-      const int it = it0 + sl;
-      const int tap = it / nk, kc = it - (it / nk) * nk;
-      av[sl] = uint4{0u, 0u, 0u, 0u};
-#pragma unroll
-      for (int i = 0; i < WPT; ++i) wv[sl][i] = uint4{0u, 0u, 0u, 0u};
-      if (it < n_it) {
-        bool in;
-        const long long src = shifted(q, 1 - tap / 3, 1 - tap % 3, s, in);
-        const int c0 = kc * 32 + ach;
-        if (in && c0 < co_n) av[sl] = *reinterpret_cast<const uint4*>(g.p + src * g.ld + g.off + c0);
-#pragma unroll
-        for (int i = 0; i < WPT; ++i) {
-          const int e = tid + i * 256;
-          const int ci = e >> 2, k0 = kc * 32 + (e & 3) * 8;
-          if (e < BN * 4 && k0 < co_n)
-            wv[sl][i] = *reinterpret_cast<const uint4*>(w + (static_cast<size_t>(tap) * BN + ci) * co_n + k0);
-        }
-      }
+    for (int k = 0; k < WIT; ++k) {
+      const int e = tid + NT * k, row = e >> 2, co = row & 31, sl = (row >> 5) % C::WSL, tap = tap0 + (row >> 5) / C::WSL;
+      wreg[k] = buf_load16(wsrc, e < W_CH ? ((tap * co_n + o0 + co) * CIN + (ck + sl) * kKC + (e & 3) * 8) * 2 : kOOB);
     }
   };
-  load(0);
-  for (int it0 = 0; it0 < n_it; it0 += kDgradKS) {
+  auto store_halo = [&] {
 #pragma unroll
-    for (int sl = 0; sl < kDgradKS; ++sl) {
-      *reinterpret_cast<uint4*>(As + ap * LDD + sl * 32 + ach) = av[sl];
-#pragma unroll
-      for (int i = 0; i < WPT; ++i) {
-        const int e = tid + i * 256;
-        if (e < BN * 4) *reinterpret_cast<uint4*>(Bs + (e >> 2) * LDD + sl * 32 + (e & 3) * 8) = wv[sl][i];
-      }
+    for (int k = 0; k < HIT; ++k) {
+      const int e = tid + NT * k, cc = e % CPP;
+      if (e < HALO_EL) halo[(cc >> 2) * C::HALO_CH + (e / CPP) * HP + (cc & 3)] = hreg[k];
     }
-    __syncthreads();
-    if (it0 + kDgradKS < n_it) load(it0 + kDgradKS);
+  };
+  auto store_w = [&](int buf) {
 #pragma unroll
-    for (int sl = 0; sl < kDgradKS; ++sl) {
-      if (it0 + sl < n_it) {  // uniform
+    for (int k = 0; k < WIT; ++k) {
+      const int e = tid + NT * k;
+      if (e < W_CH) wts[buf * W_CH + swz(e >> 2, e & 3)] = wreg[k];
+    }
+  };
+  load_halo(0);
+  load_w(0, 0);
+  f32x16 acc[MB][SPLIT ? 2 : 1];
 #pragma unroll
-        for (int kk = 0; kk < 2 / KSPLIT; ++kk) {
-          const int k = sl * 32 + (KSPLIT > 1 ? kpart : kk) * 16 + lh * 8;
+  for (int q = 0; q < 4; ++q) {
+    f32x4 b4 = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (FWD) {  // the parameter vector's biases are 4-byte aligned
 #pragma unroll
-          for (int b = 0; b < BPW; ++b) {
-            const int blk = KSPLIT > 1 ? wave % NBLK : wave + 4 * b, mb = blk & 1, nb = blk >> 1;
-            const bf16x8 a = lds_frag(As + (mb * 32 + l32) * LDD + k);
-            const bf16x8 bv = lds_frag(Bs + (nb * 32 + l32) * LDD + k);
-            acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bv, acc[b], 0, 0, 0);
+      for (int r = 0; r < 4; ++r) b4[r] = bias[o0 + 8 * q + 4 * lh + r];
+    }
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+      for (int h = 0; h < (SPLIT ? 2 : 1); ++h)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[m][h][4 * q + r] = b4[r];
+  }
+  // fragment addresses as in the persistent kernel; halo row and column of
+  // this lane's pixel in tile row m of the wave, moved by (dr, dc)
+  const int boff[2] = {l32 * 4 + ((0 + lh) ^ ((l32 >> 2) & 3)), l32 * 4 + ((2 + lh) ^ ((l32 >> 2) & 3))};
+  auto pixel = [&](int m, int dr, int dc) {
+    const int row = wave * MB + m + dr;
+    return UP ? ((row + 1) >> 1) * SHW + ((l32 + dc + 1) >> 1) : row * SHW + l32 + dc;
+  };
+  if constexpr (FWD) {
+#pragma unroll
+    for (int ck = 0; ck < NCH; ++ck) {
+      if (ck) __syncthreads();  // the previous slice's fragment reads are done
+      store_halo();
+      store_w(0);
+      __syncthreads();
+      if (ck + 1 < NCH) {
+        load_halo(ck + 1);
+        load_w(0, ck + 1);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int tap = 0; tap < 9; ++tap)
+#pragma unroll
+        for (int kh = 0; kh < 2; ++kh) {
+          const bf16x8 wf = __builtin_bit_cast(bf16x8, wts[tap * 32 * 4 + boff[kh]]);
+#pragma unroll
+          for (int m = 0; m < MB; ++m) {
+            const bf16x8 hf = __builtin_bit_cast(bf16x8, halo[pixel(m, tap / 3, tap % 3) * HP + 2 * kh + lh]);
+            acc[m][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, hf, acc[m][0], 0, 0, 0);
           }
         }
+    }
+  } else {
+    store_halo();
+#pragma unroll
+    for (int st = 0; st < 9 / C::TS; ++st) {
+      // into the buffer that stage st - 2 read: every wave is past it
+      store_w(st % C::WBUF);
+      __syncthreads();
+      if (st + 1 < 9 / C::TS) load_w((st + 1) * C::TS, 0);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int t = 0; t < C::TS; ++t) {
+        const int tap = st * C::TS + t, dr = 2 - tap / 3, dc = 2 - tap % 3;
+#pragma unroll
+        for (int sl = 0; sl < NCH; ++sl)
+#pragma unroll
+          for (int kh = 0; kh < 2; ++kh) {
+            const bf16x8 wf =
+                __builtin_bit_cast(bf16x8, wts[(st % C::WBUF) * W_CH + (t * NCH + sl) * 32 * 4 + boff[kh]]);
+#pragma unroll
+            for (int m = 0; m < MB; ++m) {
+              const bf16x8 hf =
+                  __builtin_bit_cast(bf16x8, halo[sl * C::HALO_CH + pixel(m, dr, dc) * HP + 2 * kh + lh]);
+              f32x16& a = acc[m][SPLIT ? kh : 0];
+              a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, hf, a, 0, 0, 0);
+            }
+          }
       }
     }
-    __syncthreads();
-  }
-  if constexpr (KSPLIT > 1) {  // part 0 + part 1 (the stage loop ended on a barrier: As is free)
-    static_assert(KSPLIT == 2 && NBLK * 64 * 16 * 4 <= BM * LDD * 2, "reduction fits As");
-    float* red = reinterpret_cast<float*>(As);
-    const int blk = wave % NBLK;
-    if (kpart == 1) {
+    if constexpr (SPLIT) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) red[(blk * 16 + r) * 64 + lane] = acc[0][r];
-    }
-    __syncthreads();
-    if (kpart == 0) {
+      for (int m = 0; m < MB; ++m)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[0][r] += red[(blk * 16 + r) * 64 + lane];
+        for (int r = 0; r < 16; ++r) acc[m][0][r] += acc[m][1][r];
     }
   }
-  const long long P = s.pixels();
-  if (kpart == 0) {
+  __syncthreads();
 #pragma unroll
-    for (int b = 0; b < BPW; ++b) {
-      const int blk = KSPLIT > 1 ? wave % NBLK : wave + 4 * b, mb = blk & 1, nb = blk >> 1;
-      const int col = nb * 32 + l32;
+  for (int m = 0; m < MB; ++m)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const long long p = m0 + mb * 32 + 8 * (r / 4) + 4 * lh + (r % 4);
-        if (p < P) dx.p[p * dx.ld + dx.off + col] = acc[b][r];
-      }
+    for (int q = 0; q < 4; ++q) {
+      const f32x16& v = acc[m][0];
+      *reinterpret_cast<f32x4*>(stg + ((wave * MB + m) * kTW + l32) * PITCH + 8 * q + 4 * lh) =
+          f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
     }
-  }
-}
+  __syncthreads();
 
-// ------------------------------------------------------------- gate
-// g[p][c] = bf16(dy[p][c] * (y[p][c] > 0)), the ReLU-gated output gradient
-// that the data and weight gradients read (8 channels per thread); and the
-// bias-gradient partial of the workgroup's pixels, partial[block][c] = the
-// sum over its pixels, in pixel order, of dy * (y > 0) in f32.
-__global__ void __launch_bounds__(256) gate_k(MapF dy, Map y, Map g, float* __restrict__ partial, Shape s) {
-  __shared__ float red[256 * 9];  // [thread][8], one pad slot
-  const int t = threadIdx.x, cb = dy.c / 8;
-  const long long e = static_cast<long long>(blockIdx.x) * blockDim.x + t;
-  float gf[8];
+  // items of 8 channels: chunk c8 of pixel px
+  const int c8 = (tid & 3) * 8;
+  auto staged = [&](int row, int col, float* v) {
+    const f32x4* q = reinterpret_cast<const f32x4*>(stg + (row * kTW + col) * PITCH + c8);
+    const f32x4 a = q[0], b = q[1];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) gf[i] = 0.f;
-  if (e < s.pixels() * cb) {
-    const long long p = e / cb;
-    const int c0 = static_cast<int>(e - p * cb) * 8;
-    const float4 g0 = *reinterpret_cast<const float4*>(dy.p + p * dy.ld + dy.off + c0);
-    const float4 g1 = *reinterpret_cast<const float4*>(dy.p + p * dy.ld + dy.off + c0 + 4);
-    const uint4 mk = *reinterpret_cast<const uint4*>(y.p + p * y.ld + y.off + c0);
-    const float gv[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
-    const uint32_t mw[4] = {mk.x, mk.y, mk.z, mk.w};
-    uint32_t h[8];
+    for (int i = 0; i < 4; ++i) {
+      v[i] = a[i];
+      v[4 + i] = b[i];
+    }
+  };
+  auto pack8 = [&](const float* v) {
+    return uint4{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7])};
+  };
+  if constexpr (FWD) {
+    uint16_t* yb = o.y.p + o.y.off + o0 + (static_cast<long long>(n) * s.h * s.w) * o.y.ld;
+#pragma unroll
+    for (int k = 0; k < TH * kTW / 64; ++k) {
+      const int px = (tid >> 2) + 64 * k, r = oy0 + px / kTW, c = ox0 + px % kTW;
+      float v[8];
+      staged(px / kTW, px % kTW, v);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = fmaxf(v[i], 0.f);
+      if (r < s.h && c < s.w) *reinterpret_cast<uint4*>(yb + (static_cast<long long>(r) * s.w + c) * o.y.ld + c8) = pack8(v);
+    }
+    if constexpr (EPI == kTileFwdPool) {
+      const int ph = s.h / 2, pw = s.w / 2, q = tid >> 2;  // pooled pixel of the tile: ((a + b) + c) + d of the bf16 values
+      uint16_t* pb = o.pool.p + o.pool.off + o0 + (static_cast<long long>(n) * ph * pw) * o.pool.ld;
+      const int qr = q / (kTW / 2), qc = q % (kTW / 2), r = oy0 / 2 + qr, c = ox0 / 2 + qc;
+      if (qr < TH / 2 && r < ph && c < pw) {
+        float v[8], sum[8];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          staged(2 * qr + (k >> 1), 2 * qc + (k & 1), v);
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const float b = from_bf16(to_bf16(fmaxf(v[i], 0.f)));
+            sum[i] = k ? sum[i] + b : b;
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) sum[i] *= 0.25f;
+        *reinterpret_cast<uint4*>(pb + (static_cast<long long>(r) * pw + c) * o.pool.ld + c8) = pack8(sum);
+      }
+    }
+    return;
+  }
+  if (EPI == kTileGate && grp >= o.split) {  // the skip half of a concatenation
+    float* sb = o.skip + (static_cast<long long>(n) * s.h * s.w) * o.skip_ld + (grp - o.split) * 32 + c8;
+#pragma unroll
+    for (int k = 0; k < TH * kTW / 64; ++k) {
+      const int px = (tid >> 2) + 64 * k, r = oy0 + px / kTW, c = ox0 + px % kTW;
+      float v[8];
+      staged(px / kTW, px % kTW, v);
+      if (r < s.h && c < s.w) {
+        f32x4* d = reinterpret_cast<f32x4*>(sb + (static_cast<long long>(r) * s.w + c) * o.skip_ld);
+        d[0] = f32x4{v[0], v[1], v[2], v[3]};
+        d[1] = f32x4{v[4], v[5], v[6], v[7]};
+      }
+    }
+    return;
+  }
+  // the gated gradient of the layer below, at resolution gh x gw
+  constexpr int ITEMS = EPI == kTileUpGate ? TH * kTW / 4 : EPI == kTilePoolGate ? TH * kTW * 4 : TH * kTW;  // pixels
+  constexpr int GW = EPI == kTileUpGate ? kTW / 2 : EPI == kTilePoolGate ? kTW * 2 : kTW;                    // tile width
+  const int gh = EPI == kTileUpGate ? s.h / 2 : EPI == kTilePoolGate ? s.h * 2 : s.h;
+  const int gw = EPI == kTileUpGate ? s.w / 2 : EPI == kTilePoolGate ? s.w * 2 : s.w;
+  const int gy0 = EPI == kTileUpGate ? oy0 / 2 : EPI == kTilePoolGate ? oy0 * 2 : oy0;
+  const int gx0 = EPI == kTileUpGate ? ox0 / 2 : EPI == kTilePoolGate ? ox0 * 2 : ox0;
+  const long long img = static_cast<long long>(n) * gh * gw;
+  const uint16_t* yb = o.y.p + o.y.off + o0 + c8 + img * o.y.ld;
+  uint16_t* gb = o.g.p + o.g.off + o0 + c8 + img * o.g.ld;
+  const float* sb = o.skip + (EPI == kTilePoolGate ? img * o.skip_ld + o0 + c8 : 0);
+  float sum[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) sum[i] = 0.f;
+#pragma unroll 4
+  for (int k = 0; k < (ITEMS + 63) / 64; ++k) {
+    const int px = (tid >> 2) + 64 * k, pr = px / GW, pc = px % GW, r = gy0 + pr, c = gx0 + pc;
+    if (px >= ITEMS || r >= gh || c >= gw) continue;
+    const long long p = static_cast<long long>(r) * gw + c;
+    const uint4 y4 = *reinterpret_cast<const uint4*>(yb + p * o.y.ld);
+    float v[8];
+    if constexpr (EPI == kTileUpGate) {
+      staged(2 * pr, 2 * pc, v);
+#pragma unroll
+      for (int q = 1; q < 4; ++q) {
+        float t[8];
+        staged(2 * pr + (q >> 1), 2 * pc + (q & 1), t);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] += t[i];
+      }
+    } else if constexpr (EPI == kTilePoolGate) {
+      const f32x4* sk = reinterpret_cast<const f32x4*>(sb + p * o.skip_ld);
+      const f32x4 a = sk[0], b = sk[1];
+      float t[8];
+      staged(pr >> 1, pc >> 1, t);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        v[i] = a[i] + 0.25f * t[i];
+        v[4 + i] = b[i] + 0.25f * t[4 + i];
+      }
+    } else {
+      staged(pr, pc, v);
+    }
+    const uint32_t yw[4] = {y4.x, y4.y, y4.z, y4.w};
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const uint16_t yh = static_cast<uint16_t>(mw[i >> 1] >> ((i & 1) * 16));
-      gf[i] = from_bf16(yh) > 0.f ? gv[i] : 0.f;
-      h[i] = to_bf16(gf[i]);
+      const float yi = (i & 1) ? bf16_hi(yw[i >> 1]) : bf16_lo(yw[i >> 1]);
+      v[i] = yi > 0.f ? v[i] : 0.f;
+      sum[i] += v[i];
     }
-    *reinterpret_cast<uint4*>(g.p + p * g.ld + g.off + c0) =
-        uint4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
+    *reinterpret_cast<uint4*>(gb + p * o.g.ld) = pack8(v);
   }
+  // the tile's bias-gradient partial: over the 16 lanes of a chunk, then the waves
 #pragma unroll
-  for (int i = 0; i < 8; ++i) red[t * 9 + i] = gf[i];
-  __syncthreads();
-  if (t < dy.c) {  // channel t: thread (pixel k, chunk t/8) of the block holds it at slot t%8
-    float sum = 0.f;
-    for (int k = 0; k < 256 / cb; ++k) sum += red[(k * cb + t / 8) * 9 + (t & 7)];
-    partial[static_cast<size_t>(blockIdx.x) * dy.c + t] = sum;
+  for (int i = 0; i < 8; ++i) {
+    sum[i] += __shfl_xor(sum[i], 4, 64);
+    sum[i] += __shfl_xor(sum[i], 8, 64);
+    sum[i] += __shfl_xor(sum[i], 16, 64);
+    sum[i] += __shfl_xor(sum[i], 32, 64);
   }
+  if (lane < 4) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) red[wave * 32 + c8 + i] = sum[i];
+  }
+  __syncthreads();
+  if (tid < 32)
+    o.partial[static_cast<size_t>(tile) * o.g.c + o0 + tid] = ((red[tid] + red[32 + tid]) + red[64 + tid]) + red[96 + tid];
 }
 
 // ------------------------------------------------------------- wgrad
@@ -1127,33 +1275,6 @@ __global__ void __launch_bounds__(256) update_k(UpdatePlan plan, const float* __
 }
 
 // ------------------------------------------------------------- glue kernels
-__global__ void avgpool2_bwd_add_k(MapF dy, MapF dx, Shape si) {
-  const long long e = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
-  const long long total = si.pixels() * dx.c;
-  if (e >= total) return;
-  const int ch = static_cast<int>(e % dx.c);
-  const long long p = e / dx.c;
-  const Pix q = pixel_of(p, si);
-  const long long po = (static_cast<long long>(q.n) * (si.h / 2) + q.r / 2) * (si.w / 2) + q.c / 2;
-  dx.p[p * dx.ld + dx.off + ch] += 0.25f * dy.p[po * dy.ld + dy.off + ch];
-}
-
-__global__ void upsample2_bwd_k(MapF dy, MapF dx, Shape si) {
-  const long long e = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
-  const long long total = si.pixels() * dx.c;
-  if (e >= total) return;
-  const int ch = static_cast<int>(e % dx.c);
-  const long long p = e / dx.c;
-  const Pix q = pixel_of(p, si);
-  const int wo = si.w * 2;
-  const long long b = (static_cast<long long>(q.n) * si.h * 2 + 2 * q.r) * wo + 2 * q.c;
-  float v = dy.p[b * dy.ld + dy.off + ch];
-  v += dy.p[(b + 1) * dy.ld + dy.off + ch];
-  v += dy.p[(b + wo) * dy.ld + dy.off + ch];
-  v += dy.p[(b + wo + 1) * dy.ld + dy.off + ch];
-  dx.p[p * dx.ld + dx.off + ch] = v;
-}
-
 __global__ void out_fwd_k(Map x, const float* __restrict__ w, const float* __restrict__ b,
                           const float* __restrict__ base, int base_ld, float* __restrict__ out, Shape s) {
   const long long p = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -1178,58 +1299,91 @@ __global__ void out_fwd_k(Map x, const float* __restrict__ w, const float* __res
   out[p * 3 + 2] = o2 + a2;
 }
 
-// Per pixel: dout = 2 (out - t) / count; dx = dout w^T.  Per chunk of
-// kOutChunk pixels: partial[chunk] = {dw[ci][3], db[3], sum (out - t)^2}.
-// Thread (g, i) of G = 256 / ci groups handles channel i of the chunk's
-// pixels g, g + G, ... in order; the groups are added in group order.
+// The output conv, the loss and their gradients in one pass over the last
+// layer's output x (bf16, 32 channels): out = base + b + x w, dout = 2 (out -
+// t) / count, dx = dout w^T, g = bf16(dx * (x > 0)), the gated gradient of the
+// last conv layer.  Per chunk of kOutChunk pixels: bias[chunk][32] = sum g in
+// f32, and partial[chunk] = {dw[ci][3], db[3], sum (out - t)^2}.  Four lanes
+// share a pixel, 8 channels each; a lane's sums over its pixels are added over
+// the lanes and waves in a fixed order.  (Three passes with an f32 dx and 2
+// bytes a lane took 31 us
+// of the 8 x 128^2 step, this 13.)
 constexpr int kOutChunk = 256;
-__global__ void __launch_bounds__(256) out_bwd_k(Map x, const float* __restrict__ out, const float* __restrict__ tgt,
-                                                 const float* __restrict__ w, MapF dx, float* __restrict__ partial,
-                                                 Shape s, float scale) {
-  __shared__ float red[7][256];
-  const int chunk = blockIdx.x, t = threadIdx.x;
-  const int ci = x.c, G = 256 / ci, i = t % ci, g = t / ci;
-  const long long P = s.pixels();
-  const long long p0 = static_cast<long long>(chunk) * kOutChunk;
-  const long long p1 = p0 + kOutChunk < P ? p0 + kOutChunk : P;
-  float dw0 = 0.f, dw1 = 0.f, dw2 = 0.f, db0 = 0.f, db1 = 0.f, db2 = 0.f, ls = 0.f;
-  if (g < G) {
-    const float w0 = w[i * 3], w1 = w[i * 3 + 1], w2 = w[i * 3 + 2];
-    for (long long p = p0 + g; p < p1; p += G) {
-      const float e0 = out[p * 3] - tgt[p * 3], e1 = out[p * 3 + 1] - tgt[p * 3 + 1], e2 = out[p * 3 + 2] - tgt[p * 3 + 2];
-      const float g0 = scale * e0, g1 = scale * e1, g2 = scale * e2;
-      const float xi = from_bf16(x.p[p * x.ld + x.off + i]);
-      dw0 = fmaf(xi, g0, dw0);
-      dw1 = fmaf(xi, g1, dw1);
-      dw2 = fmaf(xi, g2, dw2);
-      dx.p[p * dx.ld + dx.off + i] = g0 * w0 + g1 * w1 + g2 * w2;
-      db0 += g0;
-      db1 += g1;
-      db2 += g2;
-      ls = fmaf(e0, e0, ls);
-      ls = fmaf(e1, e1, ls);
-      ls = fmaf(e2, e2, ls);
+__global__ void __launch_bounds__(256) out_bwd_k(Map x, const float* __restrict__ base, int base_ld,
+                                                 const float* __restrict__ tgt, const float* __restrict__ w,
+                                                 const float* __restrict__ b, Map g, float* __restrict__ bias,
+                                                 float* __restrict__ partial, long long P, float scale) {
+  __shared__ float red[4][36 * 4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q = tid & 3;
+  float wl[8][3];
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) wl[i][c] = w[(q * 8 + i) * 3 + c];
+  // 24 dw, 8 sums of g, 3 db and the loss (the last four the same in all lanes of a pixel)
+  float v[36];
+#pragma unroll
+  for (int i = 0; i < 36; ++i) v[i] = 0.f;
+  const long long p0 = static_cast<long long>(blockIdx.x) * kOutChunk;
+#pragma unroll
+  for (int k = 0; k < kOutChunk / 64; ++k) {
+    const long long p = p0 + (tid >> 2) + 64 * k;
+    const bool ok = p < P;
+    // every lane takes the whole row, so that the sums run in channel order
+    float a[3] = {0.f, 0.f, 0.f}, xi[8], d[3];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) xi[i] = 0.f;
+#pragma unroll
+    for (int c8 = 0; c8 < 4; ++c8) {
+      uint4 x4 = {0u, 0u, 0u, 0u};
+      if (ok) x4 = *reinterpret_cast<const uint4*>(x.p + p * x.ld + x.off + c8 * 8);
+      const uint32_t xw[4] = {x4.x, x4.y, x4.z, x4.w};
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float f = (i & 1) ? bf16_hi(xw[i >> 1]) : bf16_lo(xw[i >> 1]);
+        if (c8 == q) xi[i] = f;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) a[c] = fmaf(f, w[(c8 * 8 + i) * 3 + c], a[c]);
+      }
     }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const float e = ok ? ((base[p * base_ld + c] + b[c]) + a[c]) - tgt[p * 3 + c] : 0.f;
+      d[c] = scale * e;
+      v[32 + c] += d[c];
+      v[35] = fmaf(e, e, v[35]);
+    }
+    float gi[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) v[i * 3 + c] = fmaf(xi[i], d[c], v[i * 3 + c]);
+      gi[i] = xi[i] > 0.f ? d[0] * wl[i][0] + d[1] * wl[i][1] + d[2] * wl[i][2] : 0.f;
+      v[24 + i] += gi[i];
+    }
+    if (ok)
+      *reinterpret_cast<uint4*>(g.p + p * g.ld + g.off + q * 8) =
+          uint4{pack_bf16(gi[0], gi[1]), pack_bf16(gi[2], gi[3]), pack_bf16(gi[4], gi[5]), pack_bf16(gi[6], gi[7])};
   }
-  const float v[7] = {dw0, dw1, dw2, db0, db1, db2, ls};
 #pragma unroll
-  for (int k = 0; k < 7; ++k) red[k][t] = v[k];
+  for (int i = 0; i < 36; ++i) {
+    v[i] += __shfl_xor(v[i], 4, 64);
+    v[i] += __shfl_xor(v[i], 8, 64);
+    v[i] += __shfl_xor(v[i], 16, 64);
+    v[i] += __shfl_xor(v[i], 32, 64);
+  }
+  if (lane < 4) {
+#pragma unroll
+    for (int i = 0; i < 36; ++i) red[wave][q * 36 + i] = v[i];
+  }
   __syncthreads();
-  const int n = ci * 3 + 4;
-  float* q = partial + static_cast<size_t>(chunk) * n;
-  if (t < ci) {  // dw[t][*]: this channel's groups in order
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      float a = 0.f;
-      for (int gg = 0; gg < G; ++gg) a += red[k][gg * ci + t];
-      q[t * 3 + k] = a;
-    }
-  } else if (t < ci + 4) {  // db and the loss: every (group, channel) thread, in thread order
-    const int k = 3 + (t - ci);
-    float a = 0.f;
-    for (int u = 0; u < G * ci; u += ci)  // one value per group: the threads of channel 0
-      a += red[k][u];
-    q[ci * 3 + (t - ci)] = a;
+  if (tid < 36 * 4) {
+    const float sum = ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid];
+    const int qq = tid / 36, i = tid - qq * 36;
+    float* out = partial + static_cast<size_t>(blockIdx.x) * 100;
+    if (i < 24) out[qq * 24 + i] = sum;
+    else if (i < 32) bias[static_cast<size_t>(blockIdx.x) * 32 + qq * 8 + i - 24] = sum;
+    else if (qq == 0) out[96 + i - 32] = sum;
   }
 }
 
@@ -1358,12 +1512,70 @@ hipError_t launch_tile(const Map& x, const Map& x2, const uint16_t* w, const flo
   return launch_conv<BN, CP, TH, UP, kEpiPlain>(x, x2, w, bias, y, pool, none, s, st);
 }
 
+// Rows of a one-tile convolution's tiles: 8, or 4 where 8 leave fewer than two
+// workgroups for each compute unit (8 x 128^2
+// step, all kernels: from 256 workgroups on 384 us, from 512 379, from 1024
+// 387).
+#ifndef DFB_TILE_MIN
+#define DFB_TILE_MIN 512
+#endif
+constexpr int kTileMin = DFB_TILE_MIN;
+int tile_rows(const Shape& s, int co) {
+  const long long tiles = static_cast<long long>(s.n) * ((s.h + 7) / 8) * ((s.w + kTW - 1) / kTW);
+  return tiles * (co / 32) >= kTileMin ? 8 : 4;
+}
+int conv_tiles(const Shape& s, int co) {
+  const int th = tile_rows(s, co);
+  return static_cast<int>(static_cast<long long>(s.n) * ((s.h + th - 1) / th) * ((s.w + kTW - 1) / kTW));
+}
+
+template <int NCH, int MB, bool UP, int EPI, bool SPLIT>
+hipError_t launch_tile_conv(const Map& x, const Map& x2, const uint16_t* w, int co, const float* bias, const TileOut& o,
+                            const Shape& s, hipStream_t st) {
+  using C = TileCfg<NCH, MB, UP, EPI == kTileFwd || EPI == kTileFwdPool>;
+  if (C::BYTES > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_tile_k<NCH, MB, UP, EPI, SPLIT>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, C::BYTES);
+    if (e != hipSuccess) return e;
+  }
+  conv_tile_k<NCH, MB, UP, EPI, SPLIT>
+      <<<static_cast<unsigned>(conv_tiles(s, co) * (co / 32)), 256, C::BYTES, st>>>(x, x2, w, co, bias, o, s);
+  return hipGetLastError();
+}
+// Output tiles from which a forward layer takes the persistent kernel: with
+// fewer, compute units are left without a workgroup, and the one-tile kernel's
+// 32-channel groups and 4-row tiles fill them (8 x 128^2 training: the seven
+// layers below it 104 -> 56 us; with 256 to 512 tiles the two are within a
+// microsecond).
+#ifndef DFB_PERSIST_MIN
+#define DFB_PERSIST_MIN 256
+#endif
+constexpr int kPersistMin = DFB_PERSIST_MIN;
+template <bool UP, int CIN>
+hipError_t tile_fwd(const Map& x, const Map& x2, const uint16_t* w, const float* bias, const Map& y, const Map& pool,
+                    const Shape& s, hipStream_t st) {
+  const Map none{nullptr, 0, 0, 0};
+  const TileOut o{y, none, pool, nullptr, 0, 0, nullptr};
+  const bool tall = tile_rows(s, y.c) == 8;
+#define DFB_TILE(EPI_)                                                                                   \
+  return tall ? launch_tile_conv<CIN / 32, 2, UP, EPI_, false>(x, x2, w, y.c, bias, o, s, st)              \
+              : launch_tile_conv<CIN / 32, 1, UP, EPI_, false>(x, x2, w, y.c, bias, o, s, st)
+  if (pool.p) DFB_TILE(kTileFwdPool);
+  DFB_TILE(kTileFwd);
+#undef DFB_TILE
+}
+
 template <bool UP>
 hipError_t conv_tile(const Map& x, const Map& x2, const uint16_t* w, const float* bias, const Map& y,
                      const Map& pool, const Shape& s, hipStream_t st) {
   const int cp = (x.c + x2.c + 31) / 32 * 32;
-#define DFB_CONV(BN_, CP_, TH_, THU_) \
-  if (y.c == BN_ && cp == CP_) return launch_tile<BN_, CP_, UP ? THU_ : TH_, UP>(x, x2, w, bias, y, pool, s, st);
+#define DFB_CONV(BN_, CP_, TH_, THU_)                                                                               \
+  if (y.c == BN_ && cp == CP_) {                                                                                    \
+    constexpr int TH = UP ? THU_ : TH_;                                                                             \
+    if (cp == x.c + x2.c && static_cast<long long>(s.n) * ((s.h + TH - 1) / TH) * ((s.w + kTW - 1) / kTW) < kPersistMin) \
+      return tile_fwd<UP, CP_>(x, x2, w, bias, y, pool, s, st);                                                     \
+    return launch_tile<BN_, CP_, TH, UP>(x, x2, w, bias, y, pool, s, st);                                           \
+  }
   DFB_CONV(32, 32, DFB_TH_32_32, DFB_TH_32_32)
   DFB_CONV(32, 64, DFB_TH_32_64, DFB_THU_32_64)
   DFB_CONV(64, 32, DFB_TH_64_32, DFB_TH_64_32)
@@ -1390,26 +1602,41 @@ hipError_t conv3x3_fwd(const Map& x, const uint16_t* w_fwd, const float* bias, c
   return up ? conv_tile<true>(x, xb, w_fwd, bias, y, pl, s, st) : conv_tile<false>(x, xb, w_fwd, bias, y, pl, s, st);
 }
 
-int gate_rows(const Shape& s, int c) { return static_cast<int>(blocks(s.pixels() * (c / 8), 256)); }
-
-hipError_t conv3x3_gate(const MapF& dy, const Map& y, const Map& g, float* partial, const Shape& s, hipStream_t st) {
-  if (dy.c % 8 || dy.ld % 4 || dy.off % 4 || y.ld % 8 || y.off % 8 || g.ld % 8 || g.off % 8 || g.c != dy.c ||
-      256 % (dy.c / 8))
-    return hipErrorInvalidValue;
-  gate_k<<<static_cast<unsigned>(gate_rows(s, dy.c)), 256, 0, st>>>(dy, y, g, partial, s);
-  return hipGetLastError();
+// The data gradient from `in` channels to ci.
+template <int EPI>
+hipError_t tile_bwd(const Map& g, const uint16_t* w, int ci, const TileOut& o, const Shape& s, hipStream_t st) {
+  const Map none{nullptr, 0, 0, 0};
+  const bool tall = tile_rows(s, ci) == 8;
+#define DFB_TILE(C_, MB_, SPLIT_) return launch_tile_conv<C_ / 32, MB_, false, EPI, SPLIT_>(g, none, w, ci, nullptr, o, s, st)
+#define DFB_TILES(C_)                                    \
+  case C_:                                               \
+    if (ci == 32 && tall) DFB_TILE(C_, 2, true);         \
+    if (ci == 32) DFB_TILE(C_, 1, true);                 \
+    if (tall) DFB_TILE(C_, 2, false);                    \
+    DFB_TILE(C_, 1, false);
+  switch (g.c) {
+    DFB_TILES(32)
+    DFB_TILES(64)
+    DFB_TILES(128)
+  }
+#undef DFB_TILES
+#undef DFB_TILE
+  return hipErrorInvalidValue;
 }
 
-hipError_t conv3x3_dgrad(const Map& g, const uint16_t* w_dgrad, const MapF& dx, const Shape& s, hipStream_t st) {
-  const unsigned nb = blocks(s.pixels(), BM);
-  if (g.c % 8 || g.ld % 8 || g.off % 8) return hipErrorInvalidValue;
-  switch (dx.c) {
-    case 32: conv_dgrad_k<32><<<nb, 256, 0, st>>>(g, w_dgrad, dx, s); break;
-    case 64: conv_dgrad_k<64><<<nb, 256, 0, st>>>(g, w_dgrad, dx, s); break;
-    case 128: conv_dgrad_k<128><<<nb, 256, 0, st>>>(g, w_dgrad, dx, s); break;
-    default: return hipErrorInvalidValue;
+hipError_t conv3x3_bwd(const Map& g, const uint16_t* w_dgrad, int ci, Adjoint adj, const TileOut& o, const Shape& s,
+                       hipStream_t st) {
+  if (g.ld % 8 || g.off % 8 || o.y.ld % 8 || o.y.off % 8 || o.g.ld % 8 || o.g.off % 8 || o.skip_ld % 4 || ci % 32)
+    return hipErrorInvalidValue;
+  // per-image byte offsets of g are 32-bit
+  if (static_cast<long long>(s.h) * s.w * g.ld >= (1LL << 30)) return hipErrorInvalidValue;
+  if (conv_tiles(s, ci) == 0) return hipSuccess;
+  switch (adj) {
+    case Adjoint::kSame: return tile_bwd<kTileGate>(g, w_dgrad, ci, o, s, st);
+    case Adjoint::kUp: return tile_bwd<kTileUpGate>(g, w_dgrad, ci, o, s, st);
+    case Adjoint::kPool: return tile_bwd<kTilePoolGate>(g, w_dgrad, ci, o, s, st);
   }
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 // Workgroups of the weight-gradient launch at most, per layer (rows of 64 x 64
@@ -1443,15 +1670,6 @@ int update_blocks(const UpdateLayer& L) { return L.cig * L.cog * L.cb * L.ob * k
 hipError_t update_params(const UpdatePlan& plan, const float* partial, const AdamArgs& a, hipStream_t st) {
   const int n = plan.conv_blocks + plan.bias[kConvLayers].first + plan.bias[kConvLayers].n;
   update_k<<<static_cast<unsigned>(n), 256, 0, st>>>(plan, partial, a);
-  return hipGetLastError();
-}
-
-hipError_t avgpool2_backward_add(const MapF& dy, const MapF& dx, const Shape& s_in, hipStream_t st) {
-  avgpool2_bwd_add_k<<<blocks(s_in.pixels() * dx.c, 256), 256, 0, st>>>(dy, dx, s_in);
-  return hipGetLastError();
-}
-hipError_t upsample2_backward(const MapF& dy, const MapF& dx, const Shape& s_in, hipStream_t st) {
-  upsample2_bwd_k<<<blocks(s_in.pixels() * dx.c, 256), 256, 0, st>>>(dy, dx, s_in);
   return hipGetLastError();
 }
 
@@ -1505,11 +1723,12 @@ hipError_t out_conv_fwd(const Map& x, const float* w, const float* b, const floa
 
 int out_rows(const Shape& s) { return static_cast<int>((s.pixels() + kOutChunk - 1) / kOutChunk); }
 
-hipError_t out_conv_backward(const Map& x, const float* out, const float* target, const float* w, const MapF& dx,
-                             float* partial, const Shape& s, hipStream_t st) {
-  if (x.c > 64) return hipErrorInvalidValue;
+hipError_t out_conv_backward(const Map& x, const float* base, int base_ld, const float* target, const float* w,
+                             const float* b, const Map& g, float* bias, float* partial, const Shape& s, hipStream_t st) {
+  if (x.c != 32 || x.ld % 8 || x.off % 8 || g.ld % 8 || g.off % 8) return hipErrorInvalidValue;
   const float scale = 2.f / static_cast<float>(s.pixels() * 3);
-  out_bwd_k<<<static_cast<unsigned>(out_rows(s)), 256, 0, st>>>(x, out, target, w, dx, partial, s, scale);
+  out_bwd_k<<<static_cast<unsigned>(out_rows(s)), 256, 0, st>>>(x, base, base_ld, target, w, b, g, bias, partial,
+                                                               s.pixels(), scale);
   return hipGetLastError();
 }
 

@@ -13,7 +13,6 @@
 #include "unet_internal.h"
 
 using dfb::unet::Map;
-using dfb::unet::MapF;
 using dfb::unet::Shape;
 
 namespace {
@@ -73,10 +72,7 @@ struct dfb_denoiser_ctx {
            *pool2 = nullptr, *e3a = nullptr, *e3b = nullptr, *d2a = nullptr, *d2b = nullptr,
            *d1a = nullptr, *d1b = nullptr;
   float* out = nullptr;  // [P0][3] network output of the last forward
-  // gradients (f32)
-  float *g_d1b = nullptr, *g_d1a = nullptr, *g_cat1 = nullptr, *g_upd2 = nullptr, *g_d2b = nullptr,
-        *g_d2a = nullptr, *g_cat2 = nullptr, *g_up3 = nullptr, *g_e3b = nullptr, *g_e3a = nullptr,
-        *g_pool2 = nullptr, *g_e2a = nullptr, *g_pool1 = nullptr, *g_e1a = nullptr;
+  float *skip1 = nullptr, *skip2 = nullptr;  // gradients (f32) of the skips
   float* scratch = nullptr;    // partial sums of every gradient (TrainPlan)
   uint16_t* gate[12] = {};     // gated output gradients of the layers (bf16)
   float* loss_dev = nullptr;
@@ -116,7 +112,6 @@ dfb_status dalloc(dfb_denoiser_ctx* n, T** p, size_t count) {
 }
 
 Map mp(uint16_t* p, int ld, int off, int c) { return Map{p, ld, off, c}; }
-MapF mf(float* p, int ld, int off, int c) { return MapF{p, ld, off, c}; }
 
 dfb_status check_shape(dfb_denoiser_ctx* n, int32_t b, int32_t h, int32_t w) {
   if (b <= 0 || h <= 0 || w <= 0 || h % 4 || w % 4)
@@ -195,7 +190,8 @@ dfb_status forward(dfb_denoiser_ctx* n, const float* in, const Shape& s0, bool t
                                          s0, st));
   } else {
     NHIP(n, conv3x3_fwd(mp(n->d1a, 32, 0, 32), n->wf[DEC1B], B(DEC1B), mp(n->d1b, 32, 0, 32), s0, st));
-    NHIP(n, dfb::unet::out_conv_fwd(mp(n->d1b, 32, 0, 32), W + n->off_ow, W + n->off_ob, in, 6, n->out, s0, st));
+    if (!training)  // the backward pass computes it itself
+      NHIP(n, dfb::unet::out_conv_fwd(mp(n->d1b, 32, 0, 32), W + n->off_ow, W + n->off_ob, in, 6, n->out, s0, st));
   }
   n->last = s0;
   n->planar = !training;
@@ -204,6 +200,16 @@ dfb_status forward(dfb_denoiser_ctx* n, const float* in, const Shape& s0, bool t
 }
 
 Shape level_shape(const Shape& s0, int level) { return Shape{s0.n, s0.h >> level, s0.w >> level}; }
+
+// The layer whose data gradient is carried through to layer i's output
+// gradient (the last layer's comes from the output conv), and the rows of
+// bias-gradient partials it makes.
+int gate_rows(int i, const Shape& s0) {
+  static const int from[12] = {ENC1B, ENC2A, ENC2B, ENC3A, ENC3B, UP2, DEC2A, DEC2B, UP1, DEC1A, DEC1B, -1};
+  if (from[i] < 0) return dfb::unet::out_rows(s0);
+  const Conv& c = kConv[from[i]];
+  return dfb::unet::conv_tiles(level_shape(s0, c.level), c.ci);
+}
 
 // Where the partial sums of a training step on a batch of shape s0 lie in the
 // scratch allocation, and what the two launches that make and use them take.
@@ -257,7 +263,7 @@ TrainPlan train_plan(const dfb_denoiser_ctx* n, const Shape& s0) {
     U.wf = n->wf[i];
     U.wd = n->wd[i];
     T.up.conv_blocks += dfb::unet::update_blocks(U);
-    T.up.bias[i] = {first_out, c.co, dfb::unet::gate_rows(s, c.co), static_cast<int>(n->off_b[i]), T.floats};
+    T.up.bias[i] = {first_out, c.co, gate_rows(i, s0), static_cast<int>(n->off_b[i]), T.floats};
     T.floats += static_cast<size_t>(T.up.bias[i].rows) * c.co;
     first_out += c.co;
   }
@@ -266,48 +272,31 @@ TrainPlan train_plan(const dfb_denoiser_ctx* n, const Shape& s0) {
   return T;
 }
 
-dfb_status backward(dfb_denoiser_ctx* n, const float* target, const Shape& s0, const TrainPlan& T) {
-  const Shape s1 = level_shape(s0, 1), s2 = level_shape(s0, 2);
+dfb_status backward(dfb_denoiser_ctx* n, const float* in, const float* target, const Shape& s0, const TrainPlan& T) {
   hipStream_t st = n->stream;
   float* S = n->scratch;
   using namespace dfb::unet;
-  NHIP(n, out_conv_backward(mp(n->d1b, 32, 0, 32), n->out, target, n->w + n->off_ow, mf(n->g_d1b, 32, 0, 32),
-                            S + T.up.bias[12].part, s0, st));
-  // one conv layer: gate its output gradient dy (output y) once, with the
-  // bias gradient's partial sums, then the data gradient into dx (unless null)
-  auto layer = [&](int L, const MapF& dy, const Map& y, const MapF* dx, const Shape& sh) {
-    const Map gm{n->gate[L], dy.c, 0, dy.c};
-    hipError_t e = conv3x3_gate(dy, y, gm, S + T.up.bias[L].part, sh, st);
-    if (e == hipSuccess && dx) e = conv3x3_dgrad(gm, n->wd[L], *dx, sh, st);
-    return e;
+  auto gate = [&](int L) { return mp(n->gate[L], kConv[L].co, 0, kConv[L].co); };
+  NHIP(n, out_conv_backward(mp(n->d1b, 32, 0, 32), in, 6, target, n->w + n->off_ow, n->w + n->off_ob, gate(DEC1B),
+                            S + T.up.bias[DEC1B].part, S + T.up.bias[12].part, s0, st));
+  // layer L's data gradient, carried through to the output gradient of the
+  // layer `to`, whose output is y; split, skip, skip_ld as in TileOut
+  auto layer = [&](int L, int to, const Map& y, Adjoint adj, int split = 1 << 20, float* skip = nullptr, int skip_ld = 0) {
+    TileOut o{y, gate(to), Map{nullptr, 0, 0, 0}, skip, skip_ld, split, S + T.up.bias[to].part};
+    return conv3x3_bwd(gate(L), n->wd[L], kConv[L].ci, adj, o, level_shape(s0, kConv[L].level), st);
   };
-  const MapF dx_d1a = mf(n->g_d1a, 32, 0, 32), dx_cat1 = mf(n->g_cat1, 64, 0, 64), dx_upd2 = mf(n->g_upd2, 64, 0, 64);
-  const MapF dx_d2a = mf(n->g_d2a, 64, 0, 64), dx_cat2 = mf(n->g_cat2, 128, 0, 128), dx_up3 = mf(n->g_up3, 128, 0, 128);
-  const MapF dx_e3a = mf(n->g_e3a, 128, 0, 128), dx_pool2 = mf(n->g_pool2, 64, 0, 64), dx_e2a = mf(n->g_e2a, 64, 0, 64);
-  const MapF dx_pool1 = mf(n->g_pool1, 32, 0, 32), dx_e1a = mf(n->g_e1a, 32, 0, 32);
-  // dec1b, dec1a
-  NHIP(n, layer(DEC1B, mf(n->g_d1b, 32, 0, 32), mp(n->d1b, 32, 0, 32), &dx_d1a, s0));
-  NHIP(n, layer(DEC1A, mf(n->g_d1a, 32, 0, 32), mp(n->d1a, 32, 0, 32), &dx_cat1, s0));
-  // up1 (input: upsampled dec2b), output cat1[0:32]
-  NHIP(n, layer(UP1, mf(n->g_cat1, 64, 0, 32), mp(n->cat1, 64, 0, 32), &dx_upd2, s0));
-  NHIP(n, upsample2_backward(mf(n->g_upd2, 64, 0, 64), mf(n->g_d2b, 64, 0, 64), s1, st));
-  // dec2b, dec2a
-  NHIP(n, layer(DEC2B, mf(n->g_d2b, 64, 0, 64), mp(n->d2b, 64, 0, 64), &dx_d2a, s1));
-  NHIP(n, layer(DEC2A, mf(n->g_d2a, 64, 0, 64), mp(n->d2a, 64, 0, 64), &dx_cat2, s1));
-  // up2 (input: upsampled enc3b), output cat2[0:64]
-  NHIP(n, layer(UP2, mf(n->g_cat2, 128, 0, 64), mp(n->cat2, 128, 0, 64), &dx_up3, s1));
-  NHIP(n, upsample2_backward(mf(n->g_up3, 128, 0, 128), mf(n->g_e3b, 128, 0, 128), s2, st));
-  // enc3b, enc3a
-  NHIP(n, layer(ENC3B, mf(n->g_e3b, 128, 0, 128), mp(n->e3b, 128, 0, 128), &dx_e3a, s2));
-  NHIP(n, layer(ENC3A, mf(n->g_e3a, 128, 0, 128), mp(n->e3a, 128, 0, 128), &dx_pool2, s2));
-  // skip 2: the enc2b output also fed pool2
-  NHIP(n, avgpool2_backward_add(mf(n->g_pool2, 64, 0, 64), mf(n->g_cat2, 128, 64, 64), s1, st));
-  NHIP(n, layer(ENC2B, mf(n->g_cat2, 128, 64, 64), mp(n->cat2, 128, 64, 64), &dx_e2a, s1));
-  NHIP(n, layer(ENC2A, mf(n->g_e2a, 64, 0, 64), mp(n->e2a, 64, 0, 64), &dx_pool1, s1));
-  // skip 1: the enc1b output also fed pool1
-  NHIP(n, avgpool2_backward_add(mf(n->g_pool1, 32, 0, 32), mf(n->g_cat1, 64, 32, 32), s0, st));
-  NHIP(n, layer(ENC1B, mf(n->g_cat1, 64, 32, 32), mp(n->cat1, 64, 32, 32), &dx_e1a, s0));
-  NHIP(n, layer(ENC1A, mf(n->g_e1a, 32, 0, 32), mp(n->e1a, 32, 0, 32), nullptr, s0));
+  const Adjoint same = Adjoint::kSame;
+  NHIP(n, layer(DEC1B, DEC1A, mp(n->d1a, 32, 0, 32), same));
+  NHIP(n, layer(DEC1A, UP1, mp(n->cat1, 64, 0, 32), same, 1, n->skip1, 32));
+  NHIP(n, layer(UP1, DEC2B, mp(n->d2b, 64, 0, 64), Adjoint::kUp));
+  NHIP(n, layer(DEC2B, DEC2A, mp(n->d2a, 64, 0, 64), same));
+  NHIP(n, layer(DEC2A, UP2, mp(n->cat2, 128, 0, 64), same, 2, n->skip2, 64));
+  NHIP(n, layer(UP2, ENC3B, mp(n->e3b, 128, 0, 128), Adjoint::kUp));
+  NHIP(n, layer(ENC3B, ENC3A, mp(n->e3a, 128, 0, 128), same));
+  NHIP(n, layer(ENC3A, ENC2B, mp(n->cat2, 128, 64, 64), Adjoint::kPool, 1 << 20, n->skip2, 64));
+  NHIP(n, layer(ENC2B, ENC2A, mp(n->e2a, 64, 0, 64), same));
+  NHIP(n, layer(ENC2A, ENC1B, mp(n->cat1, 64, 32, 32), Adjoint::kPool, 1 << 20, n->skip1, 32));
+  NHIP(n, layer(ENC1B, ENC1A, mp(n->e1a, 32, 0, 32), same));
   // every layer's weight gradient
   NHIP(n, conv3x3_wgrad(T.wg, S, st));
   return DFB_OK;
@@ -385,10 +374,7 @@ dfb_status dfb_denoiser_create(const dfb_unet_config* cfg, void* hip_stream, dfb
   struct {
     float** p;
     int64_t n;
-  } grads[] = {{&n->g_d1b, P0 * 32},  {&n->g_d1a, P0 * 32},  {&n->g_cat1, P0 * 64},  {&n->g_upd2, P0 * 64},
-               {&n->g_d2b, P1 * 64},  {&n->g_d2a, P1 * 64},  {&n->g_cat2, P1 * 128}, {&n->g_up3, P1 * 128},
-               {&n->g_e3b, P2 * 128}, {&n->g_e3a, P2 * 128}, {&n->g_pool2, P2 * 64}, {&n->g_e2a, P1 * 64},
-               {&n->g_pool1, P1 * 32}, {&n->g_e1a, P0 * 32}, {&n->out, P0 * 3}};
+  } grads[] = {{&n->skip1, P0 * 32}, {&n->skip2, P1 * 64}, {&n->out, P0 * 3}};
   for (auto& a : grads)
     if ((s = dalloc(n, a.p, static_cast<size_t>(a.n)))) return bail(s);
   for (int i = 0; i < 12; ++i) {
@@ -459,7 +445,7 @@ dfb_status dfb_denoiser_train_step(dfb_denoiser n, const float* in, const float*
   const Shape s0{b, h, w};
   const TrainPlan T = train_plan(n, s0);
   if ((s = forward(n, in, s0, true)) != DFB_OK) return s;
-  if ((s = backward(n, target, s0, T)) != DFB_OK) return s;
+  if ((s = backward(n, in, target, s0, T)) != DFB_OK) return s;
   dfb::unet::AdamArgs a{n->w, n->g, n->m, n->v, n->loss_dev, lr, n->cfg.beta1, n->cfg.beta2, n->cfg.eps, 1.f, 1.f, 0};
   if (apply_update) {
     n->step += 1;

@@ -1,0 +1,42 @@
+"""Layers with few output tiles take a kernel with one tile and 32 channels per
+workgroup, others the persistent one; data gradients take 4- or 8-row tiles by
+the number of tiles.  An image alone and the same image 256 times over go
+different ways at every resolution.
+
+Forward: the two kernels sum in the same order, so the outputs are the same
+bits.  Gradients: 256 copies scale the output gradient by an exact power of two,
+so the gated gradients are the same bits and only the f32 sums over pixels are
+split differently; with at most 2000 additions in a chain that is 2000 * 2^-24
+= 1.2e-4 of the sum of magnitudes, and 1e-4 in the 2-norm is asked."""
+import numpy as np
+import pytest
+
+from gpu_helpers import stream_handle, torch_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("h,w", [(4, 4), (36, 100), (16, 64), (20, 132)])
+def test_one_image_and_many(h, w):
+    torch = torch_dev()
+    import paper_2305_07083_amd as dfb
+    n = 256
+    rng = np.random.default_rng(h * w)
+    mu = rng.random((1, h, w, 4))
+    x = np.concatenate([mu, rng.normal(-6, 1, (1, h, w, 1)), np.full((1, h, w, 1), 0.25)], axis=3).astype(np.float32)
+    target = np.clip(mu[..., :3] + rng.normal(0, 0.05, (1, h, w, 3)), 0, 1).astype(np.float32)
+    outs, acts, grads = [], [], []
+    with dfb.Denoiser(n * h * w, seed=5, stream=stream_handle()) as d:
+        for k in (1, n):
+            xd = torch.from_numpy(x).cuda().repeat(k, 1, 1, 1)
+            td = torch.from_numpy(target).cuda().repeat(k, 1, 1, 1)
+            out = torch.empty((k, h, w, 3), dtype=torch.float32, device="cuda")
+            dfb.dfb_denoiser_forward(d.net, xd, out, k, h, w)
+            outs.append(out.cpu().numpy())
+            acts.append([np.asarray(dfb.dfb_denoiser_read_activation(d.net, i, k, h, w)) for i in range(12)])
+            dfb.dfb_denoiser_train_step(d.net, xd, td, k, h, w, 1e-3, False)
+            grads.append(dfb.dfb_denoiser_get_params(d.net, 1).astype(np.float64))
+    for a, b in [(outs[0], outs[1])] + list(zip(*acts)):
+        a, b = a.reshape(1, -1), b.reshape(n, -1)
+        assert np.array_equal(np.repeat(a, n, axis=0), b)
+    assert np.linalg.norm(grads[0] - grads[1]) <= 1e-4 * np.linalg.norm(grads[0])
