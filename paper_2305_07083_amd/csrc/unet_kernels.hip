@@ -1049,12 +1049,22 @@ __global__ void __launch_bounds__(256) conv_tile_k(Map x, Map x2, const uint16_t
 // at and below it: three x operands and one g operand feed nine MFMAs.
 //
 // All layers in one launch because one layer's tiles fill the chip for only
-// a few microseconds: 8 x 128^2 step, all 12 layers: 12 launches with one tap
-// per workgroup 367 us, 88 us now.
+// a few microseconds.  Bound by the latency of a tile's loads: its MFMAs take
+// 0.5 to 2 us.  8 x 128^2 step, all 12 layers: 12 launches with one tap per
+// workgroup 367 us, tiles staged through registers, x before g, 80 (with
+// spills), straight into LDS 54.
 constexpr int kWgTH = 8;                                // tile rows
 constexpr int kWgXP = (kWgTH + 2) * (kTW + 2);          // halo pixels
 constexpr int kWgGP = kWgTH * kTW;                      // pixels
 constexpr int kWgAcc = 9 * 16;                          // accumulators of a wave
+constexpr int kWgLds = 160 * 1024 / 2 / 16;             // 16-byte chunks of LDS: half a compute unit's
+// s_waitcnt until at most n vector memory operations are outstanding (gfx9 encoding)
+constexpr int wait_vm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
 // 16 pixels x 32 channels of a slice as an MFMA operand: this lane's channel,
@@ -1093,67 +1103,97 @@ __device__ __forceinline__ void wgrad_rows(const char* xr, const char* gr, f32x1
   }
 }
 
+// 16 bytes from each lane's offset straight into LDS at `at` (wave-uniform) +
+// 16 * lane; zeros where the offset is out of range.
+__device__ __forceinline__ void buf_load_lds16(__amdgpu_buffer_rsrc_t r, uint4* at, int byte_off) {
+  typedef __attribute__((address_space(3))) void* P;
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (P)at, 16, byte_off, 0, 0, 0);
+}
+
 // One workgroup's share of layer L, a wave taking NR rows of a tile (8 / 4 / 2
-// with 4 / 2 / 1 blocks).
-template <int NR>
+// with 4 / 2 / 1 blocks), of CB c_in and OB c_out slices.  Tiles go straight
+// from memory into LDS, x and g together, without passing through the
+// registers the accumulators fill; the single blocks' tiles, whose MFMAs are
+// the shortest, leave room for two and the next one is on its way meanwhile.
+template <int CB, int OB>
 __device__ __forceinline__ void wgrad_layer(const WgradLayer& L, int local, uint4* lds, float* __restrict__ partial) {
-  constexpr int rows = NR, parts = kWgTH / NR, nblk = 4 / parts;
-  uint4* xs = lds;                   // [2][kWgXP][4]
-  uint4* gs = lds + 2 * kWgXP * 4;   // [2][kWgGP][4]
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  constexpr int nblk = CB * OB, NR = 2 * nblk, rows = NR, parts = kWgTH / NR;
+  constexpr int XIT = (CB * kWgXP * 4 + 255) / 256, GIT = OB * kWgGP * 4 / 256;
+  constexpr int TILE_CH = (XIT + GIT) * 256, NBUF = nblk == 1 ? 2 : 1;  // 16-byte chunks of a staged tile
+  static_assert(NBUF * TILE_CH <= kWgLds, "staged tiles fit");
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ng = L.cig * L.cog, chunk = local / ng, group = local - chunk * ng;
-  const int c0 = (group % L.cig) * L.cb * 32, o0 = (group / L.cig) * L.ob * 32;
+  const int c0 = (group % L.cig) * CB * 32, o0 = (group / L.cig) * OB * 32;
   const int h = L.s.h, w = L.s.w, sw = L.up ? w / 2 : w, sh = L.up ? h / 2 : h, up = L.up;
   const int tiles_x = (w + kTW - 1) / kTW, tiles_y = (h + kWgTH - 1) / kWgTH, per_img = tiles_x * tiles_y;
   const int t0 = static_cast<int>(static_cast<long long>(chunk) * L.tiles / L.chunks);
   const int t1 = static_cast<int>(static_cast<long long>(chunk + 1) * L.tiles / L.chunks);
   // wave -> block (c_in slice, c_out slice) and part of the rows
-  const int blk = wave % nblk, part = wave / nblk, bc = blk % L.cb, bo = blk / L.cb;
+  const int blk = wave % nblk, part = wave / nblk, bc = blk % CB, bo = blk / CB;
   const int l16 = lane & 15, lbyte = ((lane >> 5) * 8 + (l16 >> 2)) * 64 + ((lane >> 4) & 1) * 32 + (l16 & 3) * 8;
   const int r0 = part * rows;
-  const char* xr = reinterpret_cast<const char*>(xs) + (bc * kWgXP + r0 * (kTW + 2)) * 64 + lbyte;
-  const char* gr = reinterpret_cast<const char*>(gs) + (bo * kWgGP + r0 * kTW) * 64 + lbyte;
+  const int xat = (bc * kWgXP + r0 * (kTW + 2)) * 64 + lbyte, gat = XIT * 256 * 16 + (bo * kWgGP + r0 * kTW) * 64 + lbyte;
   f32x16 acc[9];
 #pragma unroll
   for (int t = 0; t < 9; ++t)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
-  constexpr int XIT = (2 * kWgXP * 4 + 255) / 256, GIT = 2 * kWgGP * 4 / 256;
-  for (int t = t0; t < t1; ++t) {
+  // this thread's chunk k of x: slice, halo pixel (row, column) and 8 channels
+  // (one past the last is padding: no channel), packed as row | column << 8 |
+  // channel << 16, kept while the accumulators take the other registers
+  const int xld = L.xld, co = L.co;
+  const long long ximg = static_cast<long long>(sh) * sw * xld, gimg = static_cast<long long>(h) * w * co;
+  const uint16_t *xp = L.x, *gp = L.g;
+  int xe[XIT];
+#pragma unroll
+  for (int k = 0; k < XIT; ++k) {
+    const int e = tid + 256 * k, sl = e / (kWgXP * 4), q = e - sl * (kWgXP * 4), px = q >> 2, hr = px / (kTW + 2);
+    const int ch = c0 + sl * 32 + (q & 3) * 8;
+    xe[k] = sl < CB && ch < L.xc ? hr | (px - hr * (kTW + 2)) << 8 | ch << 16 : 0xFF;  // row 255 is outside every tile
+  }
+  auto stage = [&](int t, uint4* to) {
     const int n = t / per_img, rem = t - n * per_img, oy = (rem / tiles_x) * kWgTH, ox = (rem % tiles_x) * kTW;
-    const __amdgpu_buffer_rsrc_t xb = buf_rsrc(L.x + static_cast<long long>(n) * sh * sw * L.xld);
-    const __amdgpu_buffer_rsrc_t gb = buf_rsrc(L.g + static_cast<long long>(n) * h * w * L.co);
-    // x, then g: the two together, beside the accumulators, would not fit 256
-    // registers (the other workgroup of the compute unit computes meanwhile)
-    int tl = tid;  // opaque: the chunks' coordinates are computed per tile, not kept beside the accumulators
-    asm volatile("" : "+v"(tl));
-    uint4 xv[XIT];
+    const __amdgpu_buffer_rsrc_t xb = buf_rsrc(xp + n * ximg), gb = buf_rsrc(gp + n * gimg);
+    uint4* at = to + wave * 64;
 #pragma unroll
     for (int k = 0; k < XIT; ++k) {
-      const int e = tl + 256 * k, sl = e / (kWgXP * 4), q = e - sl * (kWgXP * 4), px = q >> 2, hr = px / (kTW + 2);
-      const int r = oy - 1 + hr, c = ox - 1 + px - hr * (kTW + 2), ch = c0 + sl * 32 + (q & 3) * 8;
-      const int ok = (sl < L.cb) & (static_cast<unsigned>(r) < static_cast<unsigned>(h)) &
-                     (static_cast<unsigned>(c) < static_cast<unsigned>(w)) & (ch < L.xc);
-      const int src = up ? (r >> 1) * sw + (c >> 1) : r * sw + c;
-      xv[k] = buf_load16(xb, ok ? (src * L.xld + ch) * 2 : kOOB);
+      const int hr = xe[k] & 0xFF, r = oy - 1 + hr, c = ox - 1 + ((xe[k] >> 8) & 0xFF);
+      int off = ((up ? (r >> 1) * sw + (c >> 1) : r * sw + c) * xld + (xe[k] >> 16)) * 2;
+      asm("" : "+v"(off));  // selected, not branched around
+      const bool ok = (hr < kWgTH + 2) & (static_cast<unsigned>(r) < static_cast<unsigned>(h)) &
+                      (static_cast<unsigned>(c) < static_cast<unsigned>(w));
+      buf_load_lds16(xb, at + 256 * k, ok ? off : kOOB);
     }
-    __syncthreads();  // the previous tile's reads are done
-#pragma unroll
-    for (int k = 0; k < XIT; ++k)
-      if (tl + 256 * k < 2 * kWgXP * 4) xs[tl + 256 * k] = xv[k];
-    __builtin_amdgcn_sched_barrier(0);
-    uint4 gv[GIT];
+    const int gr = oy + (tid >> 7), gc = ox + ((tid >> 2) & 31);  // chunk k: two rows on from chunk k - 1
+    int goff = ((gr * w + gc) * co + o0 + (tid & 3) * 8) * 2;
+    asm("" : "+v"(goff));
 #pragma unroll
     for (int k = 0; k < GIT; ++k) {
-      const int e = tl + 256 * k, sl = e / (kWgGP * 4), q = e - sl * (kWgGP * 4), px = q >> 2;
-      const int r = oy + px / kTW, c = ox + px % kTW, ch = o0 + sl * 32 + (q & 3) * 8;
-      const int ok = (sl < L.ob) & (r < h) & (c < w);
-      gv[k] = buf_load16(gb, ok ? ((r * w + c) * L.co + ch) * 2 : kOOB);
+      const int sl = k / 4, row = 2 * (k % 4);
+      const bool ok = (gr + row < h) & (gc < w);
+      buf_load_lds16(gb, at + 256 * (XIT + k), ok ? goff + (row * w * co + sl * 32) * 2 : kOOB);
     }
-#pragma unroll
-    for (int k = 0; k < GIT; ++k) gs[tl + 256 * k] = gv[k];
-    __syncthreads();
-    wgrad_rows<NR>(xr, gr, acc);
+  };
+  int buf = 0;
+  if (NBUF == 2 && t0 < t1) stage(t0, lds);
+  for (int t = t0; t < t1; ++t) {
+    if (NBUF == 2) {
+      if (t + 1 < t1) {
+        stage(t + 1, lds + (buf ^ 1) * TILE_CH);
+        __builtin_amdgcn_s_waitcnt(wait_vm(XIT + GIT));  // the tile before it has arrived
+      } else {
+        __builtin_amdgcn_s_waitcnt(wait_vm(0));
+      }
+    } else {
+      stage(t, lds);
+      __builtin_amdgcn_s_waitcnt(wait_vm(0));
+    }
+    lds_barrier();
+    const char* tile = reinterpret_cast<const char*>(lds + buf * TILE_CH);
+    wgrad_rows<NR>(tile + xat, tile + gat, acc);
+    lds_barrier();  // every wave is done with the tile
+    if (NBUF == 2) buf ^= 1;
   }
   // the parts of a block, added in a fixed order: 2 and 3 to 0 and 1, then 1 to 0
   float* red = reinterpret_cast<float*>(lds);
@@ -1187,16 +1227,16 @@ __device__ __forceinline__ void wgrad_layer(const WgradLayer& L, int local, uint
 
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 wgrad_k(WgradPlan plan, float* __restrict__ partial) {
-  __shared__ __align__(16) uint4 lds[2 * kWgXP * 4 + 2 * kWgGP * 4];
+  __shared__ __align__(16) uint4 lds[kWgLds];
   const int bid = static_cast<int>(blockIdx.x);
   int li = 0;
   for (int i = 1; i < kConvLayers; ++i)
     if (bid >= plan.l[i].first_wg) li = i;
   const WgradLayer& L = plan.l[li];
-  const int nblk = L.cb * L.ob;
-  if (nblk == 4) wgrad_layer<8>(L, bid - L.first_wg, lds, partial);
-  else if (nblk == 2) wgrad_layer<4>(L, bid - L.first_wg, lds, partial);
-  else wgrad_layer<2>(L, bid - L.first_wg, lds, partial);
+  if (L.cb == 2 && L.ob == 2) wgrad_layer<2, 2>(L, bid - L.first_wg, lds, partial);
+  else if (L.cb == 2) wgrad_layer<2, 1>(L, bid - L.first_wg, lds, partial);
+  else if (L.ob == 2) wgrad_layer<1, 2>(L, bid - L.first_wg, lds, partial);
+  else wgrad_layer<1, 1>(L, bid - L.first_wg, lds, partial);
 }
 
 // ------------------------------------------------------- gradient sums, Adam
