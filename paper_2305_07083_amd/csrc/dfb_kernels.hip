@@ -1386,12 +1386,12 @@ frame_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off,
 //      the lanes and waves of a pixel in a fixed order
 // Every sum is split the same way whatever the launch shape is.
 //
-// Bound by memory: 20 bytes a fragment (fp32), against about 85 vector
-// instructions a key in the sort, which the other workgroup of the compute
-// unit overlaps with its loads.  The LDS sort it replaces for these counts was
+// Bound by vector instructions: about 110 a key (87 in the sort), at three
+// quarters of the issue slots; 20 bytes a fragment (fp32) are half of what
+// memory moves in that time.  The LDS sort it replaces for these counts was
 // bound by the latency of its passes at 8 waves a compute unit, and read each
 // 128-byte line twice.  8192^2 heavy-tailed frame (57.9 GB, up to 512 layers):
-// 36.9 -> 15.6 ms a frame; 1500x1100 fp16, up to 128 layers: 504 -> 186 us.
+// 36.9 -> 13.7 ms a frame; 1500x1100 fp16, up to 128 layers: 504 -> 168 us.
 // Rows are 36 words apart: the 16 lanes of a pixel (at consecutive layers)
 // and the wave's 4 pixels hit all 64 banks once.
 constexpr int kDeepPitch = 36;
@@ -1413,11 +1413,18 @@ struct Quad<float> {
   using RK = RowKey64;
   static __device__ __forceinline__ float4 f(V v) { return make_float4(v.x, v.y, v.z, v.w); }
   static __device__ __forceinline__ uint4 bits(V v) { return __builtin_bit_cast(uint4, v); }
-  static __device__ __forceinline__ uint64_t key(uint32_t bits, int l) {
-    return big_key(depth_bits(__uint_as_float(bits)), l);
+  // Ordered depth bits << 17 | the byte offset of the layer's pixel in the LDS
+  // rows, below the exponent of 2^52 (a normal double, as big_key): the walk
+  // needs no multiplication.  `flip` reverses the key (its sign).
+  static __device__ __forceinline__ uint64_t key(uint32_t bits, int l, int px, uint32_t flip) {
+    const float d = __uint_as_float(bits) + 0.f;  // -0 -> +0
+    const uint32_t b = __float_as_uint(d), s = static_cast<uint32_t>(static_cast<int32_t>(b) >> 31) | 0x80000000u;
+    const uint32_t x = d != d ? 0xFFFFFFFFu : b ^ s;
+    return (static_cast<uint64_t>(__builtin_amdgcn_alignbit(0x2198u | (flip >> 17), x, 15)) << 32) | (x << 17) |
+           static_cast<uint32_t>((l * kDeepPitch + px) * 4);
   }
   static constexpr uint32_t kNaN = 0x7FC00000u;
-  static __device__ __forceinline__ int index(uint64_t k) { return key_layer(k); }
+  static __device__ __forceinline__ int at(uint64_t k, int) { return static_cast<int>(static_cast<uint32_t>(k) & 0x1FFFFu); }
 };
 template <>
 struct Quad<_Float16> {
@@ -1430,11 +1437,12 @@ struct Quad<_Float16> {
     const uint2 u = __builtin_bit_cast(uint2, v);
     return make_uint4(u.x & 0xFFFFu, u.x >> 16, u.y & 0xFFFFu, u.y >> 16);
   }
-  static __device__ __forceinline__ int32_t key(uint32_t bits, int l) {
-    return static_cast<int32_t>(half_depth_bits(static_cast<uint16_t>(bits)) << 12) | l;
+  // Ordered depth bits << 13 | the layer's row of 144 bytes in steps of 16
+  static __device__ __forceinline__ int32_t key(uint32_t bits, int l, int, uint32_t) {
+    return static_cast<int32_t>(half_depth_bits(static_cast<uint16_t>(bits)) << 13) | (l * (kDeepPitch / 4));
   }
   static constexpr uint32_t kNaN = 0x7E00u;
-  static __device__ __forceinline__ int index(int32_t k) { return k & 0xFFF; }
+  static __device__ __forceinline__ int at(int32_t k, int px_bytes) { return ((k & 0x1FFF) << 4) + px_bytes; }
 };
 
 // Pixels p .. p + 3 of a plane (aligned: the host checked P % 4 and the base).
@@ -1457,7 +1465,7 @@ __device__ __forceinline__ float add_xor8(float x) {
 }
 
 // Pixels [p0, p1) of tile u.t, K <= 16 R layers.  Returns the M2 sum (wave 0).
-template <typename FT, int R>
+template <typename FT, int R, int RMAX>
 __device__ __forceinline__ float deep_unit(const FrameArgs& a, const Unit& u, int K_in, int off, int p0, int p1, float* rows,
                                            const int64_t* lofs, float* red) {
   using Q = Quad<FT>;
@@ -1466,7 +1474,13 @@ __device__ __forceinline__ float deep_unit(const FrameArgs& a, const Unit& u, in
   constexpr int NP = (16 * R + kDeepRows - 1) / kDeepRows;  // passes over the layers
   constexpr int NC = NP % 4 == 0 ? 4 : (NP % 3 == 0 ? 3 : NP);  // passes whose colours are in flight together
   static_assert(NP % NC == 0, "colour batches");
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, j = lane & 15, px = wave * 4 + (lane >> 4);
+  // Up to 128 layers the registers hold a group's colours across the sort and
+  // the next group's depths and alphas behind it, so that every load of a group
+  // is under way while another phase computes (8192^2: 12.7 -> 12.2 ms, 1500x1100
+  // fp16: 112 -> 108 us); not in the fp32 kernels held to 80 registers, where
+  // they would spill.
+  constexpr bool EARLY = NP <= 2 && (sizeof(FT) == 2 || RMAX >= 32);
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, j = lane & 15, rank = RK::rank(j), px = wave * 4 + (lane >> 4);
   const int quad0 = (tid & 7) * 4;
   const int P = a.P;
   const size_t plane = static_cast<size_t>(P);
@@ -1474,26 +1488,36 @@ __device__ __forceinline__ float deep_unit(const FrameArgs& a, const Unit& u, in
   float* tend = red + kDeepWaves * 3 * kDeepPx;
   float* asum = tend + kDeepPx;
   float vs = 0.f;
+  // Opaque copies, made anew in every group and phase: the addresses and
+  // the l < K masks of a phase are computed there and not kept in registers
+  // across the sort.
+  int K = K_in, row0 = tid >> 3;
+  V dv[NP], av[NP], cv[NC][3];
+  auto load_depth_alpha = [&](int pq) {
+#pragma unroll
+    for (int i = 0; i < NP; ++i) dv[i] = load_quad<FT>(frag + lofs[min(row0 + i * kDeepRows, K - 1)] + 4 * plane, pq);
+#pragma unroll
+    for (int i = 0; i < NP; ++i) av[i] = load_quad<FT>(frag + lofs[min(row0 + i * kDeepRows, K - 1)] + 3 * plane, pq);
+  };
+  auto load_colours = [&](int i0, int pq) {  // of passes i0 .. i0 + NC - 1
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      asm volatile("" : "+s"(K));
+      const FT* __restrict__ b = frag + lofs[min(row0 + (i0 + i) * kDeepRows, K - 1)];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) cv[i][c] = load_quad<FT>(b + c * plane, pq);
+    }
+  };
+  // past the end of a tile whose last group is ragged: its last pixels again
+  if constexpr (EARLY) load_depth_alpha(p0 + quad0 < P ? p0 + quad0 : P - 4);
   for (int g0 = p0; g0 < p1; g0 += kDeepPx) {
-    // past the end of a tile whose last group is ragged: its last pixels again
     const int pq = g0 + quad0 < P ? g0 + quad0 : P - 4;
-    // Opaque copies, made anew in every group and phase: the addresses and
-    // the l < K masks of a phase are computed there and not kept in registers
-    // across the sort.
-    int K = K_in, row0 = tid >> 3;
+    K = K_in;
+    row0 = tid >> 3;
     asm volatile("" : "+s"(K), "+v"(row0));
     // 1. depth and alpha rows
-    V dv[NP], av[NP];
-#pragma unroll
-    for (int i = 0; i < NP; ++i) {
-      const int l = min(row0 + i * kDeepRows, K - 1);
-      dv[i] = load_quad<FT>(frag + lofs[l] + 4 * plane, pq);
-    }
-#pragma unroll
-    for (int i = 0; i < NP; ++i) {
-      const int l = min(row0 + i * kDeepRows, K - 1);
-      av[i] = load_quad<FT>(frag + lofs[l] + 3 * plane, pq);
-    }
+    if constexpr (!EARLY) load_depth_alpha(pq);
+    if constexpr (EARLY) load_colours(0, pq);
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
       const int l = min(row0 + i * kDeepRows, K - 1);
@@ -1503,12 +1527,14 @@ __device__ __forceinline__ float deep_unit(const FrameArgs& a, const Unit& u, in
     if (tid < 8) *reinterpret_cast<uint4*>(rows + K * kDeepPitch + quad0) = make_uint4(Q::kNaN, Q::kNaN, Q::kNaN, Q::kNaN);
     lds_barrier();
     int jl = j;
+    const uint32_t flip = rank & 1 ? 0x80000000u : 0u;
     asm volatile("" : "+s"(K), "+v"(jl));
     typename RK::K key[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
+      if (r && r % 8 == 0) __builtin_amdgcn_sched_barrier(0);  // reads of 8 keys at a time: registers
       const int l = min(r * 16 + jl, K);
-      key[r] = Q::key(__float_as_uint(rows[l * kDeepPitch + px]), l);
+      key[r] = Q::key(__float_as_uint(rows[l * kDeepPitch + px]), l, px, flip);
     }
     lds_barrier();
     asm volatile("" : "+s"(K), "+v"(row0));
@@ -1518,6 +1544,7 @@ __device__ __forceinline__ float deep_unit(const FrameArgs& a, const Unit& u, in
       *reinterpret_cast<float4*>(rows + l * kDeepPitch + quad0) = Q::f(av[i]);
     }
     if (tid < 8) *reinterpret_cast<float4*>(rows + K * kDeepPitch + quad0) = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (EARLY && g0 + kDeepPx < p1) load_depth_alpha(g0 + kDeepPx + quad0 < P ? g0 + kDeepPx + quad0 : P - 4);
     // 2. sort
     __builtin_amdgcn_sched_barrier(0);
     row_sort<RK, R>(key, lane);
@@ -1527,32 +1554,33 @@ __device__ __forceinline__ float deep_unit(const FrameArgs& a, const Unit& u, in
     asm volatile("" : "+s"(K), "+v"(row0));
     const int p_me = g0 + px;
     if ((a.mode & kModeKeepOrder) && p_me < P) {
-      int i0 = j * R;
+      int i0 = rank * R;
       asm volatile("" : "+v"(i0));
 #pragma unroll
       for (int r = 0; r < R; ++r)
         if (i0 + r < K)
-          a.order[static_cast<size_t>(off + i0 + r) * P + p_me] = static_cast<uint16_t>(Q::index(key[r]));
+          a.order[static_cast<size_t>(off + i0 + r) * P + p_me] = static_cast<uint16_t>(Q::at(key[r], 0) / (kDeepPitch * 4));
     }
     int at[R];
     float al[R];
     float prod = 1.f;
+    char* column = reinterpret_cast<char*>(rows);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      at[r] = Q::index(key[r]) * kDeepPitch + px;
-      al[r] = rows[at[r]];
+      at[r] = Q::at(key[r], px * 4);
+      al[r] = *reinterpret_cast<float*>(column + at[r]);
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) prod *= 1.f - al[r];
-    float T = row_product_before(prod), A = 0.f;
+    float T = row_product_before<RK>(prod), A = 0.f;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      rows[at[r]] = T;
+      *reinterpret_cast<float*>(column + at[r]) = T;
       A = fmaf(T, al[r], A);
       T *= 1.f - al[r];
     }
     A = row_sum(A);
-    if (j == 15) {
+    if (rank == 15) {
       tend[px] = T;
       asum[px] = A;
     }
@@ -1565,15 +1593,7 @@ __device__ __forceinline__ float deep_unit(const FrameArgs& a, const Unit& u, in
       for (int v = 0; v < 4; ++v) acc[c][v] = 0.f;
 #pragma unroll
     for (int i0 = 0; i0 < NP; i0 += NC) {
-      V cv[NC][3];
-#pragma unroll
-      for (int i = 0; i < NC; ++i) {
-        asm volatile("" : "+s"(K));
-        const int l = row0 + (i0 + i) * kDeepRows;
-        const FT* __restrict__ b = frag + lofs[min(l, K - 1)];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) cv[i][c] = load_quad<FT>(b + c * plane, pq);
-      }
+      if constexpr (!EARLY) load_colours(i0, pq);
 #pragma unroll
       for (int i = 0; i < NC; ++i) {
         const int l = row0 + (i0 + i) * kDeepRows;
@@ -1630,9 +1650,10 @@ deep_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off, const int64_
   const bool wave0 = __builtin_amdgcn_readfirstlane(tid) < 64;  // uniform per wave
   FrameArgs a = args;
   use_frame_state(a, read_frame_state(a));
-  float* red = reinterpret_cast<float*>(lds);
-  int64_t* lofs = reinterpret_cast<int64_t*>(lds + kDeepTail);
-  float* rows = reinterpret_cast<float*>(lds + kDeepTail) + 2 * a.deep_layers;
+  // the rows first: their offset is a constant that the LDS instructions carry
+  float* rows = reinterpret_cast<float*>(lds);
+  int64_t* lofs = reinterpret_cast<int64_t*>(lds + deep_rows_bytes(a.deep_layers));
+  float* red = reinterpret_cast<float*>(lofs + a.deep_layers);
   const int home = static_cast<int>(blockIdx.x) % a.n_queues;
   Queue q = queue_of(a, home);
   uint64_t closed = 0;
@@ -1656,15 +1677,15 @@ deep_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off, const int64_
       lds_barrier();
       const int p0 = piece * a.deep_px, p1 = p0 + a.deep_px < a.P ? p0 + a.deep_px : a.P;
       float vs;
-      if (K <= 64) vs = deep_unit<FT, 4>(a, u, K, off, p0, p1, rows, lofs, red);
-      else if (K <= 96) vs = deep_unit<FT, 6>(a, u, K, off, p0, p1, rows, lofs, red);
-      else if (RMAX == 8 || K <= 128) vs = deep_unit<FT, 8>(a, u, K, off, p0, p1, rows, lofs, red);
+      if (K <= 64) vs = deep_unit<FT, 4, RMAX>(a, u, K, off, p0, p1, rows, lofs, red);
+      else if (K <= 96) vs = deep_unit<FT, 6, RMAX>(a, u, K, off, p0, p1, rows, lofs, red);
+      else if (RMAX == 8 || K <= 128) vs = deep_unit<FT, 8, RMAX>(a, u, K, off, p0, p1, rows, lofs, red);
       else if constexpr (RMAX >= 16) {
-        if (K <= 192) vs = deep_unit<FT, 12>(a, u, K, off, p0, p1, rows, lofs, red);
-        else if (RMAX == 16 || K <= 256) vs = deep_unit<FT, 16>(a, u, K, off, p0, p1, rows, lofs, red);
+        if (K <= 192) vs = deep_unit<FT, 12, RMAX>(a, u, K, off, p0, p1, rows, lofs, red);
+        else if (RMAX == 16 || K <= 256) vs = deep_unit<FT, 16, RMAX>(a, u, K, off, p0, p1, rows, lofs, red);
         else if constexpr (RMAX >= 32) {
-          if (K <= 384) vs = deep_unit<FT, 24>(a, u, K, off, p0, p1, rows, lofs, red);
-          else vs = deep_unit<FT, 32>(a, u, K, off, p0, p1, rows, lofs, red);
+          if (K <= 384) vs = deep_unit<FT, 24, RMAX>(a, u, K, off, p0, p1, rows, lofs, red);
+          else vs = deep_unit<FT, 32, RMAX>(a, u, K, off, p0, p1, rows, lofs, red);
         }
       }
       if ((a.mode & kModeAccumulate) && wave0) {

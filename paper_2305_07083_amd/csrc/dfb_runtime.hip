@@ -341,8 +341,10 @@ void drop_graphs(dfb_ctx* h);
 // Units of the row-sort launch: `px` consecutive pixels of a tile (whole
 // groups of kDeepPx), `subs` a tile.  A unit costs one ticket and loads its
 // tile's layer offsets, so larger is cheaper until the launch runs out of
-// units: 128 pixels, or one group where that leaves fewer than four units
-// to each workgroup the chip holds (about two per compute unit).
+// units: 128 pixels, or fewer where that leaves fewer than four units to each
+// workgroup the chip holds (about two per compute unit).  2144 units of 128
+// pixels for three workgroups a compute unit (1500x1100 fp16) took 108 us, 4288
+// of 64 112, 8576 of 32 123.
 struct DeepUnits {
   int px, subs;
 };

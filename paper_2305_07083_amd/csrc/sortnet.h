@@ -1,18 +1,42 @@
 // Compile-time sorting network over N keys held in registers.
 //
-// Bitonic sort in the form where every comparator puts the smaller key at the
-// lower index: a merge of two sorted halves first compares i with its mirror
-// (i ^ (size-1)), then half-cleans with distance stride.  Because every
-// comparator is min-to-lower, keys at positions >= N can be taken as +inf and
-// every comparator touching them dropped: the network sorts any N, not only
-// powers of two.  All loops have constant trip counts and unroll completely,
-// so the key array never leaves registers.
+// Batcher's merge exchange (Knuth, The Art of Computer Programming, vol. 3,
+// 5.2.2, algorithm M): it sorts any N, not only powers of two, with every
+// comparator putting the smaller key at the lower index, and takes a fifth to
+// a quarter fewer comparators than a bitonic network (8, 12, 16, 24, 32 keys:
+// 19, 41, 63, 127, 191 against 24, 54, 80, 168, 240).  The comparator list is a
+// constant and its loop unrolls completely, so the key array never leaves
+// registers.
 #pragma once
 #include <stdint.h>
 
 namespace dfb {
 
-constexpr int pow2_ceil(int n) { return n <= 1 ? 1 : 2 * pow2_ceil((n + 1) / 2); }
+// The comparators (a[c], b[c]), a[c] < b[c], of the network for N keys.
+template <int N>
+struct MergeExchange {
+  int n = 0;
+  int a[N * 10] = {}, b[N * 10] = {};
+  constexpr MergeExchange() {
+    int top = 1;
+    while (2 * top < N) top *= 2;
+    for (int p = N > 1 ? top : 0; p > 0; p /= 2) {
+      int q = top, r = 0, d = p;
+      for (;;) {
+        for (int i = 0; i + d < N; ++i)
+          if ((i & p) == r) {
+            a[n] = i;
+            b[n] = i + d;
+            ++n;
+          }
+        if (q == p) break;
+        d = q - p;
+        q /= 2;
+        r = p;
+      }
+    }
+  }
+};
 
 template <typename K>
 __host__ __device__ __forceinline__ void compare_exchange(K& a, K& b) {
@@ -31,19 +55,9 @@ struct CompareExchange {
 // The network with a given comparator ce(a, b): min to a, max to b.
 template <int N, typename K, typename CE>
 __host__ __device__ __forceinline__ void sort_network(K (&k)[N], CE ce) {
-  constexpr int NP = pow2_ceil(N);
+  constexpr MergeExchange<N> net;
 #pragma unroll
-  for (int size = 2; size <= NP; size <<= 1) {
-#pragma unroll
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-#pragma unroll
-      for (int c = 0; c < NP / 2; ++c) {
-        const int lo = (c / stride) * (2 * stride) + (c % stride);
-        const int hi = (stride == (size >> 1)) ? (lo ^ (size - 1)) : (lo + stride);
-        if (hi < N) ce(k[lo], k[hi]);
-      }
-    }
-  }
+  for (int c = 0; c < net.n; ++c) ce(k[net.a[c]], k[net.b[c]]);
 }
 
 template <int N, typename K>
