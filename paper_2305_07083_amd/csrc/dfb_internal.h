@@ -188,6 +188,8 @@ const void* tile_variance_kernel();
 const void* state_kernel();
 // (uint32_t* p, uint32_t v, int64_t n): p[0..n) = v, any grid.
 const void* fill_u32_kernel();
+// (const uint32_t* src, uint32_t* dst, int64_t n): dst[0..n) = src[0..n), any grid.
+const void* copy_u32_kernel();
 // (const int32_t* tile_off, int32_t n_tiles, int32_t subs, int32_t* work):
 // the longest-first work list, one workgroup of kLptThreads lanes.
 const void* lpt_work_kernel();

@@ -1772,6 +1772,13 @@ __global__ void fill_u32_kernel_t(uint32_t* __restrict__ p, uint32_t v, int64_t 
     p[i] = v;
 }
 
+// n words copied (grid-stride); src may be pinned host memory.
+__global__ void copy_u32_kernel_t(const uint32_t* __restrict__ src, uint32_t* __restrict__ dst, int64_t n) {
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
+       i += static_cast<int64_t>(gridDim.x) * blockDim.x)
+    dst[i] = src[i];
+}
+
 // Longest-first work list on the device, from the per-tile CSR offsets:
 // a counting sort of the tiles by layer count, descending (one workgroup of
 // kLptThreads lanes; equal counts in any order, which changes only the
@@ -1888,6 +1895,8 @@ const void* tile_variance_kernel() { return reinterpret_cast<const void*>(&tile_
 const void* state_kernel() { return reinterpret_cast<const void*>(&state_kernel_t); }
 
 const void* fill_u32_kernel() { return reinterpret_cast<const void*>(&fill_u32_kernel_t); }
+
+const void* copy_u32_kernel() { return reinterpret_cast<const void*>(&copy_u32_kernel_t); }
 
 const void* lpt_work_kernel() { return reinterpret_cast<const void*>(&lpt_work_kernel_t); }
 

@@ -80,29 +80,21 @@ struct dfb_ctx {
   std::vector<dfb_layer> last_layers;
   std::vector<int32_t> last_expected;
   bool last_had_expected = false;
-  // Two sets of device layer tables (per-tile offsets, layer offsets, work
-  // list), used by successive layer layouts in turn, each uploaded from
-  // pinned host staging: a new layout is written to the set the frames in
-  // flight do not read, so its upload needs no wait for them.  A set is
-  // reused two layouts later, after the event recorded when the frames
-  // stopped using it.
+  std::vector<int64_t> h_block;  // layer offsets, as on the device
+  // Two sets of device layer tables (layer offsets, per-tile offsets, work
+  // list, in one allocation), used by successive layer layouts in turn, each
+  // uploaded from pinned host staging with one copy: a new layout is written to
+  // the set the frames in flight do not read, so its upload needs no wait for
+  // them.  A set, and its staging, is reused two layouts later, after the event
+  // recorded when the frames stopped using it.
   struct Tables {
-    int32_t* off = nullptr;
-    size_t off_cap = 0;
-    int64_t* block = nullptr;
-    size_t block_cap = 0;
-    int32_t* work = nullptr;
-    size_t work_cap = 0;
-    int32_t* st_off = nullptr;   // pinned staging
-    size_t st_off_cap = 0;
-    int64_t* st_block = nullptr;
-    size_t st_block_cap = 0;
-    int32_t* st_work = nullptr;
-    size_t st_work_cap = 0;
+    char* dev = nullptr;
+    size_t cap = 0;
+    char* st = nullptr;            // pinned staging
+    size_t st_cap = 0;
+    bool staged = false;           // an upload may still read the staging
     hipEvent_t released = nullptr;  // the frames that read this set are done
-    hipEvent_t staged[3] = {};      // uploads from st_off / st_block / st_work are done
     bool released_pending = false;
-    bool staged_pending[3] = {};
   } tables[2];
   int cur_tables = 0;
   int32_t* d_off = nullptr;    // the current set's arrays
@@ -368,69 +360,69 @@ bool has_deep(const dfb_ctx* h) {
 }
 DeepUnits deep_units(const dfb_ctx* h) { return deep_units(h->P, h->n_deep, h->n_cu); }
 
-// Device array of a table set, grown when too small.  Only called on a set
+// Uploads the current layout's layer and tile offsets, and n_work work-list
+// entries that `fill` writes, to a table set, stream-ordered and in one copy
+// (three, with an event each: 68 us a 1024x1024 frame, 51 now).  Only called on a set
 // no frame in flight reads (the other set's, or during the autotuner's
 // synchronous sweep).
-template <typename T>
-dfb_status ensure_device_table(dfb_ctx* h, T*& ptr, size_t& cap, size_t count) {
-  if (count <= cap && ptr) return DFB_OK;
-  if (ptr) DFB_HIP(h, hipFree(ptr));
-  ptr = nullptr;
-  cap = 0;
-  const size_t n = std::max<size_t>(count, 1);
-  if (hipMalloc(reinterpret_cast<void**>(&ptr), n * sizeof(T)) != hipSuccess) {
-    (void)hipGetLastError();
-    ptr = nullptr;
-    return fail(h, DFB_ERR_OOM, "device allocation of " + std::to_string(n * sizeof(T)) + " bytes failed");
+template <class Fill>
+dfb_status upload_tables(dfb_ctx* h, dfb_ctx::Tables& S, const std::vector<int32_t>& off, size_t n_work, Fill fill) {
+  const size_t block_bytes = h->h_block.size() * sizeof(int64_t), off_bytes = off.size() * sizeof(int32_t);
+  const size_t bytes = block_bytes + off_bytes + n_work * sizeof(int32_t);
+  if (S.staged) {  // staged twice in a row: the autotuner
+    DFB_HIP(h, hipStreamSynchronize(h->stream));
+    S.staged = false;
   }
-  cap = n;
-  return DFB_OK;
-}
-
-// Pinned staging buffer `which` of a set, ready to be written: waits for the
-// last upload from it, grows it when too small.
-template <typename T>
-dfb_status stage(dfb_ctx* h, dfb_ctx::Tables& S, int which, T*& ptr, size_t& cap, size_t count) {
-  if (S.staged_pending[which]) {
-    DFB_HIP(h, hipEventSynchronize(S.staged[which]));
-    S.staged_pending[which] = false;
+  if (bytes > S.cap) {
+    if (S.dev) DFB_HIP(h, hipFree(S.dev));
+    S.dev = nullptr;
+    S.cap = 0;
+    const size_t cap = bytes + bytes / 2;  // layouts of a moving camera vary in size
+    if (hipMalloc(reinterpret_cast<void**>(&S.dev), cap) != hipSuccess) {
+      (void)hipGetLastError();
+      S.dev = nullptr;
+      return fail(h, DFB_ERR_OOM, "device allocation of " + std::to_string(cap) + " bytes failed");
+    }
+    S.cap = cap;
   }
-  if (count <= cap && ptr) return DFB_OK;
-  if (ptr) DFB_HIP(h, hipHostFree(ptr));
-  ptr = nullptr;
-  cap = 0;
-  const size_t n = std::max<size_t>(count, 1);
-  if (hipHostMalloc(reinterpret_cast<void**>(&ptr), n * sizeof(T), hipHostMallocDefault) != hipSuccess) {
-    (void)hipGetLastError();
-    ptr = nullptr;
-    return fail(h, DFB_ERR_OOM, "pinned host allocation of " + std::to_string(n * sizeof(T)) + " bytes failed");
+  if (bytes > S.st_cap) {
+    if (S.st) DFB_HIP(h, hipHostFree(S.st));
+    S.st = nullptr;
+    S.st_cap = 0;
+    const size_t cap = bytes + bytes / 2;
+    if (hipHostMalloc(reinterpret_cast<void**>(&S.st), cap, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      S.st = nullptr;
+      return fail(h, DFB_ERR_OOM, "pinned host allocation of " + std::to_string(cap) + " bytes failed");
+    }
+    S.st_cap = cap;
   }
-  cap = n;
-  return DFB_OK;
-}
-
-// Stream-ordered upload of a staged array; the staging is free again once
-// the recorded event has passed.
-template <typename T>
-dfb_status upload(dfb_ctx* h, dfb_ctx::Tables& S, int which, T* dev, const T* staging, size_t count) {
-  if (count) DFB_HIP(h, hipMemcpyAsync(dev, staging, count * sizeof(T), hipMemcpyHostToDevice, h->stream));
-  if (!S.staged[which]) DFB_HIP(h, hipEventCreateWithFlags(&S.staged[which], hipEventDisableTiming));
-  DFB_HIP(h, hipEventRecord(S.staged[which], h->stream));
-  S.staged_pending[which] = true;
+  if (block_bytes) std::memcpy(S.st, h->h_block.data(), block_bytes);
+  std::memcpy(S.st + block_bytes, off.data(), off_bytes);
+  fill(reinterpret_cast<int32_t*>(S.st + block_bytes + off_bytes));
+  // by a kernel that reads the staging over the bus: the runtime gives a copy
+  // of more than a few pages to a DMA engine, and the frame kernel then starts
+  // 18 us later (1024x1024, every frame a new layout: 60 us a frame, 51 by the
+  // kernel)
+  const void* src = nullptr;
+  DFB_HIP(h, hipHostGetDevicePointer(const_cast<void**>(&src), S.st, 0));
+  char* dst = S.dev;
+  int64_t words = static_cast<int64_t>((bytes + 3) / 4);
+  void* params[] = {&src, &dst, &words};
+  DFB_HIP(h, hipLaunchKernel(dfb::copy_u32_kernel(), dim3(static_cast<unsigned>(std::min<int64_t>((words + 255) / 256, 1024))),
+                             dim3(256), params, 0, h->stream));
+  S.staged = true;
+  h->d_block = reinterpret_cast<int64_t*>(S.dev);
+  h->d_off = reinterpret_cast<int32_t*>(S.dev + block_bytes);
+  h->d_work = reinterpret_cast<int32_t*>(S.dev + block_bytes + off_bytes);
   return DFB_OK;
 }
 
 void free_tables(dfb_ctx* h) {
   for (auto& S : h->tables) {
-    if (S.off) (void)hipFree(S.off);
-    if (S.block) (void)hipFree(S.block);
-    if (S.work) (void)hipFree(S.work);
-    if (S.st_off) (void)hipHostFree(S.st_off);
-    if (S.st_block) (void)hipHostFree(S.st_block);
-    if (S.st_work) (void)hipHostFree(S.st_work);
+    if (S.dev) (void)hipFree(S.dev);
+    if (S.st) (void)hipHostFree(S.st);
     if (S.released) (void)hipEventDestroy(S.released);
-    for (auto& e : S.staged)
-      if (e) (void)hipEventDestroy(e);
     S = dfb_ctx::Tables{};
   }
 }
@@ -443,25 +435,25 @@ dfb_status build_work(dfb_ctx* h, const Shape& s) {
   h->subs_x = sx;
   h->subs_per_tile = sx * sy;
   h->n_work = h->n_tiles * h->subs_per_tile;
-  std::vector<int32_t> tiles(h->n_tiles);
-  for (int t = 0; t < h->n_tiles; ++t) tiles[t] = t;
-  std::stable_sort(tiles.begin(), tiles.end(), [&](int a, int b) {
-    return (h->h_off[a + 1] - h->h_off[a]) > (h->h_off[b + 1] - h->h_off[b]);
-  });
-  dfb_ctx::Tables& T = h->tables[h->cur_tables];
   const size_t n = static_cast<size_t>(h->n_work);
-  dfb_status st = ensure_device_table(h, T.work, T.work_cap, n);
+  dfb_status st = ensure(h, h->d_var_partial, h->partial_cap, n + static_cast<size_t>(h->n_tiles) * (h->n_deep ? deep_units(h).subs : 0));
   if (st != DFB_OK) return st;
-  st = ensure(h, h->d_var_partial, h->partial_cap, n + static_cast<size_t>(h->n_tiles) * (h->n_deep ? deep_units(h).subs : 0));
+  st = upload_tables(h, h->tables[h->cur_tables], h->h_off, n, [&](int32_t* work) {
+    // counting sort by layers: at[K] is the next list position of a tile of K
+    std::vector<int32_t> at(h->max_k + 2, 0);
+    for (int t = 0; t < h->n_tiles; ++t) ++at[h->h_off[t + 1] - h->h_off[t]];
+    int32_t pos = 0;
+    for (int k = h->max_k; k >= 0; --k) {
+      const int32_t c = at[k];
+      at[k] = pos;
+      pos += c;
+    }
+    for (int t = 0; t < h->n_tiles; ++t) {
+      int32_t* w = work + static_cast<size_t>(at[h->h_off[t + 1] - h->h_off[t]]++) * h->subs_per_tile;
+      for (int u = 0; u < h->subs_per_tile; ++u) w[u] = t * h->subs_per_tile + u;
+    }
+  });
   if (st != DFB_OK) return st;
-  st = stage(h, T, 2, T.st_work, T.st_work_cap, n);
-  if (st != DFB_OK) return st;
-  size_t k = 0;
-  for (int t : tiles)
-    for (int u = 0; u < h->subs_per_tile; ++u) T.st_work[k++] = t * h->subs_per_tile + u;
-  st = upload(h, T, 2, T.work, T.st_work, n);
-  if (st != DFB_OK) return st;
-  h->d_work = T.work;
   h->work_valid = true;
   return DFB_OK;
 }
@@ -1120,23 +1112,18 @@ dfb_status dfb_set_fragments(dfb_handle h, const void* frag_dev, int64_t n_block
   }
   // Upload into the table set that no frame in flight reads (no wait for
   // the frames of the current layout).
-  const bool first = !h->tables[h->cur_tables].off;
+  const bool first = !h->tables[h->cur_tables].dev;
   const int nxt = first ? h->cur_tables : 1 - h->cur_tables;
   dfb_ctx::Tables& T = h->tables[nxt];
   if (T.released_pending) {  // frames of the layout before last: normally long done
     DFB_HIP(h, hipEventSynchronize(T.released));
     T.released_pending = false;
+    T.staged = false;
   }
-  if ((s = ensure_device_table(h, T.off, T.off_cap, off.size())) != DFB_OK) return s;
-  if ((s = ensure_device_table(h, T.block, T.block_cap, block.size())) != DFB_OK) return s;
-  if ((s = stage(h, T, 0, T.st_off, T.st_off_cap, off.size())) != DFB_OK) return s;
-  if ((s = stage(h, T, 1, T.st_block, T.st_block_cap, block.size())) != DFB_OK) return s;
-  std::copy(off.begin(), off.end(), T.st_off);
-  std::copy(block.begin(), block.end(), T.st_block);
-  if ((s = upload(h, T, 0, T.off, T.st_off, off.size())) != DFB_OK) return s;
-  if ((s = upload(h, T, 1, T.block, T.st_block, block.size())) != DFB_OK) return s;
   if (h->cfg.flags & DFB_VALIDATE) {
-    s = scan_nan(h, frag_dev, T.block, n_layers);
+    h->h_block = block;
+    s = upload_tables(h, T, off, 0, [](int32_t*) {});
+    if (s == DFB_OK) s = scan_nan(h, frag_dev, h->d_block, n_layers);
     if (s != DFB_OK) {  // the frame is refused: set_fragments must come again before a composite
       h->state = State::kEmpty;
       h->n_layers = -1;
@@ -1157,13 +1144,11 @@ dfb_status dfb_set_fragments(dfb_handle h, const void* frag_dev, int64_t n_block
     O.released_pending = true;
   }
   h->cur_tables = nxt;
-  h->d_off = T.off;
-  h->d_block = T.block;
-  h->d_work = T.work;
   // a new launch shape only for a new layer-count class
   if (h->state == State::kEmpty || kcap_for(max_k) != h->kcap || layer_class(max_k) != layer_class(h->max_k))
     h->shape_valid = false;
   h->h_off.swap(off);
+  h->h_block.swap(block);
   h->n_layers = n_layers;
   h->n_blocks = n_blocks;
   h->max_k = max_k;

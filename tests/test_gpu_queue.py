@@ -62,3 +62,35 @@ def test_every_unit_once(dfb, n_tiles, tile, work, waves, op):
             dfb.dfb_composite_noalloc(cfg, frag, off, layer_off, kmax, out, stream=stream_handle())
         torch.cuda.synchronize()
         assert np.array_equal(out.cpu().numpy(), first)
+
+
+def test_layouts_of_changing_size(dfb):
+    """Every frame a layout of another size, with no synchronisation between:
+    the two table sets and their staging grow and are reused while earlier
+    frames may still be in flight.  The last frame of each size against the
+    oracle, bit-identical to the same layout on its own."""
+    torch = torch_dev()
+    rng = np.random.default_rng(5)
+    frames = []
+    for k in range(7):
+        counts = rng.integers(0, 3 + 9 * (k % 4), 96).astype(np.int32)
+        f = workloads.generation_frame(32 * 12, 32 * 8, 32, counts, 50 + k, depth_by_generation=False)
+        frames.append((f, upload(f.frag)))
+    cfg = dfb.make_config(frames[0][0].width, frames[0][0].height, 32, work=32, waves=4, fmt=dfb.DFB_FMT_RGBAF32)
+    alone = []
+    for f, frag in frames:
+        with dfb.Compositor(cfg, stream_handle()) as c:
+            c.set_fragments(frag, f.frag.shape[0], f.layers, f.expected)
+            c.composite()
+            alone.append(c.read(dfb.DFB_BUF_FINAL))
+        ref = oracle.composite(f.frag, f.layers, f.width, f.height, 32, 32, expected=f.expected, want_mag=True)
+        assert_colour(alone[-1], ref["rgba"], ref["mag"], f.name)
+    with dfb.Compositor(cfg, stream_handle()) as c:
+        out = [torch.empty((f.n_tiles, f.P, 4), dtype=torch.float32, device="cuda:0") for f, _ in frames * 3]
+        for o, (f, frag) in zip(out, frames * 3):
+            c.set_fragments(frag, f.frag.shape[0], f.layers, f.expected)
+            c.composite()
+            dfb.dfb_read_tiles(c.h, dfb.DFB_BUF_FINAL, 0, f.n_tiles, o, True)
+        dfb.dfb_synchronize(c.h)
+        for o, a in zip(out, alone * 3):
+            assert np.array_equal(o.cpu().numpy().reshape(a.shape), a)
