@@ -29,9 +29,12 @@ struct Shape {
 // also pool = bf16(2x2 average of y) at s/2.  With `x2`, the input is the
 // channel concatenation of x and x2 (x.c a multiple of 32, x2.ld == x.ld):
 // two maps that are each written with full 64- or 128-byte pixel rows.
+// `tickets`: kTicketWords words, zero between launches (each leaves them so),
+// for launches of one stream at a time.
+constexpr int kTicketWords = 8 * 32;
 hipError_t conv3x3_fwd(const Map& x, const uint16_t* w_fwd, const float* bias, const Map& y,
-                       const Shape& s, hipStream_t st, bool up = false, const Map* pool = nullptr,
-                       const Map* x2 = nullptr);
+                       const Shape& s, uint32_t* tickets, hipStream_t st, bool up = false,
+                       const Map* pool = nullptr, const Map* x2 = nullptr);
 // The data gradient of a conv3x3 (ci input channels, a multiple of 32; g its
 // gated output gradient at shape s), carried through to the gated output
 // gradient o.g of the layer that made its input: g' = bf16(dx' * (y > 0)), y
@@ -141,7 +144,7 @@ hipError_t conv3x3_in_frame(const FrameGlue& g, const uint16_t* w_fwd, const flo
 // when mode has a format.
 hipError_t conv3x3_out_frame(const Map& x, const uint16_t* w_fwd, const float* bias, const float* ow, const float* ob,
                              const FrameGlue& g, float tau, float* den, void* final_out, uint32_t mode,
-                             float inv_gamma, const Shape& s, hipStream_t st);
+                             float inv_gamma, const Shape& s, uint32_t* tickets, hipStream_t st);
 
 }  // namespace unet
 }  // namespace dfb

@@ -35,9 +35,9 @@ __device__ __forceinline__ uint16_t to_bf16(float f) {  // round to nearest even
 __device__ __forceinline__ float from_bf16(uint16_t h) { return __uint_as_float(static_cast<uint32_t>(h) << 16); }
 
 // ------------------------------------------------------------- forward
-// Persistent implicit-GEMM conv3x3 forward.  A workgroup computes a
-// contiguous range of the TH x 32-pixel output tiles (each XCD one band of
-// them) for all BN output channels; a tile is CP/32 steps, one per
+// Persistent implicit-GEMM conv3x3 forward.  A workgroup computes TH x
+// 32-pixel output tiles (each XCD has one band of them, handed out in order)
+// for all BN output channels; a tile is CP/32 steps, one per
 // 32-input-channel slice.  A step stages the slice's input halo ((TH+2) x 34
 // pixels, zero outside the image; with UP the (TH/2+2) x 18 source pixels the
 // up-sampled halo reads) and, unless all slices' weights stay resident, the
@@ -73,6 +73,7 @@ __device__ __forceinline__ float from_bf16(uint16_t h) { return __uint_as_float(
 constexpr int kTW = 32;  // tile width (pixels)
 constexpr int kXcds = 8;  // XCDs (each with its own L2) the workgroups of a launch are dealt to in turn
 constexpr int kKC = 32;  // input channels per step
+constexpr int kTicketStride = kTicketWords / kXcds;  // a counter of its own line for each XCD
 // Output-tile heights (rows of 32 pixels, 8 or 16) of the layers with
 // (output, input) channels (32, 32), (32, 64), (64, 32), (64, 64), (64, 128)
 // and (128, *).  16 rows (8 waves) for the 64-channel layers: a staged
@@ -221,7 +222,8 @@ template <int BN, int CP, int TH, bool UP, int EPI>
 __global__ void __launch_bounds__((ConvCfg<BN, TH, CP / kKC, UP>::NT))
 __attribute__((amdgpu_waves_per_eu(ConvCfg<BN, TH, CP / kKC, UP>::WAVES)))
 conv_fwd_k(Map x, Map x2, const uint16_t* __restrict__ w, const float* __restrict__ bias, Map y, Map pool, OutConv oc,
-           Shape s) {
+           Shape s, uint32_t* __restrict__ tickets) {
+  __shared__ int s_next;
   using C = ConvCfg<BN, TH, CP / kKC, UP>;
   constexpr bool POOL = EPI == kEpiPool, OUT = EPI == kEpiFrame;
   constexpr int STORE_POLICY = (BN == 32 && CP == 64) || (BN == 64 && CP == 128) ? kNT : 0;
@@ -243,18 +245,23 @@ conv_fwd_k(Map x, Map x2, const uint16_t* __restrict__ w, const float* __restric
   const int rw = C::CS > 1 ? wave % (TH / 2) : wave, cb0 = C::CS > 1 ? (wave / (TH / 2)) * NB * 32 : 0;
   const int tiles_x = (s.w + kTW - 1) / kTW, tiles_y = (s.h + TH - 1) / TH;
   const long long tiles = static_cast<long long>(s.n) * tiles_x * tiles_y;
-  // workgroup b walks the tiles [b T / G, (b + 1) T / G) in row order (the
-  // host launches G <= T workgroups, so each has at least one), sharing the
-  // halo columns of consecutive tiles through its L2.  b is the workgroup's
-  // rank on its XCD (the hardware deals workgroups to the 8 XCDs in turn)
-  // after those of the XCDs before it, so each XCD walks one contiguous
-  // band of tiles and the workgroups working on vertically adjacent tiles
-  // at the same time share their halo rows through the same L2.
+  // The hardware deals workgroups to the 8 XCDs in turn.  XCD x, with n_x of
+  // the G workgroups, has one contiguous band of tiles in row order, so the
+  // workgroups on neighbouring tiles share their halos through one L2.  In
+  // the band, workgroup xr takes tiles xr and n_x + xr, then the tiles its
+  // tickets give: workgroups of a compute unit do not advance alike (the
+  // oldest is served first: with equal shares of tiles, up1 of a 2048^2 frame
+  // ended after 85 to 153 us in its 768 workgroups), and those ahead take
+  // more (up1 128 -> 123 us; 8x256x512 forward 409 -> 399).  What bounds the
+  // layers with 64 and more channels is the matrix cores at the clock they
+  // sustain: without any load or store up1 takes 112 us; fragments read two or
+  // three steps ahead, or fewer of them, change nothing.
   const long long G = gridDim.x;
   const int xcd = static_cast<int>(blockIdx.x % kXcds), xr = static_cast<int>(blockIdx.x / kXcds);
-  const long long b0 = xcd * (G / kXcds) + (xcd < G % kXcds ? xcd : G % kXcds) + xr;
-  const long long t_begin = b0 * tiles / G, t_end = (b0 + 1) * tiles / G;
-  const int nsteps = static_cast<int>(t_end - t_begin) * NCH;
+  const int n_x = static_cast<int>(G / kXcds) + (xcd < G % kXcds);
+  const long long b0 = xcd * (G / kXcds) + (xcd < G % kXcds ? xcd : G % kXcds);
+  const int t_first = static_cast<int>(b0 * tiles / G), band = static_cast<int>((b0 + n_x) * tiles / G) - t_first;
+  const bool ticketed = band > 2 * n_x;  // uniform
   const int hi = UP ? s.h / 2 : s.h, wi = UP ? s.w / 2 : s.w;  // the map x is read from
   // The input is the channel concatenation of x and x2 (x2.c may be 0; else
   // x.c is a multiple of 32 and x2.ld == x.ld): slices below x.c read x, the
@@ -264,23 +271,14 @@ conv_fwd_k(Map x, Map x2, const uint16_t* __restrict__ w, const float* __restric
   struct Tile {
     int n, ty, tx;
   };
-  auto decode = [&](long long t) {
+  auto decode = [&](int i) {  // tile i of the band
     Tile u;
-    const long long per_img = static_cast<long long>(tiles_x) * tiles_y;
-    u.n = static_cast<int>(t / per_img);
-    const int r = static_cast<int>(t - u.n * per_img);
+    const int t = t_first + i, per_img = tiles_x * tiles_y;
+    u.n = t / per_img;
+    const int r = t - u.n * per_img;
     u.ty = r / tiles_x;
     u.tx = r - u.ty * tiles_x;
     return u;
-  };
-  auto advance = [&](Tile& u) {
-    if (++u.tx == tiles_x) {
-      u.tx = 0;
-      if (++u.ty == tiles_y) {
-        u.ty = 0;
-        ++u.n;
-      }
-    }
   };
 
   // this thread's halo elements e = tid + NT k: halo pixel e / 4 (row, column),
@@ -504,7 +502,8 @@ conv_fwd_k(Map x, Map x2, const uint16_t* __restrict__ w, const float* __restric
   };
   if (tid < BN) lbias[tid] = bias[tid];
   if (OUT && tid < 99) lout[tid] = tid < 96 ? oc.w[tid] : oc.b[tid - 96];
-  Tile cur = decode(t_begin), nxt = cur;  // the tile computed, the tile prefetched
+  int i_nxt = xr + n_x;              // the next tile; from band on: none
+  Tile cur = decode(xr), nxt = cur;  // the tile computed, the tile prefetched (G <= tiles: band >= n_x)
   constexpr bool RESW = C::WS == NCH;  // every slice's weights stay in LDS for every tile
   if (RESW) {
 #pragma unroll
@@ -523,8 +522,9 @@ conv_fwd_k(Map x, Map x2, const uint16_t* __restrict__ w, const float* __restric
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[m][j][r] = 0.f;
   epilogue(cur, true);
-  const int my_tiles = nsteps / NCH;
-  for (int it = 0; it < my_tiles; ++it) {
+  for (;;) {
+    const bool last = i_nxt >= band;
+    uint32_t ticket = 0;
 #pragma unroll
     for (int ck = 0; ck < NCH; ++ck) {
       __syncthreads();  // the previous step's fragment reads are done
@@ -538,9 +538,13 @@ conv_fwd_k(Map x, Map x2, const uint16_t* __restrict__ w, const float* __restric
         ecur = ereg;
       }
       __syncthreads();
+      // the tile after the next, asked for ahead of the loads that are waited
+      // for before it is needed
+      if (ck == 0 && ticketed && !last && tid == 0)
+        ticket = __hip_atomic_fetch_add(tickets + xcd * kTicketStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       // prefetch the next step: the next slice, or slice 0 of the next tile
-      const bool none = ck == NCH - 1 && it + 1 == my_tiles;
-      if (ck == NCH - 1 && !none) advance(nxt);
+      const bool none = ck == NCH - 1 && last;
+      if (ck == NCH - 1 && !none) nxt = decode(i_nxt);
       load_halo(nxt, (ck + 1) % NCH, none, hreg);
       if (!RESW) load_w((ck + 1) % NCH, none, wreg);
       if (ck == NCH - 1) load_base(nxt, none);
@@ -584,8 +588,17 @@ conv_fwd_k(Map x, Map x2, const uint16_t* __restrict__ w, const float* __restric
             acc[m][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[i & 1][j], hf[i & 1][m], acc[m][j], 0, 0, 0);
       }
     }
-    epilogue(cur, false);
+    if (ticketed && !last && tid == 0) {
+      s_next = 2 * n_x + static_cast<int>(ticket);
+      // each workgroup draws one ticket too many; the last of those leaves
+      // the counter at zero for the next launch
+      if (ticket == static_cast<uint32_t>(band - n_x - 1))
+        __hip_atomic_store(tickets + xcd * kTicketStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    epilogue(cur, false);  // with barriers between the write of s_next and its read
+    if (last) break;
     cur = nxt;
+    i_nxt = ticketed ? __builtin_amdgcn_readfirstlane(s_next) : band;
   }
 }
 
@@ -1511,7 +1524,7 @@ inline unsigned blocks(long long n, int t) { return static_cast<unsigned>((n + t
 
 template <int BN, int CP, int TH, bool UP, int EPI>
 hipError_t launch_conv(const Map& x, const Map& x2, const uint16_t* w, const float* bias, const Map& y, const Map& pool,
-                       const OutConv& oc, const Shape& s, hipStream_t st) {
+                       const OutConv& oc, const Shape& s, uint32_t* tickets, hipStream_t st) {
   using C = ConvCfg<BN, TH, CP / kKC, UP>;
   const void* f = reinterpret_cast<const void*>(&conv_fwd_k<BN, CP, TH, UP, EPI>);
   const size_t lds = C::BYTES + (EPI == kEpiFrame ? 99 * 4 : 0);
@@ -1537,19 +1550,19 @@ hipError_t launch_conv(const Map& x, const Map& x2, const uint16_t* w, const flo
   e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
   const long long grid = tiles < static_cast<long long>(cus) * per_cu[dev] ? tiles : static_cast<long long>(cus) * per_cu[dev];
-  conv_fwd_k<BN, CP, TH, UP, EPI><<<static_cast<unsigned>(grid), C::NT, lds, st>>>(x, x2, w, bias, y, pool, oc, s);
+  conv_fwd_k<BN, CP, TH, UP, EPI><<<static_cast<unsigned>(grid), C::NT, lds, st>>>(x, x2, w, bias, y, pool, oc, s, tickets);
   return hipGetLastError();
 }
 
 template <int BN, int CP, int TH, bool UP>
 hipError_t launch_tile(const Map& x, const Map& x2, const uint16_t* w, const float* bias, const Map& y,
-                       const Map& pool, const Shape& s, hipStream_t st) {
+                       const Map& pool, const Shape& s, uint32_t* tickets, hipStream_t st) {
   const OutConv none{nullptr, nullptr, FrameGlue{}, 0.f, nullptr};
   if (pool.p) {
-    if constexpr ((TH / 4) % 2 == 0) return launch_conv<BN, CP, TH, UP, kEpiPool>(x, x2, w, bias, y, pool, none, s, st);
+    if constexpr ((TH / 4) % 2 == 0) return launch_conv<BN, CP, TH, UP, kEpiPool>(x, x2, w, bias, y, pool, none, s, tickets, st);
     return hipErrorInvalidValue;
   }
-  return launch_conv<BN, CP, TH, UP, kEpiPlain>(x, x2, w, bias, y, pool, none, s, st);
+  return launch_conv<BN, CP, TH, UP, kEpiPlain>(x, x2, w, bias, y, pool, none, s, tickets, st);
 }
 
 // Rows of a one-tile convolution's tiles: 8, or 4 where 8 leave fewer than two
@@ -1607,14 +1620,14 @@ hipError_t tile_fwd(const Map& x, const Map& x2, const uint16_t* w, const float*
 
 template <bool UP>
 hipError_t conv_tile(const Map& x, const Map& x2, const uint16_t* w, const float* bias, const Map& y,
-                     const Map& pool, const Shape& s, hipStream_t st) {
+                     const Map& pool, const Shape& s, uint32_t* tickets, hipStream_t st) {
   const int cp = (x.c + x2.c + 31) / 32 * 32;
 #define DFB_CONV(BN_, CP_, TH_, THU_)                                                                               \
   if (y.c == BN_ && cp == CP_) {                                                                                    \
     constexpr int TH = UP ? THU_ : TH_;                                                                             \
     if (cp == x.c + x2.c && static_cast<long long>(s.n) * ((s.h + TH - 1) / TH) * ((s.w + kTW - 1) / kTW) < kPersistMin) \
       return tile_fwd<UP, CP_>(x, x2, w, bias, y, pool, s, st);                                                     \
-    return launch_tile<BN_, CP_, TH, UP>(x, x2, w, bias, y, pool, s, st);                                           \
+    return launch_tile<BN_, CP_, TH, UP>(x, x2, w, bias, y, pool, s, tickets, st);                                  \
   }
   DFB_CONV(32, 32, DFB_TH_32_32, DFB_TH_32_32)
   DFB_CONV(32, 64, DFB_TH_32_64, DFB_THU_32_64)
@@ -1628,7 +1641,7 @@ hipError_t conv_tile(const Map& x, const Map& x2, const uint16_t* w, const float
 }
 
 hipError_t conv3x3_fwd(const Map& x, const uint16_t* w_fwd, const float* bias, const Map& y, const Shape& s,
-                       hipStream_t st, bool up, const Map* pool, const Map* x2) {
+                       uint32_t* tickets, hipStream_t st, bool up, const Map* pool, const Map* x2) {
   const Map none{nullptr, 0, 0, 0};
   const Map& xb = x2 ? *x2 : none;
   if (x.c % 8 || x.ld % 8 || x.off % 8 || y.ld % 8 || y.off % 8) return hipErrorInvalidValue;
@@ -1639,7 +1652,8 @@ hipError_t conv3x3_fwd(const Map& x, const uint16_t* w_fwd, const float* bias, c
   if (img >= (1LL << 30) || static_cast<long long>(s.h) * s.w * y.ld >= (1LL << 30)) return hipErrorInvalidValue;
   const Map& pl = pool ? *pool : none;
   if (pool && (pl.ld % 8 || pl.off % 8 || pl.c != y.c)) return hipErrorInvalidValue;
-  return up ? conv_tile<true>(x, xb, w_fwd, bias, y, pl, s, st) : conv_tile<false>(x, xb, w_fwd, bias, y, pl, s, st);
+  return up ? conv_tile<true>(x, xb, w_fwd, bias, y, pl, s, tickets, st)
+            : conv_tile<false>(x, xb, w_fwd, bias, y, pl, s, tickets, st);
 }
 
 // The data gradient from `in` channels to ci.
@@ -1739,7 +1753,7 @@ hipError_t conv3x3_in_frame(const FrameGlue& g, const uint16_t* w_fwd, const flo
 
 hipError_t conv3x3_out_frame(const Map& x, const uint16_t* w_fwd, const float* bias, const float* ow, const float* ob,
                              const FrameGlue& g, float tau, float* den, void* final_out, uint32_t mode,
-                             float inv_gamma, const Shape& s, hipStream_t st) {
+                             float inv_gamma, const Shape& s, uint32_t* tickets, hipStream_t st) {
   if (x.c != 32 || x.ld % 8 || x.off % 8 || !den || s.n != 1 || s.h != g.height || s.w != g.width)
     return hipErrorInvalidValue;
   if ((mode & (kModeFmtRGBA8 | kModeFmtF32)) && !final_out) return hipErrorInvalidValue;
@@ -1749,7 +1763,7 @@ hipError_t conv3x3_out_frame(const Map& x, const uint16_t* w_fwd, const float* b
   const Map none{nullptr, 0, 0, 0};
   const OutConv oc{ow, ob, g, tau, den};
   const Map y{nullptr, 32, 0, 32};
-  hipError_t e = launch_conv<32, 32, DFB_TH_32_32, false, kEpiFrame>(x, none, w_fwd, bias, y, none, oc, s, st);
+  hipError_t e = launch_conv<32, 32, DFB_TH_32_32, false, kEpiFrame>(x, none, w_fwd, bias, y, none, oc, s, tickets, st);
   if (e != hipSuccess) return e;
   frame_display_k<<<blocks(T * g.P, 256), 256, 0, st>>>(g, den, final_out, mode, inv_gamma);
   return hipGetLastError();

@@ -76,6 +76,7 @@ struct dfb_denoiser_ctx {
   float* scratch = nullptr;    // partial sums of every gradient (TrainPlan)
   uint16_t* gate[12] = {};     // gated output gradients of the layers (bf16)
   float* loss_dev = nullptr;
+  uint32_t* tickets = nullptr;  // of the persistent convolutions
   Shape last{0, 0, 0};
   bool planar = false;  // the last forward kept the skip concatenations as separate maps
   bool lean = false;    // the last forward fused the output conv and did not store dec1b
@@ -160,6 +161,7 @@ dfb_status forward(dfb_denoiser_ctx* n, const float* in, const Shape& s0, bool t
   const float* W = n->w;
   auto B = [&](int i) { return W + n->off_b[i]; };
   using dfb::unet::conv3x3_fwd;
+  uint32_t* const tk = n->tickets;
   const Map pool1 = mp(n->pool1, 32, 0, 32), pool2 = mp(n->pool2, 64, 0, 64);
   const CatLayout c = cat_layout(n, s0, !training);
   if (lean) {
@@ -168,28 +170,28 @@ dfb_status forward(dfb_denoiser_ctx* n, const float* in, const Shape& s0, bool t
     NHIP(n, dfb::unet::pack_input(in, 6, n->xin, s0, st));
     NHIP(n, dfb::unet::conv3x3_in_fwd(mp(n->xin, 8, 0, 8), n->wf[ENC1A], B(ENC1A), mp(n->e1a, 32, 0, 32), s0, st));
   }
-  NHIP(n, conv3x3_fwd(mp(n->e1a, 32, 0, 32), n->wf[ENC1B], B(ENC1B), c.enc1b, s0, st, false, &pool1));
-  NHIP(n, conv3x3_fwd(pool1, n->wf[ENC2A], B(ENC2A), mp(n->e2a, 64, 0, 64), s1, st));
-  NHIP(n, conv3x3_fwd(mp(n->e2a, 64, 0, 64), n->wf[ENC2B], B(ENC2B), c.enc2b, s1, st, false, &pool2));
-  NHIP(n, conv3x3_fwd(pool2, n->wf[ENC3A], B(ENC3A), mp(n->e3a, 128, 0, 128), s2, st));
-  NHIP(n, conv3x3_fwd(mp(n->e3a, 128, 0, 128), n->wf[ENC3B], B(ENC3B), mp(n->e3b, 128, 0, 128), s2, st));
-  NHIP(n, conv3x3_fwd(mp(n->e3b, 128, 0, 128), n->wf[UP2], B(UP2), c.up2, s1, st, true));
+  NHIP(n, conv3x3_fwd(mp(n->e1a, 32, 0, 32), n->wf[ENC1B], B(ENC1B), c.enc1b, s0, tk, st, false, &pool1));
+  NHIP(n, conv3x3_fwd(pool1, n->wf[ENC2A], B(ENC2A), mp(n->e2a, 64, 0, 64), s1, tk, st));
+  NHIP(n, conv3x3_fwd(mp(n->e2a, 64, 0, 64), n->wf[ENC2B], B(ENC2B), c.enc2b, s1, tk, st, false, &pool2));
+  NHIP(n, conv3x3_fwd(pool2, n->wf[ENC3A], B(ENC3A), mp(n->e3a, 128, 0, 128), s2, tk, st));
+  NHIP(n, conv3x3_fwd(mp(n->e3a, 128, 0, 128), n->wf[ENC3B], B(ENC3B), mp(n->e3b, 128, 0, 128), s2, tk, st));
+  NHIP(n, conv3x3_fwd(mp(n->e3b, 128, 0, 128), n->wf[UP2], B(UP2), c.up2, s1, tk, st, true));
   if (training)
-    NHIP(n, conv3x3_fwd(mp(n->cat2, 128, 0, 128), n->wf[DEC2A], B(DEC2A), mp(n->d2a, 64, 0, 64), s1, st));
+    NHIP(n, conv3x3_fwd(mp(n->cat2, 128, 0, 128), n->wf[DEC2A], B(DEC2A), mp(n->d2a, 64, 0, 64), s1, tk, st));
   else
-    NHIP(n, conv3x3_fwd(c.up2, n->wf[DEC2A], B(DEC2A), mp(n->d2a, 64, 0, 64), s1, st, false, nullptr, &c.enc2b));
-  NHIP(n, conv3x3_fwd(mp(n->d2a, 64, 0, 64), n->wf[DEC2B], B(DEC2B), mp(n->d2b, 64, 0, 64), s1, st));
-  NHIP(n, conv3x3_fwd(mp(n->d2b, 64, 0, 64), n->wf[UP1], B(UP1), c.up1, s0, st, true));
+    NHIP(n, conv3x3_fwd(c.up2, n->wf[DEC2A], B(DEC2A), mp(n->d2a, 64, 0, 64), s1, tk, st, false, nullptr, &c.enc2b));
+  NHIP(n, conv3x3_fwd(mp(n->d2a, 64, 0, 64), n->wf[DEC2B], B(DEC2B), mp(n->d2b, 64, 0, 64), s1, tk, st));
+  NHIP(n, conv3x3_fwd(mp(n->d2b, 64, 0, 64), n->wf[UP1], B(UP1), c.up1, s0, tk, st, true));
   if (training)
-    NHIP(n, conv3x3_fwd(mp(n->cat1, 64, 0, 64), n->wf[DEC1A], B(DEC1A), mp(n->d1a, 32, 0, 32), s0, st));
+    NHIP(n, conv3x3_fwd(mp(n->cat1, 64, 0, 64), n->wf[DEC1A], B(DEC1A), mp(n->d1a, 32, 0, 32), s0, tk, st));
   else
-    NHIP(n, conv3x3_fwd(c.up1, n->wf[DEC1A], B(DEC1A), mp(n->d1a, 32, 0, 32), s0, st, false, nullptr, &c.enc1b));
+    NHIP(n, conv3x3_fwd(c.up1, n->wf[DEC1A], B(DEC1A), mp(n->d1a, 32, 0, 32), s0, tk, st, false, nullptr, &c.enc1b));
   if (lean) {
     NHIP(n, dfb::unet::conv3x3_out_frame(mp(n->d1a, 32, 0, 32), n->wf[DEC1B], B(DEC1B), W + n->off_ow, W + n->off_ob,
                                          fv->glue, tau, fv->denoised, fv->final_out, fv->display_mode, fv->inv_gamma,
-                                         s0, st));
+                                         s0, tk, st));
   } else {
-    NHIP(n, conv3x3_fwd(mp(n->d1a, 32, 0, 32), n->wf[DEC1B], B(DEC1B), mp(n->d1b, 32, 0, 32), s0, st));
+    NHIP(n, conv3x3_fwd(mp(n->d1a, 32, 0, 32), n->wf[DEC1B], B(DEC1B), mp(n->d1b, 32, 0, 32), s0, tk, st));
     if (!training)  // the backward pass computes it itself
       NHIP(n, dfb::unet::out_conv_fwd(mp(n->d1b, 32, 0, 32), W + n->off_ow, W + n->off_ob, in, 6, n->out, s0, st));
   }
@@ -384,7 +386,11 @@ dfb_status dfb_denoiser_create(const dfb_unet_config* cfg, void* hip_stream, dfb
   // the most partial sums of any batch of at most P0 pixels: its images are at
   // least 4 x 4, so the smallest ones have the most tiles
   const size_t sc = train_plan(n, Shape{static_cast<int>((P0 + 15) / 16), 4, 4}).floats;
-  if ((s = dalloc(n, &n->scratch, sc)) || (s = dalloc(n, &n->loss_dev, 4))) return bail(s);
+  if ((s = dalloc(n, &n->scratch, sc)) || (s = dalloc(n, &n->loss_dev, 4)) ||
+      (s = dalloc(n, &n->tickets, dfb::unet::kTicketWords)))
+    return bail(s);
+  if (hipMemsetAsync(n->tickets, 0, sizeof(uint32_t) * dfb::unet::kTicketWords, n->stream) != hipSuccess)
+    return bail(nfail(n, DFB_ERR_HIP, "clearing the ticket counters"));
   // initial parameters: He-normal conv3x3 weights, zero biases, N(0, 0.01) output weights
   std::vector<float> h(np, 0.f);
   uint64_t st = 0x5DEECE66Dull ^ cfg->seed;

@@ -40,3 +40,22 @@ def test_one_image_and_many(h, w):
         a, b = a.reshape(1, -1), b.reshape(n, -1)
         assert np.array_equal(np.repeat(a, n, axis=0), b)
     assert np.linalg.norm(grads[0] - grads[1]) <= 1e-4 * np.linalg.norm(grads[0])
+
+
+def test_repeated_forwards_of_changing_size():
+    """The persistent kernels hand out tiles by counters that every launch
+    leaves at zero: sizes on both sides of two tiles a workgroup in turn, each
+    three times, always the same bits."""
+    torch = torch_dev()
+    import paper_2305_07083_amd as dfb
+    rng = np.random.default_rng(8)
+    sizes = [(2, 256, 512), (1, 64, 128), (1, 512, 516), (7, 100, 260)]
+    first = {}
+    with dfb.Denoiser(max(n * h * w for n, h, w in sizes), seed=5, stream=stream_handle()) as d:
+        xs = {s: torch.from_numpy(rng.random(s + (6,)).astype(np.float32)).cuda() for s in sizes}
+        for _ in range(3):
+            for s in sizes:
+                out = torch.empty(s + (3,), dtype=torch.float32, device="cuda")
+                dfb.dfb_denoiser_forward(d.net, xs[s], out, *s)
+                got = out.cpu().numpy()
+                assert np.array_equal(first.setdefault(s, got), got), s
