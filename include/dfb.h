@@ -341,9 +341,9 @@ dfb_status dfb_validate_layers(const dfb_config* cfg, int64_t n_blocks, const df
  * allocation): one plain frame -- the same frame kernel as
  * dfb_composite_frame, without accumulation -- into caller-owned outputs.
  * It calls no allocator: its work queue's counters, the frame state and the
- * longest-first work list (built on the device from tile_off_dev) live in a
- * static device array of DFB_NOALLOC_MAX_WORK work units plus 208 KiB, one
- * per GPU, held until the process ends; the first call on a device clears
+ * longest-first tile list (built on the device from tile_off_dev) live in a
+ * static device array of 16 bytes for each of DFB_NOALLOC_MAX_WORK tiles plus
+ * 208 KiB (16.2 MiB), one per GPU, held until the process ends; the first call on a device clears
  * it (a fill kernel on hip_stream).  All calls on one GPU share that array:
  * calls that overlap in time on one GPU (different streams or threads)
  * race and give wrong results; calls ordered on one stream are safe.

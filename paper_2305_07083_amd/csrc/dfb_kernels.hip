@@ -1276,15 +1276,25 @@ __device__ __forceinline__ void finish_workgroup(const FrameArgs& a, uint32_t se
   }
 }
 
+// The tile at a position of the launch's list; without a list, in tile order.
+__device__ __forceinline__ TileRec tile_rec(const FrameArgs& a, const TileRec* __restrict__ recs,
+                                            const int32_t* __restrict__ tile_off, int pos) {
+  if (recs) return recs[pos];
+  const int off = tile_off[pos];
+  return {pos, off, tile_off[pos + 1] - off, 0};
+}
+
 // KCAP 8, 16, 32: register-sort capacity (tiles with more layers are other
 // launches'); KCAP 0: only the tiles with more than a.big_min layers.
 template <typename FT, int KCAP, int OP>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(min_waves(KCAP, sizeof(FT) == 2))))
 frame_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off,
-               const int64_t* __restrict__ layer_off, const int32_t* __restrict__ work_list) {
+               const int64_t* __restrict__ layer_off, const TileRec* __restrict__ recs) {
   extern __shared__ __align__(16) char lds[];
-  __shared__ int s_item;
-  __shared__ float s_red[4];
+  // the next unit and a unit's M2 sums, in two buffers used in turn: a wave may
+  // be a unit behind another, so one barrier a unit is enough
+  __shared__ __align__(16) int4 s_next[2];
+  __shared__ float s_red[2][4];
   constexpr bool kLast = KCAP > 0;  // the frame's last launch: it counts its workgroups and advances the state
   const int tid = threadIdx.x;
   const int n_waves = static_cast<int>(blockDim.x >> 6);
@@ -1296,28 +1306,24 @@ frame_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off,
   Queue q = queue_of(a, home);
   int it = r < q.n ? unit_at(a, q, r) : a.n_work;  // the first unit is static
   // its table entries are on their way while the state is read
-  int w = 0, off = 0, K = 0;
-  auto unit_tables = [&] {
-    w = work_list ? work_list[it] : it;
-    const int t = w / a.subs_per_tile;
-    off = tile_off[t];
-    K = tile_off[t + 1] - off;
-  };
-  if (it < a.n_work) unit_tables();
+  TileRec rec = {0, 0, 0, 0};
+  if (it < a.n_work) rec = tile_rec(a, recs, tile_off, it / a.subs_per_tile);
   const uint32_t seq = use_frame_state(a, seq_read);
   q.ctr += a.slot;
   if (kLast && blockIdx.x == 0) recycle_slots(a);
   uint64_t closed = 0;  // counters this workgroup has found empty
+  int turn = 0;
   while (it < a.n_work) {
     // the next unit's ticket is taken now and read after this unit's work
     const uint32_t next = wave0 && !a.one_each ? take_ticket(q) : 0u;
     Unit u;
-    u.t = w / a.subs_per_tile;
-    const int s = w - u.t * a.subs_per_tile;
+    u.t = rec.tile;
+    const int s = it - (it / a.subs_per_tile) * a.subs_per_tile, w = u.t * a.subs_per_tile + s;
     u.sy0 = (s / a.subs_x) * a.work_h;
     u.sx0 = (s - (s / a.subs_x) * a.subs_x) * a.work_w;
     u.y0 = (u.t / a.tiles_x) * a.tile_h;
     u.x0 = (u.t - (u.t / a.tiles_x) * a.tiles_x) * a.tile_w;
+    const int off = rec.off, K = rec.layers;
     const int64_t* __restrict__ blk = layer_off + off;
     float* wl = reinterpret_cast<float*>(lds);
     float vs = 0.f;
@@ -1354,19 +1360,25 @@ frame_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off,
     const bool acc = (a.mode & kModeAccumulate) != 0 && mine;
     if (acc) {
       vs = wave_sum(vs);  // fixed-order reductions only: deterministic
-      if ((tid & 63) == 0) s_red[tid >> 6] = vs;
+      if ((tid & 63) == 0) s_red[turn][tid >> 6] = vs;
     }
-    lds_barrier();  // s_red complete; every lane has read s_item
-    if (wave0 && acc) store_partial(a, w, s_red, n_waves);
-    if (a.one_each) break;
-    if (wave0) {
+    if (wave0 && !a.one_each) {  // the next unit and its tile, while the other waves finish this one
       int v = ticket_to_unit(a, q, next);
       if (v == a.n_work) v = next_open_unit(a, q, closed);
-      if (__lane_id() == 0) s_item = v;
+      int4 n = {v, 0, 0, 0};
+      if (v < a.n_work) {
+        const TileRec t = tile_rec(a, recs, tile_off, v / a.subs_per_tile);
+        n = {v, t.tile, t.off, t.layers};
+      }
+      if (__lane_id() == 0) s_next[turn] = n;
     }
-    lds_barrier();
-    it = __builtin_amdgcn_readfirstlane(s_item);
-    if (it < a.n_work) unit_tables();
+    lds_barrier();  // s_red and s_next complete
+    if (wave0 && acc) store_partial(a, w, s_red[turn], n_waves);
+    if (a.one_each) break;
+    const int4 n = s_next[turn];
+    it = __builtin_amdgcn_readfirstlane(n.x);
+    rec = {__builtin_amdgcn_readfirstlane(n.y), __builtin_amdgcn_readfirstlane(n.z), __builtin_amdgcn_readfirstlane(n.w), 0};
+    turn ^= 1;
   }
   if (kLast) finish_workgroup(a, seq, home);
 }
@@ -1643,7 +1655,7 @@ constexpr int deep_waves(int rmax) { return rmax >= 32 ? 4 : 6; }
 template <typename FT, int RMAX>
 __global__ void __launch_bounds__(kDeepThreads) __attribute__((amdgpu_waves_per_eu(deep_waves(RMAX))))
 deep_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off, const int64_t* __restrict__ layer_off,
-              const int32_t* __restrict__ work_list) {
+              const TileRec* __restrict__ recs) {
   extern __shared__ __align__(16) char lds[];
   __shared__ int s_item;
   const int tid = threadIdx.x;
@@ -1664,13 +1676,13 @@ deep_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off, const int64_
     // position it of the launch's list: piece it % deep_subs of the tile at
     // sorted position it / deep_subs
     const int pos = it / a.deep_subs, piece = it - pos * a.deep_subs;
+    const TileRec rec = tile_rec(a, recs, tile_off, pos);
     Unit u;
-    u.t = (work_list ? work_list[pos * a.subs_per_tile] : pos * a.subs_per_tile) / a.subs_per_tile;
+    u.t = rec.tile;
     u.sx0 = u.sy0 = 0;
     u.y0 = (u.t / a.tiles_x) * a.tile_h;
     u.x0 = (u.t - (u.t / a.tiles_x) * a.tiles_x) * a.tile_w;
-    const int off = tile_off[u.t];
-    const int K = tile_off[u.t + 1] - off;
+    const int off = rec.off, K = rec.layers;
     const bool mine = K > kRegMax && K <= kDeepMax && K <= a.deep_layers;
     if (mine) {
       for (int i = tid; i < K; i += kDeepThreads) lofs[i] = layer_off[off + i];
@@ -1779,17 +1791,14 @@ __global__ void copy_u32_kernel_t(const uint32_t* __restrict__ src, uint32_t* __
     dst[i] = src[i];
 }
 
-// Longest-first work list on the device, from the per-tile CSR offsets:
-// a counting sort of the tiles by layer count, descending (one workgroup of
-// kLptThreads lanes; equal counts in any order, which changes only the
-// order units are taken in, never a result), then every tile's units in
-// order.  work[pos * subs + u] = t * subs + u for the tile t at sorted
-// position pos.
+// Longest-first list of the tiles on the device, from the per-tile CSR offsets:
+// a counting sort by layer count, descending (one workgroup of kLptThreads
+// lanes; equal counts in any order, which changes only the order units are
+// taken in, never a result).
 constexpr int kLptBins = kMaxLayers + 1;                                // K = 0 .. kMaxLayers
 constexpr int kLptPer = (kLptBins + kLptThreads - 1) / kLptThreads;    // bins per lane in the scan
 __global__ void __launch_bounds__(kLptThreads) lpt_work_kernel_t(const int32_t* __restrict__ tile_off,
-                                                                 int32_t n_tiles, int32_t subs,
-                                                                 int32_t* __restrict__ work) {
+                                                                 int32_t n_tiles, TileRec* __restrict__ recs) {
   __shared__ int32_t cnt[kLptBins];     // bin j holds layer count K = kMaxLayers - j
   __shared__ int32_t wave_tot[kLptThreads / 64];
   const int tid = threadIdx.x;
@@ -1831,10 +1840,9 @@ __global__ void __launch_bounds__(kLptThreads) lpt_work_kernel_t(const int32_t* 
   }
   __syncthreads();
   for (int t = tid; t < n_tiles; t += kLptThreads) {
-    int K = tile_off[t + 1] - tile_off[t];
-    K = K < 0 ? 0 : (K > kMaxLayers ? kMaxLayers : K);
-    const int pos = atomicAdd(&cnt[kMaxLayers - K], 1);
-    for (int u = 0; u < subs; ++u) work[static_cast<int64_t>(pos) * subs + u] = t * subs + u;
+    const int off = tile_off[t], layers = tile_off[t + 1] - off;
+    const int K = layers < 0 ? 0 : (layers > kMaxLayers ? kMaxLayers : layers);
+    recs[atomicAdd(&cnt[kMaxLayers - K], 1)] = {t, off, layers, 0};
   }
 }
 

@@ -80,9 +80,8 @@ struct dfb_ctx {
   std::vector<dfb_layer> last_layers;
   std::vector<int32_t> last_expected;
   bool last_had_expected = false;
-  std::vector<int64_t> h_block;  // layer offsets, as on the device
-  // Two sets of device layer tables (layer offsets, per-tile offsets, work
-  // list, in one allocation), used by successive layer layouts in turn, each
+  // Two sets of device layer tables (layer offsets, the tiles most layers first,
+  // per-tile offsets, in one allocation), used by successive layer layouts in turn, each
   // uploaded from pinned host staging with one copy: a new layout is written to
   // the set the frames in flight do not read, so its upload needs no wait for
   // them.  A set, and its staging, is reused two layouts later, after the event
@@ -90,6 +89,9 @@ struct dfb_ctx {
   struct Tables {
     char* dev = nullptr;
     size_t cap = 0;
+    int64_t* block = nullptr;      // the arrays in dev
+    dfb::TileRec* recs = nullptr;
+    int32_t* off = nullptr;
     char* st = nullptr;            // pinned staging
     size_t st_cap = 0;
     bool staged = false;           // an upload may still read the staging
@@ -99,7 +101,7 @@ struct dfb_ctx {
   int cur_tables = 0;
   int32_t* d_off = nullptr;    // the current set's arrays
   int64_t* d_block = nullptr;
-  int32_t* d_work = nullptr;
+  dfb::TileRec* d_recs = nullptr;
   float* d_var_partial = nullptr;
   size_t partial_cap = 0;
   uint32_t* d_flag = nullptr;
@@ -124,7 +126,7 @@ struct dfb_ctx {
   int grid = 0;
   int n_work = 0;
   int subs_x = 1, subs_per_tile = 1;
-  bool work_valid = false;  // d_work matches shape + layer table
+  bool work_valid = false;  // the units match shape + layer table
 
   // timing: a ring of event pairs, harvested when a slot is reused; every
   // timing_every-th composite is timed (0: none)
@@ -360,16 +362,15 @@ bool has_deep(const dfb_ctx* h) {
 }
 DeepUnits deep_units(const dfb_ctx* h) { return deep_units(h->P, h->n_deep, h->n_cu); }
 
-// Uploads the current layout's layer and tile offsets, and n_work work-list
-// entries that `fill` writes, to a table set, stream-ordered and in one copy
-// (three, with an event each: 68 us a 1024x1024 frame, 51 now).  Only called on a set
-// no frame in flight reads (the other set's, or during the autotuner's
-// synchronous sweep).
-template <class Fill>
-dfb_status upload_tables(dfb_ctx* h, dfb_ctx::Tables& S, const std::vector<int32_t>& off, size_t n_work, Fill fill) {
-  const size_t block_bytes = h->h_block.size() * sizeof(int64_t), off_bytes = off.size() * sizeof(int32_t);
-  const size_t bytes = block_bytes + off_bytes + n_work * sizeof(int32_t);
-  if (S.staged) {  // staged twice in a row: the autotuner
+// Uploads a layout's layer offsets, tile records and tile offsets to a table
+// set, stream-ordered and in one copy (three, with an event each: 68 us a
+// 1024x1024 frame, 51 now).  Only called on a set no frame in flight reads.
+dfb_status upload_tables(dfb_ctx* h, dfb_ctx::Tables& S, const std::vector<int64_t>& block,
+                         const std::vector<int32_t>& off, int max_k) {
+  const size_t block_bytes = (block.size() * sizeof(int64_t) + 15) / 16 * 16;
+  const size_t rec_bytes = static_cast<size_t>(h->n_tiles) * sizeof(dfb::TileRec), off_bytes = off.size() * sizeof(int32_t);
+  const size_t bytes = block_bytes + rec_bytes + off_bytes;
+  if (S.staged) {  // a layout that was refused after its upload
     DFB_HIP(h, hipStreamSynchronize(h->stream));
     S.staged = false;
   }
@@ -397,9 +398,22 @@ dfb_status upload_tables(dfb_ctx* h, dfb_ctx::Tables& S, const std::vector<int32
     }
     S.st_cap = cap;
   }
-  if (block_bytes) std::memcpy(S.st, h->h_block.data(), block_bytes);
-  std::memcpy(S.st + block_bytes, off.data(), off_bytes);
-  fill(reinterpret_cast<int32_t*>(S.st + block_bytes + off_bytes));
+  if (!block.empty()) std::memcpy(S.st, block.data(), block.size() * sizeof(int64_t));
+  dfb::TileRec* recs = reinterpret_cast<dfb::TileRec*>(S.st + block_bytes);
+  // counting sort by layers: at[K] is the next list position of a tile of K
+  std::vector<int32_t> at(max_k + 1, 0);
+  for (int t = 0; t < h->n_tiles; ++t) ++at[off[t + 1] - off[t]];
+  int32_t pos = 0;
+  for (int k = max_k; k >= 0; --k) {
+    const int32_t c = at[k];
+    at[k] = pos;
+    pos += c;
+  }
+  for (int t = 0; t < h->n_tiles; ++t) {
+    const int32_t k = off[t + 1] - off[t];
+    recs[at[k]++] = {t, off[t], k, 0};
+  }
+  std::memcpy(S.st + block_bytes + rec_bytes, off.data(), off_bytes);
   // by a kernel that reads the staging over the bus: the runtime gives a copy
   // of more than a few pages to a DMA engine, and the frame kernel then starts
   // 18 us later (1024x1024, every frame a new layout: 60 us a frame, 51 by the
@@ -412,9 +426,9 @@ dfb_status upload_tables(dfb_ctx* h, dfb_ctx::Tables& S, const std::vector<int32
   DFB_HIP(h, hipLaunchKernel(dfb::copy_u32_kernel(), dim3(static_cast<unsigned>(std::min<int64_t>((words + 255) / 256, 1024))),
                              dim3(256), params, 0, h->stream));
   S.staged = true;
-  h->d_block = reinterpret_cast<int64_t*>(S.dev);
-  h->d_off = reinterpret_cast<int32_t*>(S.dev + block_bytes);
-  h->d_work = reinterpret_cast<int32_t*>(S.dev + block_bytes + off_bytes);
+  S.block = reinterpret_cast<int64_t*>(S.dev);
+  S.recs = reinterpret_cast<dfb::TileRec*>(S.dev + block_bytes);
+  S.off = reinterpret_cast<int32_t*>(S.dev + block_bytes + rec_bytes);
   return DFB_OK;
 }
 
@@ -427,8 +441,7 @@ void free_tables(dfb_ctx* h) {
   }
 }
 
-// Work list for a shape: every (tile, unit) pair, tiles with more layers
-// first (longest-processing-time order), ties by tile id.
+// The units of the current layout with a launch shape.
 dfb_status build_work(dfb_ctx* h, const Shape& s) {
   drop_graphs(h);
   const int sx = h->cfg.tile_w / s.work_w, sy = h->cfg.tile_h / s.work_h;
@@ -437,22 +450,6 @@ dfb_status build_work(dfb_ctx* h, const Shape& s) {
   h->n_work = h->n_tiles * h->subs_per_tile;
   const size_t n = static_cast<size_t>(h->n_work);
   dfb_status st = ensure(h, h->d_var_partial, h->partial_cap, n + static_cast<size_t>(h->n_tiles) * (h->n_deep ? deep_units(h).subs : 0));
-  if (st != DFB_OK) return st;
-  st = upload_tables(h, h->tables[h->cur_tables], h->h_off, n, [&](int32_t* work) {
-    // counting sort by layers: at[K] is the next list position of a tile of K
-    std::vector<int32_t> at(h->max_k + 2, 0);
-    for (int t = 0; t < h->n_tiles; ++t) ++at[h->h_off[t + 1] - h->h_off[t]];
-    int32_t pos = 0;
-    for (int k = h->max_k; k >= 0; --k) {
-      const int32_t c = at[k];
-      at[k] = pos;
-      pos += c;
-    }
-    for (int t = 0; t < h->n_tiles; ++t) {
-      int32_t* w = work + static_cast<size_t>(at[h->h_off[t + 1] - h->h_off[t]]++) * h->subs_per_tile;
-      for (int u = 0; u < h->subs_per_tile; ++u) w[u] = t * h->subs_per_tile + u;
-    }
-  });
   if (st != DFB_OK) return st;
   h->work_valid = true;
   return DFB_OK;
@@ -577,13 +574,13 @@ struct KernelLaunch {
   FrameArgs fa;
   const int32_t* tab_off;
   const int64_t* tab_layer;
-  const int32_t* tab_work;
+  const dfb::TileRec* recs;
   void* params[4];
   void bind() {
     params[0] = &fa;
     params[1] = &tab_off;
     params[2] = &tab_layer;
-    params[3] = &tab_work;
+    params[3] = &recs;
   }
 };
 
@@ -629,7 +626,7 @@ struct FrameShape {
 // per-kernel buffers filled in by the caller's base): fills L.k[0..nk).
 dfb_status plan_kernels(dfb_ctx* h, const dfb_config& c, const FrameArgs& base, uint32_t* queue_base,
                         const Shape& sh, const FrameShape& fs, const int32_t* tab_off,
-                        const int64_t* tab_layer, const int32_t* tab_work, FrameLaunch& L) {
+                        const int64_t* tab_layer, const dfb::TileRec* recs, FrameLaunch& L) {
   const bool sorting = c.tile_op == DFB_OP_ALPHA_BLEND;
   L.nk = 0;
   for (int ring : {1, 2, 0}) {
@@ -641,7 +638,7 @@ dfb_status plan_kernels(dfb_ctx* h, const dfb_config& c, const FrameArgs& base, 
     K.fa.state = dfb::state_of(queue_base);
     K.tab_off = tab_off;
     K.tab_layer = tab_layer;
-    K.tab_work = tab_work;
+    K.recs = recs;
     if (ring == 2) {
       const int first = fs.n_big > 0 ? fs.n_big : 0;
       K.func = dfb::deep_kernel(c.frag_dtype, fs.max_k);
@@ -651,7 +648,7 @@ dfb_status plan_kernels(dfb_ctx* h, const dfb_config& c, const FrameArgs& base, 
       K.fa.deep_subs = K.fa.queue_block = fs.du.subs;
       K.fa.deep_layers = dfb::deep_layers(fs.max_k);
       K.fa.n_work = ((fs.n_deep < 0 ? fs.n_tiles : fs.n_deep) - first) * fs.du.subs;
-      K.tab_work = tab_work + static_cast<size_t>(first) * base.subs_per_tile;
+      K.recs = recs + first;
     } else {
       const int kc = ring == 1 ? 0 : fs.kcap;
       K.func = dfb::frame_kernel(c.frag_dtype, kc, c.tile_op);
@@ -662,7 +659,7 @@ dfb_status plan_kernels(dfb_ctx* h, const dfb_config& c, const FrameArgs& base, 
       if (ring == 1 && fs.n_big >= 0) K.fa.n_work = (base.quad_ok ? fs.n_big : fs.n_deep) * base.subs_per_tile;
       if (ring == 0 && sorting && fs.n_deep > 0) {
         K.fa.n_work -= fs.n_deep * base.subs_per_tile;
-        K.tab_work = tab_work + static_cast<size_t>(fs.n_deep) * base.subs_per_tile;
+        K.recs = recs + fs.n_deep;
       }
     }
     int grid_max = 0;
@@ -680,7 +677,7 @@ dfb_status prepare_launch(dfb_ctx* h, uint32_t mode, FrameLaunch& L) {
   const FrameShape fs{h->max_k, h->kcap, h->n_tiles, h->n_cu, h->n_deep, h->n_big,
                       h->cfg.tile_op == DFB_OP_ALPHA_BLEND && (base.quad_ok ? h->n_big : h->n_deep) > 0, has_deep(h),
                       deep_units(h)};
-  dfb_status st = plan_kernels(h, h->cfg, base, h->d_queue_ring, h->shape, fs, h->d_off, h->d_block, h->d_work, L);
+  dfb_status st = plan_kernels(h, h->cfg, base, h->d_queue_ring, h->shape, fs, h->d_off, h->d_block, h->d_recs, L);
   if (st != DFB_OK) return st;
   L.acc = (mode & dfb::kModeAccumulate) != 0;
   L.va = make_var_args(h);
@@ -921,12 +918,12 @@ dfb_status frame_view(dfb_ctx* h, FrameView* v, bool want_denoised) {
 
 // Scratch of dfb_composite_noalloc (the entry point for callers that cannot
 // allocate): the work queue's counters, finish counters and frame state
-// (kQueueWords words), then the longest-first work list of at most
-// DFB_NOALLOC_MAX_WORK units.  One copy per device, held until the process
+// (kQueueWords words), then the longest-first list of at most
+// DFB_NOALLOC_MAX_WORK tiles.  One copy per device, held until the process
 // ends.  Host code uses it only through the device address that
 // hipGetSymbolAddress returns for the current device, never by its name.
 namespace {
-constexpr int64_t kScratchWords = dfb::kQueueWords + DFB_NOALLOC_MAX_WORK;
+constexpr int64_t kScratchWords = dfb::kQueueWords + 4 * static_cast<int64_t>(DFB_NOALLOC_MAX_WORK);
 static __device__ __align__(256) uint32_t scratch[kScratchWords];
 
 constexpr int kScratchDevices = 64;
@@ -1120,10 +1117,9 @@ dfb_status dfb_set_fragments(dfb_handle h, const void* frag_dev, int64_t n_block
     T.released_pending = false;
     T.staged = false;
   }
+  if ((s = upload_tables(h, T, block, off, max_k)) != DFB_OK) return s;
   if (h->cfg.flags & DFB_VALIDATE) {
-    h->h_block = block;
-    s = upload_tables(h, T, off, 0, [](int32_t*) {});
-    if (s == DFB_OK) s = scan_nan(h, frag_dev, h->d_block, n_layers);
+    s = scan_nan(h, frag_dev, T.block, n_layers);
     if (s != DFB_OK) {  // the frame is refused: set_fragments must come again before a composite
       h->state = State::kEmpty;
       h->n_layers = -1;
@@ -1144,11 +1140,13 @@ dfb_status dfb_set_fragments(dfb_handle h, const void* frag_dev, int64_t n_block
     O.released_pending = true;
   }
   h->cur_tables = nxt;
+  h->d_off = T.off;
+  h->d_block = T.block;
+  h->d_recs = T.recs;
   // a new launch shape only for a new layer-count class
   if (h->state == State::kEmpty || kcap_for(max_k) != h->kcap || layer_class(max_k) != layer_class(h->max_k))
     h->shape_valid = false;
   h->h_off.swap(off);
-  h->h_block.swap(block);
   h->n_layers = n_layers;
   h->n_blocks = n_blocks;
   h->max_k = max_k;
@@ -1496,7 +1494,8 @@ dfb_status dfb_composite_noalloc(const dfb_config* cfg, const void* frag_dev, co
   if ((s = scratch_of_current_device(&base, &first)) != DFB_OK) return s;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   uint32_t* queue = static_cast<uint32_t*>(base);
-  int32_t* work = reinterpret_cast<int32_t*>(queue + dfb::kQueueWords);
+  dfb::TileRec* recs = reinterpret_cast<dfb::TileRec*>(queue + dfb::kQueueWords);
+  static_assert(dfb::kQueueWords % 4 == 0, "records are 16-byte aligned");
   if (first) {  // counters and frame state start at zero; a fill kernel, no memset node
     int64_t words = kScratchWords;
     uint32_t zero = 0;
@@ -1516,13 +1515,13 @@ dfb_status dfb_composite_noalloc(const dfb_config* cfg, const void* frag_dev, co
   const bool blend = cfg->tile_op == DFB_OP_ALPHA_BLEND;
   const FrameShape fs{max_layers, kcap_for(max_layers), n_tiles, n_cu, -1, -1, blend && max_layers > (a.quad_ok ? dfb::kDeepMax : dfb::kRegMax),
                       blend && max_layers > dfb::kRegMax && a.quad_ok, deep_units(a.P, n_tiles, n_cu)};
-  if ((s = plan_kernels(nullptr, *cfg, a, queue, sh, fs, tile_off_dev, layer_off_dev, work, L)) != DFB_OK) return s;
+  if ((s = plan_kernels(nullptr, *cfg, a, queue, sh, fs, tile_off_dev, layer_off_dev, recs, L)) != DFB_OK) return s;
   L.bind();
   if (L.nk == 1 && L.k[0].fa.one_each) {
-    L.k[0].tab_work = nullptr;  // every unit has a workgroup of its own: their order does not matter
+    L.k[0].recs = nullptr;  // every unit has a workgroup of its own: their order does not matter
   } else {
-    int32_t nt = n_tiles, subs = a.subs_per_tile;
-    void* lp[] = {&tile_off_dev, &nt, &subs, &work};
+    int32_t nt = n_tiles;
+    void* lp[] = {&tile_off_dev, &nt, &recs};
     DFB_HIP(nullptr, hipLaunchKernel(dfb::lpt_work_kernel(), dim3(1), dim3(dfb::kLptThreads), lp, 0, st));
   }
   for (int i = 0; i < L.nk; ++i)
