@@ -110,7 +110,8 @@ struct FrameArgs {
   int32_t work_shift;          // log2(work_w) if a power of two, else -1
   int32_t big_lds;             // LDS bytes for keys + weights of the LDS sort
   int32_t vec_ok;              // 16-byte plane loads possible (alignment, work_w, tile_w)
-  int32_t deep_px, deep_subs;  // row-sort launch: pixels per unit, units per tile
+  int32_t deep_subs;           // row-sort launch: units (groups of kDeepPx pixels) per tile, else 0
+  int32_t max_run;             // units a draw takes at most (the row sort's; else 1)
   int32_t deep_layers;         // row-sort launch: layers its LDS holds
   int32_t quad_ok;             // 4-pixel plane loads are aligned: the row sort can run
   int32_t big_min;             // LDS sort: it takes the tiles of more layers than this

@@ -1132,7 +1132,8 @@ __device__ __forceinline__ float variance_of_mean(float sum, int inside_px, int 
 // whose counter is drained reads all counters at once, one a lane, and goes
 // on to the next open one (s + 1, s + 2, ... mod S) or ends.  A launch whose
 // counters hold no more units than workgroups start on them (a.one_each)
-// takes no tickets at all.  Workgroups are dealt to the 8 XCDs in turn and S
+// takes no tickets at all.  The row sort draws runs of consecutive units (run_of)
+// and starts on one.  Workgroups are dealt to the 8 XCDs in turn and S
 // is a multiple of 8 on every grid of 8 workgroups or more, so the units of
 // one tile run at about the same time under one XCD's L2: unit rows that
 // share cache lines (fp16 planes, units narrower than a line) are fetched
@@ -1140,13 +1141,22 @@ __device__ __forceinline__ float variance_of_mean(float sum, int inside_px, int 
 struct Queue {
   uint32_t* ctr;
   int s, g, n;  // counter, workgroups starting on it, units it holds
+  int run;      // units a workgroup starts with: the first g * run units are given without a ticket
 };
+
+// A draw of up to a.max_run consecutive units (the row sort's), fewer as the
+// counter runs out: each workgroup's half share of what is left.
+__device__ __forceinline__ int run_of(const FrameArgs& a, int left, int g) {
+  const int n = left / (2 * g);
+  return n < 1 ? 1 : (n < a.max_run ? n : a.max_run);
+}
 
 __device__ __forceinline__ Queue queue_of(const FrameArgs& a, int s) {
   Queue q;
   q.s = s;
   q.g = (static_cast<int>(gridDim.x) - s + a.n_queues - 1) / a.n_queues;
   q.n = queue_units(a.n_work, a.queue_block, a.n_queues, s);
+  q.run = run_of(a, q.n, q.g);
   q.ctr = a.queue + static_cast<size_t>(s) * kQueueStride + a.slot;
   return q;
 }
@@ -1157,39 +1167,43 @@ __device__ __forceinline__ int unit_at(const FrameArgs& a, const Queue& q, int j
   return ((j / B) * a.n_queues + q.s) * B + j % B;
 }
 
-__device__ __forceinline__ uint32_t take_ticket(const Queue& q) {
+__device__ __forceinline__ uint32_t take_ticket(const Queue& q, int n = 1) {
   uint32_t v = 0;
-  if (__lane_id() == 0) v = atomicAdd(q.ctr, 1u);
+  if (__lane_id() == 0) v = atomicAdd(q.ctr, static_cast<uint32_t>(n));
   return v;
 }
 
-__device__ __forceinline__ int ticket_to_unit(const FrameArgs& a, const Queue& q, uint32_t v) {
-  const int64_t j = static_cast<int64_t>(__builtin_amdgcn_readfirstlane(v)) + q.g;
-  return j < q.n ? unit_at(a, q, static_cast<int>(j)) : a.n_work;
+// The index in its counter of the unit a ticket names, or -1: none left.
+__device__ __forceinline__ int ticket_index(const Queue& q, uint32_t v) {
+  const int64_t j = static_cast<int64_t>(__builtin_amdgcn_readfirstlane(v)) + q.g * q.run;
+  return j < q.n ? static_cast<int>(j) : -1;
 }
 
 // The next unit after counter q has no more for this launch (wave 0, all
 // lanes): lane s reads counter s, so finding the open ones costs one trip to
 // the coherent level and not one a counter.  `closed` holds the counters this
-// workgroup is done with, so the loop ends.  Reading them in turn put 15
-// dependent trips behind the last unit of every workgroup; kernel times
-// before, and now with the split finish counts and ticketless launches too:
-// 256^2, 4 ranks 13.9 -> 7.1 us, 1280x720 27.4 -> 15.5, 1920x1080 fp16 average
-// 25.4 -> 21.3, 4096x1024 fp16 159 -> 154 a frame.
-__device__ __forceinline__ int next_open_unit(const FrameArgs& a, Queue& q, uint64_t& closed) {
+// workgroup is done with, so the loop ends.  Sets q to the unit's counter and
+// count to the run drawn, and returns its first index there, or -1: the launch
+// has no more.  Reading the
+// counters in turn put 15 dependent trips behind the last unit of every
+// workgroup; kernel times before, and now with the split finish counts and
+// ticketless launches too: 256^2, 4 ranks 13.9 -> 7.1 us, 1280x720 27.4 -> 15.5,
+// 1920x1080 fp16 average 25.4 -> 21.3, 4096x1024 fp16 159 -> 154 a frame.
+__device__ __forceinline__ int next_open_unit(const FrameArgs& a, Queue& q, uint64_t& closed, int& count) {
   const int S = a.n_queues, lane = static_cast<int>(__lane_id());
   const Queue mine = queue_of(a, lane < S ? lane : 0);
-  int v = a.n_work;
-  while (v == a.n_work) {
+  int j = -1;
+  while (j < 0) {
     closed |= 1ull << q.s;
     const uint32_t c = __hip_atomic_load(mine.ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint64_t open = __ballot(lane < S && static_cast<int64_t>(c) + mine.g < mine.n) & ~closed;
+    const uint64_t open = __ballot(lane < S && static_cast<int64_t>(c) + mine.g * mine.run < mine.n) & ~closed;
     if (open == 0) break;
     const uint64_t after = open & (~0ull << q.s);  // counters past q.s first, then from 0
     q = queue_of(a, __builtin_ctzll(after ? after : open));
-    v = ticket_to_unit(a, q, take_ticket(q));
+    count = run_of(a, q.n - q.g * q.run - static_cast<int>(__builtin_amdgcn_readlane(c, q.s)), q.g);
+    j = ticket_index(q, take_ticket(q, count));
   }
-  return v;
+  return j;
 }
 
 // A unit's M2 sum (all waves) -> var_partial[w].  Runs on all lanes of wave
@@ -1363,8 +1377,10 @@ frame_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off,
       if ((tid & 63) == 0) s_red[turn][tid >> 6] = vs;
     }
     if (wave0 && !a.one_each) {  // the next unit and its tile, while the other waves finish this one
-      int v = ticket_to_unit(a, q, next);
-      if (v == a.n_work) v = next_open_unit(a, q, closed);
+      int j = ticket_index(q, next);
+      int one = 1;
+      if (j < 0) j = next_open_unit(a, q, closed, one);
+      const int v = j < 0 ? a.n_work : unit_at(a, q, j);
       int4 n = {v, 0, 0, 0};
       if (v < a.n_work) {
         const TileRec t = tile_rec(a, recs, tile_off, v / a.subs_per_tile);
@@ -1403,7 +1419,7 @@ frame_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off,
 // memory moves in that time.  The LDS sort it replaces for these counts was
 // bound by the latency of its passes at 8 waves a compute unit, and read each
 // 128-byte line twice.  8192^2 heavy-tailed frame (57.9 GB, up to 512 layers):
-// 36.9 -> 13.7 ms a frame; 1500x1100 fp16, up to 128 layers: 504 -> 168 us.
+// 36.9 -> 13.6 ms a frame; 1500x1100 fp16, up to 128 layers: 504 -> 148 us.
 // Rows are 36 words apart: the 16 lanes of a pixel (at consecutive layers)
 // and the wave's 4 pixels hit all 64 banks once.
 constexpr int kDeepPitch = 36;
@@ -1476,9 +1492,10 @@ __device__ __forceinline__ float add_xor8(float x) {
   return x + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x128, 0xf, 0xf, true));  // row_ror:8
 }
 
-// Pixels [p0, p1) of tile u.t, K <= 16 R layers.  Returns the M2 sum (wave 0).
+// Pixels [p0, p1) of tile u.t, K <= 16 R layers; every group's M2 sum goes to
+// a.deep_partial.
 template <typename FT, int R, int RMAX>
-__device__ __forceinline__ float deep_unit(const FrameArgs& a, const Unit& u, int K_in, int off, int p0, int p1, float* rows,
+__device__ __forceinline__ void deep_unit(const FrameArgs& a, const Unit& u, int K_in, int off, int p0, int p1, float* rows,
                                            const int64_t* lofs, float* red) {
   using Q = Quad<FT>;
   using V = typename Q::V;
@@ -1499,7 +1516,6 @@ __device__ __forceinline__ float deep_unit(const FrameArgs& a, const Unit& u, in
   const FT* __restrict__ frag = static_cast<const FT*>(a.frag);
   float* tend = red + kDeepWaves * 3 * kDeepPx;
   float* asum = tend + kDeepPx;
-  float vs = 0.f;
   // Opaque copies, made anew in every group and phase: the addresses and
   // the l < K masks of a phase are computed there and not kept in registers
   // across the sort.
@@ -1633,6 +1649,7 @@ __device__ __forceinline__ float deep_unit(const FrameArgs& a, const Unit& u, in
             make_float4(acc[c][0], acc[c][1], acc[c][2], acc[c][3]);
     }
     lds_barrier();
+    float vs = 0.f;
     if (tid < kDeepPx && g0 + tid < p1) {
       float s[3] = {0.f, 0.f, 0.f};
 #pragma unroll
@@ -1641,10 +1658,13 @@ __device__ __forceinline__ float deep_unit(const FrameArgs& a, const Unit& u, in
         for (int c = 0; c < 3; ++c) s[c] += red[(w * 3 + c) * kDeepPx + tid];
       const int p = g0 + tid, ty = p / a.tile_w, tx = p - ty * a.tile_w;
       const bool inside = u.x0 + tx < a.width && u.y0 + ty < a.height;
-      vs += finish_px(a, u, p, inside, with_background(a, u.t, p, make_float4(s[0], s[1], s[2], asum[tid]), tend[tid]));
+      vs = finish_px(a, u, p, inside, with_background(a, u.t, p, make_float4(s[0], s[1], s[2], asum[tid]), tend[tid]));
+    }
+    if ((a.mode & kModeAccumulate) && wave == 0) {
+      vs = wave_sum(vs);
+      if (lane == 0) a.deep_partial[static_cast<size_t>(u.t) * a.deep_subs + g0 / kDeepPx] = vs;
     }
   }
-  return vs;
 }
 
 // Waves per SIMD the register allocation is held to: 512 layers need 74 KB of
@@ -1657,7 +1677,7 @@ __global__ void __launch_bounds__(kDeepThreads) __attribute__((amdgpu_waves_per_
 deep_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off, const int64_t* __restrict__ layer_off,
               const TileRec* __restrict__ recs) {
   extern __shared__ __align__(16) char lds[];
-  __shared__ int s_item;
+  __shared__ __align__(16) int4 s_next;
   const int tid = threadIdx.x;
   const bool wave0 = __builtin_amdgcn_readfirstlane(tid) < 64;  // uniform per wave
   FrameArgs a = args;
@@ -1666,55 +1686,61 @@ deep_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off, const int64_
   float* rows = reinterpret_cast<float*>(lds);
   int64_t* lofs = reinterpret_cast<int64_t*>(lds + deep_rows_bytes(a.deep_layers));
   float* red = reinterpret_cast<float*>(lofs + a.deep_layers);
+  // A unit is one group of kDeepPx pixels; a workgroup draws runs of them.
   const int home = static_cast<int>(blockIdx.x) % a.n_queues;
   Queue q = queue_of(a, home);
   uint64_t closed = 0;
-  const int r = static_cast<int>(blockIdx.x) / a.n_queues;
-  int it = r < q.n ? unit_at(a, q, r) : a.n_work;
-  while (it < a.n_work) {
-    const uint32_t next = wave0 && !a.one_each ? take_ticket(q) : 0u;
-    // position it of the launch's list: piece it % deep_subs of the tile at
-    // sorted position it / deep_subs
-    const int pos = it / a.deep_subs, piece = it - pos * a.deep_subs;
-    const TileRec rec = tile_rec(a, recs, tile_off, pos);
-    Unit u;
-    u.t = rec.tile;
-    u.sx0 = u.sy0 = 0;
-    u.y0 = (u.t / a.tiles_x) * a.tile_h;
-    u.x0 = (u.t - (u.t / a.tiles_x) * a.tiles_x) * a.tile_w;
-    const int off = rec.off, K = rec.layers;
-    const bool mine = K > kRegMax && K <= kDeepMax && K <= a.deep_layers;
-    if (mine) {
-      for (int i = tid; i < K; i += kDeepThreads) lofs[i] = layer_off[off + i];
-      lds_barrier();
-      const int p0 = piece * a.deep_px, p1 = p0 + a.deep_px < a.P ? p0 + a.deep_px : a.P;
-      float vs;
-      if (K <= 64) vs = deep_unit<FT, 4, RMAX>(a, u, K, off, p0, p1, rows, lofs, red);
-      else if (K <= 96) vs = deep_unit<FT, 6, RMAX>(a, u, K, off, p0, p1, rows, lofs, red);
-      else if (RMAX == 8 || K <= 128) vs = deep_unit<FT, 8, RMAX>(a, u, K, off, p0, p1, rows, lofs, red);
-      else if constexpr (RMAX >= 16) {
-        if (K <= 192) vs = deep_unit<FT, 12, RMAX>(a, u, K, off, p0, p1, rows, lofs, red);
-        else if (RMAX == 16 || K <= 256) vs = deep_unit<FT, 16, RMAX>(a, u, K, off, p0, p1, rows, lofs, red);
-        else if constexpr (RMAX >= 32) {
-          if (K <= 384) vs = deep_unit<FT, 24, RMAX>(a, u, K, off, p0, p1, rows, lofs, red);
-          else vs = deep_unit<FT, 32, RMAX>(a, u, K, off, p0, p1, rows, lofs, red);
+  int j = static_cast<int>(blockIdx.x) / a.n_queues * q.run, count = q.run;  // the run: units j .. j + count - 1 of q
+  if (j >= q.n) return;
+  for (;;) {
+    count = count < q.n - j ? count : q.n - j;
+    const int count_next = run_of(a, q.n - j - count, q.g);
+    const uint32_t next = wave0 && !a.one_each ? take_ticket(q, count_next) : 0u;
+    bool mine = true;
+    while (count > 0 && mine) {  // in two where a run goes over the end of a block or of a tile
+      const int it = unit_at(a, q, j), pos = it / a.deep_subs, piece = it - pos * a.deep_subs;
+      const int n = min(count, min(a.deep_subs - piece, a.queue_block - j % a.queue_block));
+      const TileRec rec = tile_rec(a, recs, tile_off, pos);
+      Unit u;
+      u.t = rec.tile;
+      u.sx0 = u.sy0 = 0;
+      u.y0 = (u.t / a.tiles_x) * a.tile_h;
+      u.x0 = (u.t - (u.t / a.tiles_x) * a.tiles_x) * a.tile_w;
+      const int off = rec.off, K = rec.layers;
+      mine = K > kRegMax;  // the list is in descending order of layers: a tile of few ends the counter
+      if (mine && K <= kDeepMax && K <= a.deep_layers) {
+        for (int i = tid; i < K; i += kDeepThreads) lofs[i] = layer_off[off + i];
+        lds_barrier();
+        const int p0 = piece * kDeepPx, p1 = p0 + n * kDeepPx < a.P ? p0 + n * kDeepPx : a.P;
+        if (K <= 64) deep_unit<FT, 4, RMAX>(a, u, K, off, p0, p1, rows, lofs, red);
+        else if (K <= 96) deep_unit<FT, 6, RMAX>(a, u, K, off, p0, p1, rows, lofs, red);
+        else if (RMAX == 8 || K <= 128) deep_unit<FT, 8, RMAX>(a, u, K, off, p0, p1, rows, lofs, red);
+        else if constexpr (RMAX >= 16) {
+          if (K <= 192) deep_unit<FT, 12, RMAX>(a, u, K, off, p0, p1, rows, lofs, red);
+          else if (RMAX == 16 || K <= 256) deep_unit<FT, 16, RMAX>(a, u, K, off, p0, p1, rows, lofs, red);
+          else if constexpr (RMAX >= 32) {
+            if (K <= 384) deep_unit<FT, 24, RMAX>(a, u, K, off, p0, p1, rows, lofs, red);
+            else deep_unit<FT, 32, RMAX>(a, u, K, off, p0, p1, rows, lofs, red);
+          }
         }
       }
-      if ((a.mode & kModeAccumulate) && wave0) {
-        vs = wave_sum(vs);
-        if (__lane_id() == 0) a.deep_partial[static_cast<size_t>(u.t) * a.deep_subs + piece] = vs;
-      }
+      j += n;
+      count -= n;
+      lds_barrier();  // the LDS rows and offsets are free; every lane has read s_next
     }
-    lds_barrier();  // every lane has read s_item; the LDS rows are free
     if (a.one_each) break;
     if (wave0) {
-      // the list is in descending order of layers: a tile of few ends the counter
-      int v = K > kRegMax ? ticket_to_unit(a, q, next) : a.n_work;
-      if (v == a.n_work) v = next_open_unit(a, q, closed);
-      if (__lane_id() == 0) s_item = v;
+      int jn = mine ? ticket_index(q, next) : -1, cn = count_next;
+      if (jn < 0) jn = next_open_unit(a, q, closed, cn);
+      if (__lane_id() == 0) s_next = {jn, cn, q.s, 0};
     }
     lds_barrier();
-    it = __builtin_amdgcn_readfirstlane(s_item);
+    const int4 sn = s_next;
+    j = __builtin_amdgcn_readfirstlane(sn.x);
+    if (j < 0) break;
+    count = __builtin_amdgcn_readfirstlane(sn.y);
+    const int counter = __builtin_amdgcn_readfirstlane(sn.z);
+    if (counter != q.s) q = queue_of(a, counter);  // wave 0 is there already
   }
 }
 

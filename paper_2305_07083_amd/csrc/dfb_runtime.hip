@@ -332,23 +332,15 @@ std::vector<Shape> candidates(const dfb_config& c, int max_k) {
 
 void drop_graphs(dfb_ctx* h);
 
-// Units of the row-sort launch: `px` consecutive pixels of a tile (whole
-// groups of kDeepPx), `subs` a tile.  A unit costs one ticket and loads its
-// tile's layer offsets, so larger is cheaper until the launch runs out of
-// units: 128 pixels, or fewer where that leaves fewer than four units to each
-// workgroup the chip holds (about two per compute unit).  2144 units of 128
-// pixels for three workgroups a compute unit (1500x1100 fp16) took 108 us, 4288
-// of 64 112, 8576 of 32 123.
-struct DeepUnits {
-  int px, subs;
-};
-DeepUnits deep_units(int P, int64_t deep_tiles, int n_cu) {
-  for (int px : {4 * dfb::kDeepPx, 2 * dfb::kDeepPx, dfb::kDeepPx}) {
-    const int subs = (P + px - 1) / px;
-    if (px == dfb::kDeepPx || deep_tiles * subs >= static_cast<int64_t>(8) * n_cu) return {px, subs};
-  }
-  return {dfb::kDeepPx, (P + dfb::kDeepPx - 1) / dfb::kDeepPx};
-}
+// Units of the row-sort launch in a tile: groups of kDeepPx pixels.  A
+// workgroup draws runs of up to kDeepRun of them (each run loads the tile's
+// layer offsets and starts its loads from cold), shorter ones as its counter
+// runs out; blocks of kDeepRun go round the counters, so that all of them hold
+// pieces of every tile.  1500x1100 fp16 (67 such tiles, 768 workgroups), the
+// launch: fixed units of 128 pixels 106 us, of 64 112, of 32 123; runs of up to
+// 4 groups 101, 8 90, 16 89; 8192^2: 12.3 ms with 128 pixels, 12.1, 12.0, 11.9.
+constexpr int kDeepRun = 16;
+int deep_subs(int P) { return (P + dfb::kDeepPx - 1) / dfb::kDeepPx; }
 
 // The row sort reads 4 pixels a lane: blocks and planes start at multiples
 // of P elements, so P and the base have to be aligned; else the LDS sort
@@ -360,7 +352,6 @@ bool has_deep(const dfb_ctx* h) {
   return h->cfg.tile_op == DFB_OP_ALPHA_BLEND && h->n_deep > h->n_big &&
          quad_aligned(h->frag, h->cfg.frag_dtype, h->P);
 }
-DeepUnits deep_units(const dfb_ctx* h) { return deep_units(h->P, h->n_deep, h->n_cu); }
 
 // Uploads a layout's layer offsets, tile records and tile offsets to a table
 // set, stream-ordered and in one copy (three, with an event each: 68 us a
@@ -449,7 +440,7 @@ dfb_status build_work(dfb_ctx* h, const Shape& s) {
   h->subs_per_tile = sx * sy;
   h->n_work = h->n_tiles * h->subs_per_tile;
   const size_t n = static_cast<size_t>(h->n_work);
-  dfb_status st = ensure(h, h->d_var_partial, h->partial_cap, n + static_cast<size_t>(h->n_tiles) * (h->n_deep ? deep_units(h).subs : 0));
+  dfb_status st = ensure(h, h->d_var_partial, h->partial_cap, n + static_cast<size_t>(h->n_tiles) * (h->n_deep ? deep_subs(h->P) : 0));
   if (st != DFB_OK) return st;
   h->work_valid = true;
   return DFB_OK;
@@ -473,6 +464,7 @@ FrameArgs base_args(const dfb_config& c, int tiles_x, int n_tiles, const Shape& 
   a.frag = frag;
   a.slot = a.clear_slot = 0;  // the kernel takes both from the device frame state
   a.n_queues = 1;             // set once the grid is known
+  a.max_run = 1;
   const int sx = c.tile_w / sh.work_w, sy = c.tile_h / sh.work_h;
   a.subs_x = sx;
   a.subs_per_tile = sx * sy;
@@ -545,7 +537,7 @@ dfb::VarianceArgs make_var_args(dfb_ctx* h) {
   v.var_partial = h->d_var_partial;
   v.deep_partial = h->d_var_partial + h->n_work;
   v.tile_off = h->d_off;
-  v.deep_subs = has_deep(h) ? deep_units(h).subs : 0;
+  v.deep_subs = has_deep(h) ? deep_subs(h->P) : 0;
   v.tile_var = h->tile_var;
   v.n_tiles = h->n_tiles;
   v.subs_per_tile = h->subs_per_tile;
@@ -619,7 +611,6 @@ struct FrameShape {
   int max_k, kcap, n_tiles, n_cu;
   int n_deep, n_big;
   bool big, deep;
-  DeepUnits du;
 };
 
 // The frame kernels of a frame (geometry args, queue allocation, tables and
@@ -644,10 +635,12 @@ dfb_status plan_kernels(dfb_ctx* h, const dfb_config& c, const FrameArgs& base, 
       K.func = dfb::deep_kernel(c.frag_dtype, fs.max_k);
       K.threads = dfb::kDeepThreads;
       K.lds = dfb::deep_lds_bytes(fs.max_k);
-      K.fa.deep_px = fs.du.px;
-      K.fa.deep_subs = K.fa.queue_block = fs.du.subs;
+      const int subs = deep_subs(base.P);
+      K.fa.deep_subs = subs;
+      K.fa.queue_block = std::min(subs, kDeepRun);
+      K.fa.max_run = kDeepRun;
       K.fa.deep_layers = dfb::deep_layers(fs.max_k);
-      K.fa.n_work = ((fs.n_deep < 0 ? fs.n_tiles : fs.n_deep) - first) * fs.du.subs;
+      K.fa.n_work = ((fs.n_deep < 0 ? fs.n_tiles : fs.n_deep) - first) * subs;
       K.recs = recs + first;
     } else {
       const int kc = ring == 1 ? 0 : fs.kcap;
@@ -675,8 +668,7 @@ dfb_status plan_kernels(dfb_ctx* h, const dfb_config& c, const FrameArgs& base, 
 dfb_status prepare_launch(dfb_ctx* h, uint32_t mode, FrameLaunch& L) {
   FrameArgs base = make_args(h, mode);
   const FrameShape fs{h->max_k, h->kcap, h->n_tiles, h->n_cu, h->n_deep, h->n_big,
-                      h->cfg.tile_op == DFB_OP_ALPHA_BLEND && (base.quad_ok ? h->n_big : h->n_deep) > 0, has_deep(h),
-                      deep_units(h)};
+                      h->cfg.tile_op == DFB_OP_ALPHA_BLEND && (base.quad_ok ? h->n_big : h->n_deep) > 0, has_deep(h)};
   dfb_status st = plan_kernels(h, h->cfg, base, h->d_queue_ring, h->shape, fs, h->d_off, h->d_block, h->d_recs, L);
   if (st != DFB_OK) return st;
   L.acc = (mode & dfb::kModeAccumulate) != 0;
@@ -696,7 +688,7 @@ dfb_status launch_frame(dfb_ctx* h, uint32_t mode, hipEvent_t t0 = nullptr, hipE
   if (st != DFB_OK) return st;
   if (t0) DFB_HIP(h, hipEventRecord(t0, h->stream));
   for (int i = 0; i < L.nk; ++i) {
-    if (skip_deep && L.k[i].fa.deep_px) continue;
+    if (skip_deep && L.k[i].fa.deep_subs) continue;
     DFB_HIP(h, hipLaunchKernel(L.k[i].func, dim3(L.k[i].grid), dim3(L.k[i].threads), L.k[i].params, L.k[i].lds,
                                h->stream));
   }
@@ -1514,7 +1506,7 @@ dfb_status dfb_composite_noalloc(const dfb_config* cfg, const void* frag_dev, co
   FrameLaunch L;
   const bool blend = cfg->tile_op == DFB_OP_ALPHA_BLEND;
   const FrameShape fs{max_layers, kcap_for(max_layers), n_tiles, n_cu, -1, -1, blend && max_layers > (a.quad_ok ? dfb::kDeepMax : dfb::kRegMax),
-                      blend && max_layers > dfb::kRegMax && a.quad_ok, deep_units(a.P, n_tiles, n_cu)};
+                      blend && max_layers > dfb::kRegMax && a.quad_ok};
   if ((s = plan_kernels(nullptr, *cfg, a, queue, sh, fs, tile_off_dev, layer_off_dev, recs, L)) != DFB_OK) return s;
   L.bind();
   if (L.nk == 1 && L.k[0].fa.one_each) {
