@@ -104,6 +104,7 @@ struct FrameArgs {
   int32_t n_queues;            // counters in use: min(kQueues, grid)
   int32_t queue_block;         // consecutive work-list positions per counter block (units per tile)
   int32_t n_work;
+  int32_t list_end;            // set by the kernel: no unit from here on is this launch's
   int32_t width, height, tiles_x, n_tiles;
   int32_t tile_w, tile_h, P;
   int32_t work_w, work_h, subs_x, subs_per_tile, work_px;

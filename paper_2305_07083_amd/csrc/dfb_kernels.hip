@@ -1157,6 +1157,7 @@ __device__ __forceinline__ Queue queue_of(const FrameArgs& a, int s) {
   q.g = (static_cast<int>(gridDim.x) - s + a.n_queues - 1) / a.n_queues;
   q.n = queue_units(a.n_work, a.queue_block, a.n_queues, s);
   q.run = run_of(a, q.n, q.g);
+  if (a.list_end < a.n_work) q.n = queue_units(a.list_end, a.queue_block, a.n_queues, s);
   q.ctr = a.queue + static_cast<size_t>(s) * kQueueStride + a.slot;
   return q;
 }
@@ -1247,6 +1248,7 @@ __device__ __forceinline__ uint32_t read_frame_state(FrameArgs& a) {
 __device__ __forceinline__ uint32_t use_frame_state(FrameArgs& a, uint32_t seq_in) {
   const uint32_t seq = __builtin_amdgcn_readfirstlane(seq_in);
   const int n_prev = static_cast<int>(__builtin_amdgcn_readfirstlane(a.n_acc));
+  a.list_end = a.n_work;
   a.slot = static_cast<int32_t>(seq % kSlots);
   a.clear_slot = static_cast<int32_t>((seq + kSlots / 2) % kSlots);
   a.n_acc = (a.mode & kModeAccumulate) ? n_prev + 1 : n_prev;
@@ -1314,6 +1316,7 @@ frame_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off,
   const int n_waves = static_cast<int>(blockDim.x >> 6);
   const bool wave0 = __builtin_amdgcn_readfirstlane(tid) < 64;  // uniform per wave
   FrameArgs a = args;
+  a.list_end = a.n_work;
   const uint32_t seq_read = read_frame_state(a);
   const int home = static_cast<int>(blockIdx.x) % a.n_queues;
   const int r = static_cast<int>(blockIdx.x) / a.n_queues;
@@ -1707,7 +1710,10 @@ deep_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off, const int64_
       u.y0 = (u.t / a.tiles_x) * a.tile_h;
       u.x0 = (u.t - (u.t / a.tiles_x) * a.tiles_x) * a.tile_w;
       const int off = rec.off, K = rec.layers;
-      mine = K > kRegMax;  // the list is in descending order of layers: a tile of few ends the counter
+      mine = K > kRegMax;
+      // the list is in descending order of layers: a tile of few ends it, for
+      // every counter (asking each in turn took 15 draws of every workgroup)
+      if (!mine) a.list_end = min(a.list_end, pos * a.deep_subs);
       if (mine && K <= kDeepMax && K <= a.deep_layers) {
         for (int i = tid; i < K; i += kDeepThreads) lofs[i] = layer_off[off + i];
         lds_barrier();
