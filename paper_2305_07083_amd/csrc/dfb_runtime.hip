@@ -591,7 +591,8 @@ struct FrameLaunch {
 // Work-queue counters of a launch whose grid is K.grid.  Where every counter's
 // units can have a workgroup of their own on the chip at once, the grid is
 // that large and the launch takes no tickets: small frames, whose time is the
-// latency of a unit, save its queue trips (@ONEEACH@).
+// latency of a unit, save its queue trips
+// (about 1 us each, at both ends).
 void set_queues(KernelLaunch& K, int grid_max) {
   FrameArgs& a = K.fa;
   a.n_queues = std::min(dfb::kQueues, K.grid);
