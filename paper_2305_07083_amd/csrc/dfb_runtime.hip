@@ -122,6 +122,7 @@ struct dfb_ctx {
   // launch shape
   Shape shape{0, 0, 0, 64 * 1024};
   bool shape_valid = false;
+  bool shape_standin = false;  // not chosen by timing: no launch of its layout depends on it
   int kcap = 8;
   int grid = 0;
   int n_work = 0;
@@ -795,7 +796,13 @@ dfb_status set_acc_count(dfb_ctx* h, int32_t value) {
   return DFB_OK;
 }
 
+// Whether the launches that the autotuner times have a unit.  It leaves the
+// row sort out, so with every tile in that launch there is nothing to time.
+bool shape_matters(const dfb_ctx* h) { return !has_deep(h) || h->n_big > 0 || h->n_deep < h->n_tiles; }
+
 dfb_status autotune(dfb_ctx* h) {
+  h->shape_standin = false;
+  if (!h->graphs.empty()) DFB_HIP(h, hipStreamSynchronize(h->stream));  // replays in flight hold the old shape
   AutotuneKey key{h->device,      h->cfg.width,   h->cfg.height,          h->cfg.tile_w,
                   h->cfg.tile_h,  h->cfg.frag_dtype, h->cfg.tile_op,      h->kcap,
                   layer_class(h->max_k), h->cfg.work_w, h->cfg.work_h, h->cfg.waves_per_tile};
@@ -809,6 +816,11 @@ dfb_status autotune(dfb_ctx* h) {
   if (it != g_autotune_cache.end()) {
     h->shape = it->second;
     h->shape_valid = true;
+    return build_work(h, h->shape);
+  }
+  if (!shape_matters(h)) {  // a stand-in, kept out of the cache: the layouts of the class that have other tiles are timed
+    h->shape = cands[0];
+    h->shape_valid = h->shape_standin = true;
     return build_work(h, h->shape);
   }
   hipEvent_t e0, e1;
@@ -860,8 +872,10 @@ dfb_status harvest(dfb_ctx* h, int slot) {
   return DFB_OK;
 }
 
-dfb_status prepare_shape(dfb_ctx* h) {
-  if (h->shape_valid && h->work_valid) return DFB_OK;
+// Under capture the caller has checked that a shape is there, and a stand-in
+// has to do.
+dfb_status prepare_shape(dfb_ctx* h, bool captured) {
+  if (h->shape_valid && h->work_valid && (captured || !h->shape_standin || !shape_matters(h))) return DFB_OK;
   return autotune(h);
 }
 
@@ -1156,7 +1170,11 @@ dfb_status dfb_set_fragments(dfb_handle h, const void* frag_dev, int64_t n_block
   if (!h->shape_valid) {
     // fixed shapes skip the autotuner
     auto c = candidates(h->cfg, max_k);
-    if (c.size() == 1) { h->shape = c[0]; h->shape_valid = true; }
+    if (c.size() == 1) {
+      h->shape = c[0];
+      h->shape_valid = true;
+      h->shape_standin = false;
+    }
   }
   if (h->shape_valid) {
     s = build_work(h, h->shape);
@@ -1255,7 +1273,7 @@ dfb_status dfb_composite_frame(dfb_handle h, uint32_t frame_flags) {
       return fail(h, DFB_ERR_STATE, "accumulate one frame before capturing an accumulating frame");
     if (replay) return fail(h, DFB_ERR_INVALID_ARG, "DFB_REPLAY cannot be captured");
   }
-  s = prepare_shape(h);
+  s = prepare_shape(h, captured);
   if (s != DFB_OK) return s;
   uint32_t mode = display_mode(h->cfg);
   if (h->cfg.flags & DFB_KEEP_FINISHED) mode |= dfb::kModeKeepFinished;
