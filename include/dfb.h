@@ -178,7 +178,10 @@ dfb_status dfb_set_fragments(dfb_handle h, const void* frag_dev, int64_t n_block
  * display pixels are those of this frame.
  * Tonemap: y = clamp(x,0,1) (NaN -> 0), colour ^ (1/gamma), code
  * floor(255 y + 0.5).  If work_w/waves_per_tile are 0, the first frame of a
- * new layer layout first autotunes them (synchronously).
+ * new layer layout first autotunes them (synchronously); so does the first
+ * frame of a layout with tiles of 33 to 512 layers whose fragment buffer is
+ * aligned to 4 pixels where the buffers before it were not, or the reverse
+ * (such tiles then take another kernel).
  * Per-frame state (the work queue's counter slot, the accumulation count)
  * lives in device memory and is advanced by the frame's own kernels, so the
  * launches of one call are the same for every frame of a layer table:

@@ -31,18 +31,23 @@ enum class State { kEmpty, kReady, kComposited };
 // padded size of the largest tile's sort), so a new layer layout of the same
 // class reuses it instead of autotuning again.  The caller's fixed work
 // unit and wave count (0 = tuned) are part of the key: they restrict the
-// candidates.
+// candidates.  So is the kernel that takes the tiles of kRegMax + 1 ..
+// kDeepMax layers (route, an index of dfb_ctx::tuned): the LDS sort's time
+// depends on the shape, the row sort's does not.
 struct AutotuneKey {
-  int device, width, height, tile_w, tile_h, dtype, op, kcap, lk, work_w, work_h, waves;
+  int device, width, height, tile_w, tile_h, dtype, op, kcap, lk, work_w, work_h, waves, route;
   bool operator<(const AutotuneKey& o) const {
-    return std::tie(device, width, height, tile_w, tile_h, dtype, op, kcap, lk, work_w, work_h, waves) <
+    return std::tie(device, width, height, tile_w, tile_h, dtype, op, kcap, lk, work_w, work_h, waves, route) <
            std::tie(o.device, o.width, o.height, o.tile_w, o.tile_h, o.dtype, o.op, o.kcap, o.lk, o.work_w,
-                    o.work_h, o.waves);
+                    o.work_h, o.waves, o.route);
   }
 };
 struct Shape {
   int work_w, work_h, waves;
   int big_lds;  // LDS budget of the LDS sort
+  bool operator==(const Shape& o) const {
+    return work_w == o.work_w && work_h == o.work_h && waves == o.waves && big_lds == o.big_lds;
+  }
 };
 std::map<AutotuneKey, Shape> g_autotune_cache;
 
@@ -109,7 +114,7 @@ struct dfb_ctx {
   dfb::FrameState* d_state = nullptr;  // inside d_queue_ring
 
   // Frame graphs for DFB_REPLAY: one per (fragment buffer, frame mode) of the
-  // current layer table and launch shape; dropped when either changes.
+  // current layer table; dropped when it changes or a shape is chosen anew.
   struct GraphEntry {
     const void* frag;
     uint32_t mode;
@@ -119,10 +124,16 @@ struct dfb_ctx {
   static constexpr int kMaxGraphs = 8;
   std::vector<GraphEntry> graphs;
 
-  // launch shape
+  // launch shape: the one in use, and the ones chosen for the layer-count class
+  // where the LDS sort ([0]) and where the row sort ([1]) takes the tiles of
+  // kRegMax + 1 .. kDeepMax layers, which the fragment buffer's alignment
+  // decides; [1] too where there are none
   Shape shape{0, 0, 0, 64 * 1024};
-  bool shape_valid = false;
-  bool shape_standin = false;  // not chosen by timing: no launch of its layout depends on it
+  struct {
+    Shape shape;
+    bool valid;
+    bool standin;  // not chosen by timing: no launch of its layout depends on it
+  } tuned[2] = {};
   int kcap = 8;
   int grid = 0;
   int n_work = 0;
@@ -304,7 +315,7 @@ int layer_class(int max_k) {
 // (frames whose deepest tiles the LDS sort takes) a small or a large LDS
 // budget for the LDS sort -- two workgroups per CU, or one with twice the
 // pixels per sorting group.
-std::vector<Shape> candidates(const dfb_config& c, int max_k) {
+std::vector<Shape> candidates(const dfb_config& c, int max_k, int route) {
   std::vector<std::pair<int, int>> sizes;
   if (c.work_w) {
     sizes.push_back({c.work_w, c.work_h});
@@ -322,8 +333,7 @@ std::vector<Shape> candidates(const dfb_config& c, int max_k) {
   if (c.waves_per_tile) waves.push_back(c.waves_per_tile);
   else waves = {1, 2, 4};
   std::vector<int> ldss{dfb::big_lds_bytes(max_k)};
-  const bool row_sort = (static_cast<int64_t>(c.tile_w) * c.tile_h) % 4 == 0;
-  if (max_k > (row_sort ? dfb::kDeepMax : 128) && c.tile_op == DFB_OP_ALPHA_BLEND) ldss.push_back(64 * 1024);
+  if (max_k > (route ? dfb::kDeepMax : 128) && c.tile_op == DFB_OP_ALPHA_BLEND) ldss.push_back(64 * 1024);
   std::vector<Shape> out;
   for (auto& s : sizes)
     for (int w : waves)
@@ -349,10 +359,10 @@ int deep_subs(int P) { return (P + dfb::kDeepPx - 1) / dfb::kDeepPx; }
 bool quad_aligned(const void* frag, int dtype, int P) {
   return P % 4 == 0 && reinterpret_cast<uintptr_t>(frag) % (dtype == DFB_F16 ? 8 : 16) == 0;
 }
-bool has_deep(const dfb_ctx* h) {
-  return h->cfg.tile_op == DFB_OP_ALPHA_BLEND && h->n_deep > h->n_big &&
-         quad_aligned(h->frag, h->cfg.frag_dtype, h->P);
-}
+// Tiles of a layout that one or the other takes.
+bool deep_tiles(const dfb_ctx* h) { return h->cfg.tile_op == DFB_OP_ALPHA_BLEND && h->n_deep > h->n_big; }
+bool has_deep(const dfb_ctx* h) { return deep_tiles(h) && quad_aligned(h->frag, h->cfg.frag_dtype, h->P); }
+int route_of(const dfb_ctx* h) { return !deep_tiles(h) || has_deep(h); }
 
 // Uploads a layout's layer offsets, tile records and tile offsets to a table
 // set, stream-ordered and in one copy (three, with an event each: 68 us a
@@ -433,15 +443,19 @@ void free_tables(dfb_ctx* h) {
   }
 }
 
-// The units of the current layout with a launch shape.
+// The units of the current layout with a launch shape.  Graphs keep the shape
+// they were built with, and go only when the partial sums move.
 dfb_status build_work(dfb_ctx* h, const Shape& s) {
-  drop_graphs(h);
   const int sx = h->cfg.tile_w / s.work_w, sy = h->cfg.tile_h / s.work_h;
   h->subs_x = sx;
   h->subs_per_tile = sx * sy;
   h->n_work = h->n_tiles * h->subs_per_tile;
-  const size_t n = static_cast<size_t>(h->n_work);
-  dfb_status st = ensure(h, h->d_var_partial, h->partial_cap, n + static_cast<size_t>(h->n_tiles) * (h->n_deep ? deep_subs(h->P) : 0));
+  const size_t n = static_cast<size_t>(h->n_work) + static_cast<size_t>(h->n_tiles) * (h->n_deep ? deep_subs(h->P) : 0);
+  if (n > h->partial_cap && !h->graphs.empty()) {
+    DFB_HIP(h, hipStreamSynchronize(h->stream));
+    drop_graphs(h);
+  }
+  dfb_status st = ensure(h, h->d_var_partial, h->partial_cap, n);
   if (st != DFB_OK) return st;
   h->work_valid = true;
   return DFB_OK;
@@ -800,29 +814,27 @@ dfb_status set_acc_count(dfb_ctx* h, int32_t value) {
 // row sort out, so with every tile in that launch there is nothing to time.
 bool shape_matters(const dfb_ctx* h) { return !has_deep(h) || h->n_big > 0 || h->n_deep < h->n_tiles; }
 
+dfb_status use_shape(dfb_ctx* h, const Shape& s, bool standin = false) {
+  const int r = route_of(h);
+  h->tuned[r].shape = h->shape = s;
+  h->tuned[r].valid = true;
+  h->tuned[r].standin = standin;
+  return build_work(h, s);
+}
+
 dfb_status autotune(dfb_ctx* h) {
-  h->shape_standin = false;
+  const int route = route_of(h);
   if (!h->graphs.empty()) DFB_HIP(h, hipStreamSynchronize(h->stream));  // replays in flight hold the old shape
+  drop_graphs(h);
   AutotuneKey key{h->device,      h->cfg.width,   h->cfg.height,          h->cfg.tile_w,
                   h->cfg.tile_h,  h->cfg.frag_dtype, h->cfg.tile_op,      h->kcap,
-                  layer_class(h->max_k), h->cfg.work_w, h->cfg.work_h, h->cfg.waves_per_tile};
-  auto cands = candidates(h->cfg, h->max_k);
-  if (cands.size() == 1) {
-    h->shape = cands[0];
-    h->shape_valid = true;
-    return build_work(h, h->shape);
-  }
+                  layer_class(h->max_k), h->cfg.work_w, h->cfg.work_h, h->cfg.waves_per_tile, route};
+  auto cands = candidates(h->cfg, h->max_k, route);
+  if (cands.size() == 1) return use_shape(h, cands[0]);
   auto it = g_autotune_cache.find(key);
-  if (it != g_autotune_cache.end()) {
-    h->shape = it->second;
-    h->shape_valid = true;
-    return build_work(h, h->shape);
-  }
-  if (!shape_matters(h)) {  // a stand-in, kept out of the cache: the layouts of the class that have other tiles are timed
-    h->shape = cands[0];
-    h->shape_valid = h->shape_standin = true;
-    return build_work(h, h->shape);
-  }
+  if (it != g_autotune_cache.end()) return use_shape(h, it->second);
+  // a stand-in, kept out of the cache: the layouts of the class that have other tiles are timed
+  if (!shape_matters(h)) return use_shape(h, cands[0], true);
   hipEvent_t e0, e1;
   DFB_HIP(h, hipEventCreate(&e0));
   DFB_HIP(h, hipEventCreate(&e1));
@@ -856,9 +868,7 @@ dfb_status autotune(dfb_ctx* h) {
   DFB_HIP(h, hipEventDestroy(e0));
   DFB_HIP(h, hipEventDestroy(e1));
   g_autotune_cache[key] = best_s;
-  h->shape = best_s;
-  h->shape_valid = true;
-  return build_work(h, best_s);
+  return use_shape(h, best_s);
 }
 
 dfb_status harvest(dfb_ctx* h, int slot) {
@@ -872,11 +882,16 @@ dfb_status harvest(dfb_ctx* h, int slot) {
   return DFB_OK;
 }
 
-// Under capture the caller has checked that a shape is there, and a stand-in
-// has to do.
+// The shape of the current layout and buffer: chosen, or chosen before and
+// switched to.  Under capture the caller has checked that units were built, and
+// the shape in use has to do: nothing may be timed or allocated.
 dfb_status prepare_shape(dfb_ctx* h, bool captured) {
-  if (h->shape_valid && h->work_valid && (captured || !h->shape_standin || !shape_matters(h))) return DFB_OK;
-  return autotune(h);
+  if (captured) return DFB_OK;
+  const auto& T = h->tuned[route_of(h)];
+  if (!T.valid || (T.standin && shape_matters(h))) return autotune(h);
+  if (h->work_valid && h->shape == T.shape) return DFB_OK;
+  h->shape = T.shape;
+  return build_work(h, h->shape);
 }
 
 // Device NaN scan of every layer's depth plane (DFB_VALIDATE).  Uses the
@@ -1154,7 +1169,7 @@ dfb_status dfb_set_fragments(dfb_handle h, const void* frag_dev, int64_t n_block
   h->d_recs = T.recs;
   // a new launch shape only for a new layer-count class
   if (h->state == State::kEmpty || kcap_for(max_k) != h->kcap || layer_class(max_k) != layer_class(h->max_k))
-    h->shape_valid = false;
+    h->tuned[0].valid = h->tuned[1].valid = false;
   h->h_off.swap(off);
   h->n_layers = n_layers;
   h->n_blocks = n_blocks;
@@ -1167,16 +1182,15 @@ dfb_status dfb_set_fragments(dfb_handle h, const void* frag_dev, int64_t n_block
   h->last_had_expected = expected != nullptr;
   if (expected) h->last_expected.assign(expected, expected + h->n_tiles);
   h->work_valid = false;
-  if (!h->shape_valid) {
+  const int route = route_of(h);
+  if (!h->tuned[route].valid) {
     // fixed shapes skip the autotuner
-    auto c = candidates(h->cfg, max_k);
-    if (c.size() == 1) {
-      h->shape = c[0];
-      h->shape_valid = true;
-      h->shape_standin = false;
-    }
+    auto c = candidates(h->cfg, max_k, route);
+    if (c.size() == 1) h->tuned[route] = {c[0], true, false};
   }
-  if (h->shape_valid) {
+  // where only the other route's is known, a capture has that one to use
+  if (h->tuned[route].valid || h->tuned[1 - route].valid) {
+    h->shape = h->tuned[h->tuned[route].valid ? route : 1 - route].shape;
     s = build_work(h, h->shape);
     if (s != DFB_OK) return s;
   }
@@ -1266,7 +1280,7 @@ dfb_status dfb_composite_frame(dfb_handle h, uint32_t frame_flags) {
   // the launch shape and the accumulation buffers must already exist.
   const bool captured = capturing(h);
   if (captured) {
-    if (!(h->shape_valid && h->work_valid))
+    if (!h->work_valid)
       return fail(h, DFB_ERR_STATE, "the first frame of a new layer layout chooses the launch shape "
                                     "(synchronously): composite it before capturing");
     if (acc && !h->accum)

@@ -98,3 +98,56 @@ def test_stand_in_under_capture():
             check(dfb, c, mixed)
         c.composite()
         check(dfb, c, mixed)
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+def test_buffers_of_both_alignments(dtype):
+    """Planes off a 4-pixel boundary send the tiles of more than 32 layers to
+    the LDS sort, whose time depends on the shape: such a buffer's first frame
+    chooses for itself (or takes the choice from the cache), then buffers of both
+    kinds in turn choose nothing, launched or replayed, each with its own result
+    and its own shape, and under capture the shape at hand is used."""
+    torch = torch_dev()
+    import paper_2305_07083_amd as dfb
+    f = frame([40, 3, 60, 9, 64, 33, 35], 6 + np.dtype(dtype).itemsize).as_dtype(dtype)
+    cfg = dfb.make_config(f.width, f.height, 64, background=BG, fmt=dfb.DFB_FMT_RGBAF32,
+                          dtype=dfb.DFB_F16 if dtype == np.float16 else dfb.DFB_F32)
+    n = f.frag.size
+    raw = torch.zeros(n + 1, dtype=torch.from_numpy(f.frag[:0]).dtype, device="cuda:0")
+    bufs = [upload(f.frag), raw[1:]]
+    raw[1:].copy_(bufs[0].reshape(-1))
+    torch.cuda.synchronize()
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s), dfb.Compositor(cfg, s.cuda_stream) as c:
+        shapes = []
+        for d in bufs:
+            c.set_fragments(d, f.frag.shape[0], f.layers, f.expected)
+            assert chooses(dfb, c)
+            check(dfb, c, f)
+            shapes.append((c.info().work_w, c.info().work_h, c.info().waves_per_tile))
+        for replay in (False, True):
+            for k in range(6):
+                c.set_fragments(bufs[k % 2], f.frag.shape[0], f.layers, f.expected)
+                if replay:
+                    c.composite(replay=True)
+                else:
+                    assert not chooses(dfb, c)
+                    assert shapes[k % 2] == (c.info().work_w, c.info().work_h, c.info().waves_per_tile)
+                check(dfb, c, f)
+        c.set_fragments(bufs[0], f.frag.shape[0], f.layers, f.expected)
+        c.composite()
+        c.set_fragments(bufs[1], f.frag.shape[0], f.layers, f.expected)
+        s.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            c.composite()
+        for _ in range(3):
+            graph.replay()
+            s.synchronize()
+            check(dfb, c, f)
+    with dfb.Compositor(cfg, stream_handle()) as c:  # each from the cache
+        for k in (1, 0, 1):
+            c.set_fragments(bufs[k], f.frag.shape[0], f.layers, f.expected)
+            c.composite()
+            assert shapes[k] == (c.info().work_w, c.info().work_h, c.info().waves_per_tile)
+            check(dfb, c, f)
