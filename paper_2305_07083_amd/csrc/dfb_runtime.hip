@@ -107,8 +107,8 @@ struct dfb_ctx {
   int32_t* d_off = nullptr;    // the current set's arrays
   int64_t* d_block = nullptr;
   dfb::TileRec* d_recs = nullptr;
-  float* d_var_partial = nullptr;
-  size_t partial_cap = 0;
+  float* d_var_partial = nullptr;   // with the accumulation: partial M2 sums of the units,
+  float* d_deep_partial = nullptr;  // and of the row sort's groups
   uint32_t* d_flag = nullptr;
   uint32_t* d_queue_ring = nullptr;  // kQueues x kSlots counters, finish counters, FrameState
   dfb::FrameState* d_state = nullptr;  // inside d_queue_ring
@@ -444,30 +444,34 @@ void free_tables(dfb_ctx* h) {
 }
 
 // The units of the current layout with a launch shape.  Graphs keep the shape
-// they were built with, and go only when the partial sums move.
-dfb_status build_work(dfb_ctx* h, const Shape& s) {
+// they were built with.
+void build_work(dfb_ctx* h, const Shape& s) {
   const int sx = h->cfg.tile_w / s.work_w, sy = h->cfg.tile_h / s.work_h;
   h->subs_x = sx;
   h->subs_per_tile = sx * sy;
   h->n_work = h->n_tiles * h->subs_per_tile;
-  const size_t n = static_cast<size_t>(h->n_work) + static_cast<size_t>(h->n_tiles) * (h->n_deep ? deep_subs(h->P) : 0);
-  if (n > h->partial_cap && !h->graphs.empty()) {
-    DFB_HIP(h, hipStreamSynchronize(h->stream));
-    drop_graphs(h);
-  }
-  dfb_status st = ensure(h, h->d_var_partial, h->partial_cap, n);
-  if (st != DFB_OK) return st;
   h->work_valid = true;
-  return DFB_OK;
 }
 
+// The accumulation and the partial sums of its variance, sized for every
+// layout and launch shape, so that they stay where they are: graphs that the
+// caller captured hold their addresses.
 dfb_status ensure_accum(dfb_ctx* h) {
-  if (h->accum) return DFB_OK;
+  if (h->accum) return DFB_OK;  // allocated last
   const size_t px = static_cast<size_t>(h->n_tiles) * h->P;
-  dfb_status s = alloc_plain(h, reinterpret_cast<void**>(&h->accum), px * 16);
-  if (s != DFB_OK) return s;
-  s = alloc_plain(h, reinterpret_cast<void**>(&h->m2), px * 12);
-  if (s != DFB_OK) return s;
+  size_t units = 0;
+  for (const Shape& s : candidates(h->cfg, 0, 1))
+    units = std::max(units, static_cast<size_t>(h->n_tiles) * (h->cfg.tile_w / s.work_w) * (h->cfg.tile_h / s.work_h));
+  const size_t groups = h->cfg.tile_op == DFB_OP_ALPHA_BLEND && h->P % 4 == 0 ? static_cast<size_t>(h->n_tiles) * deep_subs(h->P) : 0;
+  struct {
+    float** p;
+    size_t bytes;
+  } bufs[] = {{&h->m2, px * 12}, {&h->d_var_partial, units * 4}, {&h->d_deep_partial, groups * 4}, {&h->accum, px * 16}};
+  for (auto& b : bufs) {
+    if (*b.p) continue;
+    const dfb_status s = alloc_plain(h, reinterpret_cast<void**>(b.p), b.bytes);
+    if (s != DFB_OK) return s;
+  }
   return DFB_OK;
 }
 
@@ -521,7 +525,7 @@ FrameArgs make_args(dfb_ctx* h, uint32_t mode) {
   a.m2 = h->m2;
   a.tile_var = h->tile_var;
   a.var_partial = h->d_var_partial;
-  a.deep_partial = h->d_var_partial + h->n_work;
+  a.deep_partial = h->d_deep_partial;
   a.final_out = h->final_out;
   a.order = h->order;
   return a;
@@ -550,7 +554,7 @@ dfb_status grid_of(dfb_ctx* h, const void* func, int threads, size_t lds, int n_
 dfb::VarianceArgs make_var_args(dfb_ctx* h) {
   dfb::VarianceArgs v{};
   v.var_partial = h->d_var_partial;
-  v.deep_partial = h->d_var_partial + h->n_work;
+  v.deep_partial = h->d_deep_partial;
   v.tile_off = h->d_off;
   v.deep_subs = has_deep(h) ? deep_subs(h->P) : 0;
   v.tile_var = h->tile_var;
@@ -814,12 +818,12 @@ dfb_status set_acc_count(dfb_ctx* h, int32_t value) {
 // row sort out, so with every tile in that launch there is nothing to time.
 bool shape_matters(const dfb_ctx* h) { return !has_deep(h) || h->n_big > 0 || h->n_deep < h->n_tiles; }
 
-dfb_status use_shape(dfb_ctx* h, const Shape& s, bool standin = false) {
+void use_shape(dfb_ctx* h, const Shape& s, bool standin = false) {
   const int r = route_of(h);
   h->tuned[r].shape = h->shape = s;
   h->tuned[r].valid = true;
   h->tuned[r].standin = standin;
-  return build_work(h, s);
+  build_work(h, s);
 }
 
 dfb_status autotune(dfb_ctx* h) {
@@ -830,11 +834,15 @@ dfb_status autotune(dfb_ctx* h) {
                   h->cfg.tile_h,  h->cfg.frag_dtype, h->cfg.tile_op,      h->kcap,
                   layer_class(h->max_k), h->cfg.work_w, h->cfg.work_h, h->cfg.waves_per_tile, route};
   auto cands = candidates(h->cfg, h->max_k, route);
-  if (cands.size() == 1) return use_shape(h, cands[0]);
   auto it = g_autotune_cache.find(key);
-  if (it != g_autotune_cache.end()) return use_shape(h, it->second);
-  // a stand-in, kept out of the cache: the layouts of the class that have other tiles are timed
-  if (!shape_matters(h)) return use_shape(h, cands[0], true);
+  if (cands.size() == 1 || it != g_autotune_cache.end() || !shape_matters(h)) {
+    // without a choice to make, a stand-in that the cache does not keep: the
+    // layouts of the class that have other tiles are timed
+    if (cands.size() == 1) use_shape(h, cands[0]);
+    else if (it != g_autotune_cache.end()) use_shape(h, it->second);
+    else use_shape(h, cands[0], true);
+    return DFB_OK;
+  }
   hipEvent_t e0, e1;
   DFB_HIP(h, hipEventCreate(&e0));
   DFB_HIP(h, hipEventCreate(&e1));
@@ -843,13 +851,12 @@ dfb_status autotune(dfb_ctx* h) {
   const uint32_t mode = display_mode(h->cfg);
   for (const Shape& s : cands) {
     h->shape = s;
-    dfb_status st = build_work(h, s);
-    if (st != DFB_OK) return st;
+    build_work(h, s);
     std::vector<float> times;
     int warm = 5, timed = 5;  // frames longer than 5 ms: 1 warm-up, 3 timed
     for (int r = 0; r < warm + timed; ++r) {
       DFB_HIP(h, hipEventRecord(e0, h->stream));
-      st = launch_frame(h, mode, nullptr, nullptr, true);
+      const dfb_status st = launch_frame(h, mode, nullptr, nullptr, true);
       if (st != DFB_OK) return st;
       DFB_HIP(h, hipEventRecord(e1, h->stream));
       DFB_HIP(h, hipEventSynchronize(e1));
@@ -868,7 +875,8 @@ dfb_status autotune(dfb_ctx* h) {
   DFB_HIP(h, hipEventDestroy(e0));
   DFB_HIP(h, hipEventDestroy(e1));
   g_autotune_cache[key] = best_s;
-  return use_shape(h, best_s);
+  use_shape(h, best_s);
+  return DFB_OK;
 }
 
 dfb_status harvest(dfb_ctx* h, int slot) {
@@ -889,9 +897,11 @@ dfb_status prepare_shape(dfb_ctx* h, bool captured) {
   if (captured) return DFB_OK;
   const auto& T = h->tuned[route_of(h)];
   if (!T.valid || (T.standin && shape_matters(h))) return autotune(h);
-  if (h->work_valid && h->shape == T.shape) return DFB_OK;
-  h->shape = T.shape;
-  return build_work(h, h->shape);
+  if (!h->work_valid || !(h->shape == T.shape)) {
+    h->shape = T.shape;
+    build_work(h, h->shape);
+  }
+  return DFB_OK;
 }
 
 // Device NaN scan of every layer's depth plane (DFB_VALIDATE).  Uses the
@@ -1077,7 +1087,7 @@ dfb_status dfb_destroy(dfb_handle h) {
     if (h->ev1[i]) (void)hipEventDestroy(h->ev1[i]);
   }
   void* bufs[] = {h->finished, h->accum, h->m2, h->tile_var, h->final_out, h->order, h->denoised,
-                  h->d_var_partial, h->d_queue_ring, h->d_flag};
+                  h->d_var_partial, h->d_deep_partial, h->d_queue_ring, h->d_flag};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
   free_tables(h);
@@ -1191,8 +1201,7 @@ dfb_status dfb_set_fragments(dfb_handle h, const void* frag_dev, int64_t n_block
   // where only the other route's is known, a capture has that one to use
   if (h->tuned[route].valid || h->tuned[1 - route].valid) {
     h->shape = h->tuned[h->tuned[route].valid ? route : 1 - route].shape;
-    s = build_work(h, h->shape);
-    if (s != DFB_OK) return s;
+    build_work(h, h->shape);
   }
   h->state = State::kReady;
   return DFB_OK;
