@@ -196,7 +196,8 @@ dfb_status dfb_set_fragments(dfb_handle h, const void* frag_dev, int64_t n_block
  *    chosen yet (composite one frame first) or, with DFB_ACCUMULATE, if no
  *    frame was accumulated yet; it does no timing.  The graph holds the
  *    fragment buffer given to the last dfb_set_fragments and the layer
- *    table: replays see what those hold when they run.
+ *    table: replays see what those hold when they run.  A handle has two
+ *    tables, which its layouts use in turn: capture again for another layout.
  * Errors: before any dfb_set_fragments -> DFB_ERR_STATE; unknown flags ->
  * DFB_ERR_INVALID_ARG. */
 dfb_status dfb_composite_frame(dfb_handle h, uint32_t frame_flags);

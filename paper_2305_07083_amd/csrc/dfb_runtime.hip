@@ -85,8 +85,8 @@ struct dfb_ctx {
   std::vector<dfb_layer> last_layers;
   std::vector<int32_t> last_expected;
   bool last_had_expected = false;
-  // Two sets of device layer tables (layer offsets, the tiles most layers first,
-  // per-tile offsets, in one allocation), used by successive layer layouts in turn, each
+  // Two sets of device layer tables (the tiles most layers first, per-tile
+  // offsets, layer offsets, in one allocation), used by successive layer layouts in turn, each
   // uploaded from pinned host staging with one copy: a new layout is written to
   // the set the frames in flight do not read, so its upload needs no wait for
   // them.  A set, and its staging, is reused two layouts later, after the event
@@ -94,9 +94,9 @@ struct dfb_ctx {
   struct Tables {
     char* dev = nullptr;
     size_t cap = 0;
-    int64_t* block = nullptr;      // the arrays in dev
-    dfb::TileRec* recs = nullptr;
+    dfb::TileRec* recs = nullptr;  // the arrays in dev
     int32_t* off = nullptr;
+    int64_t* block = nullptr;
     char* st = nullptr;            // pinned staging
     size_t st_cap = 0;
     bool staged = false;           // an upload may still read the staging
@@ -369,9 +369,11 @@ int route_of(const dfb_ctx* h) { return !deep_tiles(h) || has_deep(h); }
 // 1024x1024 frame, 51 now).  Only called on a set no frame in flight reads.
 dfb_status upload_tables(dfb_ctx* h, dfb_ctx::Tables& S, const std::vector<int64_t>& block,
                          const std::vector<int32_t>& off, int max_k) {
-  const size_t block_bytes = (block.size() * sizeof(int64_t) + 15) / 16 * 16;
-  const size_t rec_bytes = static_cast<size_t>(h->n_tiles) * sizeof(dfb::TileRec), off_bytes = off.size() * sizeof(int32_t);
-  const size_t bytes = block_bytes + rec_bytes + off_bytes;
+  // the arrays whose size is the handle's come first: all of them stay where
+  // they are until the set grows, for graphs that hold their addresses
+  const size_t rec_bytes = static_cast<size_t>(h->n_tiles) * sizeof(dfb::TileRec);
+  const size_t off_bytes = (off.size() * sizeof(int32_t) + 7) / 8 * 8;
+  const size_t bytes = rec_bytes + off_bytes + block.size() * sizeof(int64_t);
   if (S.staged) {  // a layout that was refused after its upload
     DFB_HIP(h, hipStreamSynchronize(h->stream));
     S.staged = false;
@@ -400,8 +402,8 @@ dfb_status upload_tables(dfb_ctx* h, dfb_ctx::Tables& S, const std::vector<int64
     }
     S.st_cap = cap;
   }
-  if (!block.empty()) std::memcpy(S.st, block.data(), block.size() * sizeof(int64_t));
-  dfb::TileRec* recs = reinterpret_cast<dfb::TileRec*>(S.st + block_bytes);
+  if (!block.empty()) std::memcpy(S.st + rec_bytes + off_bytes, block.data(), block.size() * sizeof(int64_t));
+  dfb::TileRec* recs = reinterpret_cast<dfb::TileRec*>(S.st);
   // counting sort by layers: at[K] is the next list position of a tile of K
   std::vector<int32_t> at(max_k + 1, 0);
   for (int t = 0; t < h->n_tiles; ++t) ++at[off[t + 1] - off[t]];
@@ -415,7 +417,7 @@ dfb_status upload_tables(dfb_ctx* h, dfb_ctx::Tables& S, const std::vector<int64
     const int32_t k = off[t + 1] - off[t];
     recs[at[k]++] = {t, off[t], k, 0};
   }
-  std::memcpy(S.st + block_bytes + rec_bytes, off.data(), off_bytes);
+  std::memcpy(S.st + rec_bytes, off.data(), off.size() * sizeof(int32_t));
   // by a kernel that reads the staging over the bus: the runtime gives a copy
   // of more than a few pages to a DMA engine, and the frame kernel then starts
   // 18 us later (1024x1024, every frame a new layout: 60 us a frame, 51 by the
@@ -428,9 +430,9 @@ dfb_status upload_tables(dfb_ctx* h, dfb_ctx::Tables& S, const std::vector<int64
   DFB_HIP(h, hipLaunchKernel(dfb::copy_u32_kernel(), dim3(static_cast<unsigned>(std::min<int64_t>((words + 255) / 256, 1024))),
                              dim3(256), params, 0, h->stream));
   S.staged = true;
-  S.block = reinterpret_cast<int64_t*>(S.dev);
-  S.recs = reinterpret_cast<dfb::TileRec*>(S.dev + block_bytes);
-  S.off = reinterpret_cast<int32_t*>(S.dev + block_bytes + rec_bytes);
+  S.recs = reinterpret_cast<dfb::TileRec*>(S.dev);
+  S.off = reinterpret_cast<int32_t*>(S.dev + rec_bytes);
+  S.block = reinterpret_cast<int64_t*>(S.dev + rec_bytes + off_bytes);
   return DFB_OK;
 }
 
