@@ -1237,11 +1237,11 @@ __device__ __forceinline__ FrameState* frame_state(const FrameArgs& a) { return 
 // the device state.  Nothing waits for them until they are used, so the
 // unit's table reads run meanwhile.  The last workgroup to finish advances the
 // state after every workgroup's wave 0 has counted it finished, so a read whose
-// value matters has to come before its workgroup's count: wave 0 uses its
-// own values before it counts; the other waves use theirs only in a unit
-// (n_acc), which ends at a barrier with wave 0.  A workgroup without a unit
-// passes no barrier, and its other waves may read the advanced state: they use
-// neither value.
+// value is used has to come before its workgroup's count: a wave has its values
+// before the barrier that ends its first unit.  Workgroup 0 recycles slots with
+// every wave's value whether it has a unit or not; where it has none (a launch
+// without units, every tile being deep) the host launches one wave, which reads
+// before it counts.
 __device__ __forceinline__ uint32_t read_frame_state(FrameArgs& a) {
   const FrameState* st = frame_state(a);
   const uint32_t seq = __hip_atomic_load(&st->seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1262,12 +1262,10 @@ __device__ __forceinline__ uint32_t use_frame_state(FrameArgs& a, uint32_t seq_i
 // Recycle the slot of the frame kSlots/2 ahead (counters, finish counts) in
 // every ring.  The frame's last launch does it for all of them: a frame of
 // another layer layout may not run the other launches, and a slot left
-// uncleared would hand out no units kSlots frames later.  Wave 0 only: it
-// has read the sequence number before it counts its workgroup finished (with
-// every tile deep this launch has no unit, and no barrier before the count).
+// uncleared would hand out no units kSlots frames later.
 __device__ __forceinline__ void recycle_slots(const FrameArgs& a) {
   constexpr int kPages = kRings * (kQueues + 1);
-  for (int i = static_cast<int>(__lane_id()); i < 2 * kPages; i += 64)  // a page's ticket and finish counters
+  for (int i = threadIdx.x; i < 2 * kPages; i += blockDim.x)  // a page's ticket and finish counters
     __hip_atomic_store(a.rings + static_cast<size_t>(i % kPages) * kQueueStride + (i / kPages) * kFinishWord + a.clear_slot,
                        0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -1332,7 +1330,7 @@ frame_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off,
   if (it < a.n_work) rec = tile_rec(a, recs, tile_off, it / a.subs_per_tile);
   const uint32_t seq = use_frame_state(a, seq_read);
   q.ctr += a.slot;
-  if (kLast && blockIdx.x == 0 && wave0) recycle_slots(a);
+  if (kLast && blockIdx.x == 0) recycle_slots(a);
   uint64_t closed = 0;  // counters this workgroup has found empty
   int turn = 0;
   while (it < a.n_work) {
