@@ -109,6 +109,7 @@ struct dfb_ctx {
   dfb::TileRec* d_recs = nullptr;
   float* d_var_partial = nullptr;   // with the accumulation: partial M2 sums of the units,
   float* d_deep_partial = nullptr;  // and of the row sort's groups
+  bool accum_ready = false;         // all of them, accum and m2 are there
   uint32_t* d_flag = nullptr;
   uint32_t* d_queue_ring = nullptr;  // kQueues x kSlots counters, finish counters, FrameState
   dfb::FrameState* d_state = nullptr;  // inside d_queue_ring
@@ -459,7 +460,7 @@ void build_work(dfb_ctx* h, const Shape& s) {
 // layout and launch shape, so that they stay where they are: graphs that the
 // caller captured hold their addresses.
 dfb_status ensure_accum(dfb_ctx* h) {
-  if (h->accum) return DFB_OK;  // allocated last
+  if (h->accum_ready) return DFB_OK;
   const size_t px = static_cast<size_t>(h->n_tiles) * h->P;
   size_t units = 0;
   for (const Shape& s : candidates(h->cfg, 0, 1))
@@ -468,12 +469,13 @@ dfb_status ensure_accum(dfb_ctx* h) {
   struct {
     float** p;
     size_t bytes;
-  } bufs[] = {{&h->m2, px * 12}, {&h->d_var_partial, units * 4}, {&h->d_deep_partial, groups * 4}, {&h->accum, px * 16}};
+  } bufs[] = {{&h->accum, px * 16}, {&h->m2, px * 12}, {&h->d_var_partial, units * 4}, {&h->d_deep_partial, groups * 4}};
   for (auto& b : bufs) {
     if (*b.p) continue;
     const dfb_status s = alloc_plain(h, reinterpret_cast<void**>(b.p), b.bytes);
     if (s != DFB_OK) return s;
   }
+  h->accum_ready = true;
   return DFB_OK;
 }
 
@@ -934,7 +936,7 @@ dfb_status frame_view(dfb_ctx* h, FrameView* v, bool want_denoised) {
   dfb_status s = check_usable(h);
   if (s != DFB_OK) return s;
   if (!v) return DFB_ERR_INVALID_ARG;
-  if (!h->accum || h->acc_n < 1) return fail(h, DFB_ERR_STATE, "no accumulated frame");
+  if (!h->accum_ready || h->acc_n < 1) return fail(h, DFB_ERR_STATE, "no accumulated frame");
   if (want_denoised && !h->denoised) {
     s = alloc_plain(h, reinterpret_cast<void**>(&h->denoised), static_cast<size_t>(h->n_tiles) * h->P * 16);
     if (s != DFB_OK) return s;
@@ -1299,7 +1301,7 @@ dfb_status dfb_composite_frame(dfb_handle h, uint32_t frame_flags) {
     if (!h->work_valid)
       return fail(h, DFB_ERR_STATE, "the first frame of a new layer layout chooses the launch shape "
                                     "(synchronously): composite it before capturing");
-    if (acc && !h->accum)
+    if (acc && !h->accum_ready)
       return fail(h, DFB_ERR_STATE, "accumulate one frame before capturing an accumulating frame");
     if (replay) return fail(h, DFB_ERR_INVALID_ARG, "DFB_REPLAY cannot be captured");
   }
@@ -1359,7 +1361,7 @@ dfb_status dfb_accumulate(dfb_handle h) {
   if (h->state != State::kComposited || !h->have_finished)
     return fail(h, DFB_ERR_STATE, "dfb_accumulate needs a frame composited with DFB_KEEP_FINISHED and without "
                                   "DFB_ACCUMULATE, not accumulated yet");
-  if (capturing(h) && !h->accum)
+  if (capturing(h) && !h->accum_ready)
     return fail(h, DFB_ERR_STATE, "accumulate one frame before capturing dfb_accumulate");
   s = ensure_accum(h);
   if (s != DFB_OK) return s;
