@@ -132,7 +132,7 @@ typedef struct {
   int32_t work_w, work_h, waves_per_tile;  /* the launch shape in use (after autotune) */
   int32_t accumulation_id;                 /* frames folded in since the last reset (read from
                                               the device: counts graph replays too) */
-  int32_t grid_size;                       /* persistent workgroups per frame */
+  int32_t grid_size;                       /* persistent workgroups of the frame's last launch */
   int64_t n_fragments;                     /* sum over tiles of layers * P */
 } dfb_info;
 
@@ -167,13 +167,14 @@ dfb_status dfb_destroy(dfb_handle h);
 dfb_status dfb_set_fragments(dfb_handle h, const void* frag_dev, int64_t n_blocks,
                              const dfb_layer* layers, int32_t n_layers, const int32_t* expected);
 
-/* Composite every tile of the frame in one persistent launch on the handle's
- * stream that takes tiles from a device work queue in longest-first order:
+/* Composite every tile of the frame on the handle's stream, in one persistent
+ * launch, or up to three where tiles have more than 32 layers, each taking
+ * tiles from a device work queue in longest-first order:
  * per pixel, sort the layers by (depth with NaN last and -0 == +0,
  * source_id), blend front to back with premultiplied "over", put the
  * background colour behind (Sec. 4.2, Listing 4).  With DFB_ACCUMULATE the
- * same launch folds the frame into the running mean (Welford) and writes the
- * display pixels of the mean, and a second, small launch combines its
+ * same launches fold the frame into the running mean (Welford) and write the
+ * display pixels of the mean, and a further, small launch combines their
  * per-unit sums into the per-tile variance of the mean; without it the
  * display pixels are those of this frame.
  * Tonemap: y = clamp(x,0,1) (NaN -> 0), colour ^ (1/gamma), code
@@ -185,7 +186,7 @@ dfb_status dfb_set_fragments(dfb_handle h, const void* frag_dev, int64_t n_block
  * Per-frame state (the work queue's counter slot, the accumulation count)
  * lives in device memory and is advanced by the frame's own kernels, so the
  * launches of one call are the same for every frame of a layer table:
- *  - DFB_REPLAY launches the frame as a replay of a HIP graph (frame kernel,
+ *  - DFB_REPLAY launches the frame as a replay of a HIP graph (frame kernels,
  *    then the variance combine of an accumulating frame) that the handle
  *    builds on first use for the current layer table, launch shape,
  *    fragment buffer and flags, and keeps (up to 8 buffers and flag sets)

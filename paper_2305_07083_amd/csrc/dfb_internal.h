@@ -8,8 +8,8 @@
 
 namespace dfb {
 
-// Layers per tile handled by the register sort; above it, the workgroup-wide
-// LDS sort takes over.
+// Layers per tile handled by the register sort; above it, the row sort and
+// the workgroup-wide LDS sort take over.
 constexpr int kRegMax = 32;
 // Layers per tile handled by the row sort (16 lanes of a wave sort a pixel in
 // registers); tiles with more, up to kMaxLayers, take the LDS sort.
@@ -126,7 +126,7 @@ struct FrameArgs {
   float* accum;                // [n_tiles][P][4]
   float* m2;                   // [n_tiles][3][P]
   float* tile_var;             // [n_tiles]
-  float* var_partial;          // [n_work] M2 sum of each unit (accumulating frames)
+  float* var_partial;          // [n_tiles * subs_per_tile] M2 sum of each unit (accumulating frames)
   float* deep_partial;         // [n_tiles * deep_subs] the same of the row-sort units
   void* final_out;             // RGBA8 uint32[n_tiles][P] or float4[n_tiles][P]
   uint16_t* order;             // [n_layers][P]

@@ -351,6 +351,9 @@ void drop_graphs(dfb_ctx* h);
 // pieces of every tile.  1500x1100 fp16 (67 such tiles, 768 workgroups), the
 // launch: fixed units of 128 pixels 106 us, of 64 112, of 32 123; runs of up to
 // 4 groups 101, 8 90, 16 89; 8192^2: 12.3 ms with 128 pixels, 12.1, 12.0, 11.9.
+// Both have counts that vary from tile to tile; where all tiles have 40 layers,
+// so that none is left to even out, runs take 5 to 8 % longer than fixed units of
+// 128 pixels.  A least run by layer count did not help there.
 constexpr int kDeepRun = 16;
 int deep_subs(int P) { return (P + dfb::kDeepPx - 1) / dfb::kDeepPx; }
 

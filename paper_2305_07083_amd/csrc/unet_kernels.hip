@@ -1566,7 +1566,7 @@ hipError_t launch_tile(const Map& x, const Map& x2, const uint16_t* w, const flo
 }
 
 // Rows of a one-tile convolution's tiles: 8, or 4 where 8 leave fewer than two
-// workgroups for each compute unit (8 x 128^2
+// workgroups for each of 256 compute units (8 x 128^2
 // step, all kernels: from 256 workgroups on 384 us, from 512 379, from 1024
 // 387).
 #ifndef DFB_TILE_MIN
@@ -1596,7 +1596,7 @@ hipError_t launch_tile_conv(const Map& x, const Map& x2, const uint16_t* w, int 
   return hipGetLastError();
 }
 // Output tiles from which a forward layer takes the persistent kernel: with
-// fewer, compute units are left without a workgroup, and the one-tile kernel's
+// fewer, some of 256 compute units are left without a workgroup, and the one-tile kernel's
 // 32-channel groups and 4-row tiles fill them (8 x 128^2 training: the seven
 // layers below it 104 -> 56 us; with 256 to 512 tiles the two are within a
 // microsecond).
@@ -1694,8 +1694,8 @@ hipError_t conv3x3_bwd(const Map& g, const uint16_t* w_dgrad, int ci, Adjoint ad
 }
 
 // Workgroups of the weight-gradient launch at most, per layer (rows of 64 x 64
-// channel groups included): the layers' shares of about 512, two for every
-// compute unit, by their tiles at the three resolutions and the cycles of a
+// channel groups included): the layers' shares of about 512, two for each of
+// 256 compute units, by their tiles at the three resolutions and the cycles of a
 // tile (its MFMAs, and as much again to stage it for the 32-channel layers).
 int wgrad_chunks(int layer, long long tiles) {
   static const int cap[kConvLayers] = {51, 51, 17, 27, 7, 7, 27, 27, 27, 70, 70, 51};
