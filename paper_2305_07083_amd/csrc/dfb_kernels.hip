@@ -1420,9 +1420,9 @@ frame_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off,
 //      the lanes and waves of a pixel in a fixed order
 // Every sum is split the same way whatever the launch shape is.
 //
-// Bound by vector instructions: about 110 a key (87 in the sort), at three
-// quarters of the issue slots; 20 bytes a fragment (fp32) are half of what
-// memory moves in that time.  The LDS sort it replaces for these counts was
+// Bound by vector instructions: 106 a key, padding keys among them (87 in the
+// sort), at 81 % of the issue slots on the 8192^2 frame below (fp16, 1500x1100:
+// 70 %); 20 bytes a fragment (fp32) are two thirds of what memory moves in that time.  The LDS sort it replaces for these counts was
 // bound by the latency of its passes at 8 waves a compute unit, and read each
 // 128-byte line twice.  8192^2 heavy-tailed frame (57.9 GB, up to 512 layers):
 // 36.9 -> 13.6 ms a frame; 1500x1100 fp16, up to 128 layers: 504 -> 148 us.

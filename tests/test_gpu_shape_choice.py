@@ -1,6 +1,6 @@
-"""Which frames choose a launch shape.  Choosing times every candidate (24 shapes
-or more, 10 frames each, with a synchronisation after each), so a frame that
-chooses takes over 200 times as long as one that does not, and one that does not
+"""Which frames choose a launch shape.  Choosing times every candidate (15 shapes
+of 64x64 tiles, 10 frames each, with a synchronisation after each), so a frame that
+chooses takes over 100 times as long as one that does not, and one that does not
 a few times as long at most: 20 separates them."""
 import time
 
