@@ -50,6 +50,7 @@ struct Shape {
   }
 };
 std::map<AutotuneKey, Shape> g_autotune_cache;
+std::mutex g_autotune_mu;  // handles of several threads share the cache
 
 }  // namespace
 
@@ -846,13 +847,18 @@ dfb_status autotune(dfb_ctx* h) {
                   h->cfg.tile_h,  h->cfg.frag_dtype, h->cfg.tile_op,      h->kcap,
                   layer_class(h->max_k), h->cfg.work_w, h->cfg.work_h, h->cfg.waves_per_tile, route};
   auto cands = candidates(h->cfg, h->max_k, route);
-  auto it = g_autotune_cache.find(key);
-  if (cands.size() == 1 || it != g_autotune_cache.end() || !shape_matters(h)) {
+  Shape known;
+  bool cached = false;
+  if (cands.size() > 1) {
+    std::lock_guard<std::mutex> lock(g_autotune_mu);
+    const auto it = g_autotune_cache.find(key);
+    if ((cached = it != g_autotune_cache.end())) known = it->second;
+  }
+  if (cands.size() == 1 || cached || !shape_matters(h)) {
     // without a choice to make, a stand-in that the cache does not keep: the
     // layouts of the class that have other tiles are timed
     if (cands.size() == 1) use_shape(h, cands[0]);
-    else if (it != g_autotune_cache.end()) use_shape(h, it->second);
-    else use_shape(h, cands[0], true);
+    else use_shape(h, cached ? known : cands[0], !cached);
     return DFB_OK;
   }
   hipEvent_t e0, e1;
@@ -886,7 +892,10 @@ dfb_status autotune(dfb_ctx* h) {
   }
   DFB_HIP(h, hipEventDestroy(e0));
   DFB_HIP(h, hipEventDestroy(e1));
-  g_autotune_cache[key] = best_s;
+  {
+    std::lock_guard<std::mutex> lock(g_autotune_mu);
+    g_autotune_cache[key] = best_s;
+  }
   use_shape(h, best_s);
   return DFB_OK;
 }
