@@ -1214,10 +1214,11 @@ dfb_status dfb_set_fragments(dfb_handle h, const void* frag_dev, int64_t n_block
   if (expected) h->last_expected.assign(expected, expected + h->n_tiles);
   h->work_valid = false;
   const int route = route_of(h);
-  if (!h->tuned[route].valid) {
+  for (int r : {0, 1}) {
     // fixed shapes skip the autotuner
-    auto c = candidates(h->cfg, max_k, route);
-    if (c.size() == 1) h->tuned[route] = {c[0], true, false};
+    if (h->tuned[r].valid || (r != route && h->P % 4 != 0)) continue;
+    auto c = candidates(h->cfg, max_k, r);
+    if (c.size() == 1) h->tuned[r] = {c[0], true, false};
   }
   // where only the other route's is known, a capture has that one to use
   if (h->tuned[route].valid || h->tuned[1 - route].valid) {

@@ -151,3 +151,29 @@ def test_buffers_of_both_alignments(dtype):
             c.composite()
             assert shapes[k] == (c.info().work_w, c.info().work_h, c.info().waves_per_tile)
             check(dfb, c, f)
+
+
+def test_fixed_units_captured_first():
+    """With the work unit and the waves given, a buffer off a 4-pixel boundary
+    leaves only the LDS sort's budget to choose (from 129 layers on); captured
+    before any frame, it takes the aligned buffer's."""
+    torch = torch_dev()
+    import paper_2305_07083_amd as dfb
+    f = frame([150, 3, 200, 40], 9, tile=32)
+    cfg = dfb.make_config(f.width, f.height, 32, work=32, waves=4, background=BG, fmt=dfb.DFB_FMT_RGBAF32)
+    raw = torch.zeros(f.frag.size + 1, dtype=torch.float32, device="cuda:0")
+    raw[1:].copy_(upload(f.frag).reshape(-1))
+    torch.cuda.synchronize()
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s), dfb.Compositor(cfg, s.cuda_stream) as c:
+        c.set_fragments(raw[1:], f.frag.shape[0], f.layers, f.expected)
+        s.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            c.composite()
+        for _ in range(3):
+            graph.replay()
+            s.synchronize()
+            check(dfb, c, f)
+        c.composite()
+        check(dfb, c, f)
