@@ -1422,10 +1422,11 @@ frame_kernel_t(FrameArgs args, const int32_t* __restrict__ tile_off,
 //
 // Bound by vector instructions: 106 a key, padding keys among them (87 in the
 // sort), at 81 % of the issue slots on the 8192^2 frame below (fp16, 1500x1100:
-// 70 %); 20 bytes a fragment (fp32) are two thirds of what memory moves in that time.  The LDS sort it replaces for these counts was
-// bound by the latency of its passes at 8 waves a compute unit, and read each
-// 128-byte line twice.  8192^2 heavy-tailed frame (57.9 GB, up to 512 layers):
-// 36.9 -> 13.6 ms a frame; 1500x1100 fp16, up to 128 layers: 504 -> 148 us.
+// 70 %); 20 bytes a fragment (fp32) are two thirds of what memory moves in that
+// time.  The LDS sort it replaces for these counts was bound by the latency of
+// its passes at 8 waves a compute unit, and read each 128-byte line twice.
+// 8192^2 heavy-tailed frame (57.9 GB, up to 512 layers): 36.9 -> 13.4 ms a frame;
+// 1500x1100 fp16, up to 128 layers: 504 -> 150 us.
 // Rows are 36 words apart: the 16 lanes of a pixel (at consecutive layers)
 // and the wave's 4 pixels hit all 64 banks once.
 constexpr int kDeepPitch = 36;
